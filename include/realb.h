@@ -212,10 +212,12 @@ int realb_grouped_moe_ffn_down(realb_ctx* ctx, int prec, const int32_t* expert_o
                                long long max_rows, const void* h_mid, const uint8_t* h_s,
                                const void* w2, const uint8_t* w2_s, void* y_rows, void* stream);
 
-/* Tuning hook for the grouped GEMMs' kernel: 0 = automatic (default: 16 where the output
- * width is a multiple of its tile -- I % 128 == 0 for gate/up, H % 256 == 0 for down -- else 2),
- * 16 = persistent 256x256 tiles fed by direct-to-LDS loads, 2 = register-staged 256x128
- * tiles with two blocks per CU, 8 = register-staged 256x256 tiles with one block per CU.
+/* Tuning hook for the grouped GEMMs' kernel: 0 = automatic (default: direct-to-LDS loads, tile
+ * shapes picked on the device from the expert segments), 16 = persistent 256x256 tiles fed by
+ * direct-to-LDS loads, 4 / 1 / 5 = the same with 128x256, 64x256 or 64x128 tiles (5 needs at least
+ * four K-steps: K >= 1024 on the FP4 path, K >= 256 on the BF16 path, else 1 is used),
+ * 2 = register-staged 256x128 tiles with two blocks per CU, 8 = register-staged 256x256 tiles with
+ * one block per CU (where the output width is a multiple of its tile, else 2).
  * Process-wide; outputs are bit-identical for every choice (the accumulation order along K
  * does not change).  REALB_EINVAL for any other value. */
 int realb_set_gemm_tile(int wn);

@@ -1,0 +1,235 @@
+// Device code shared by the grouped GEMM kernels of ffn.hip: kernel parameters, the MFMA step, the order of
+// weight rows inside a tile, the register epilogues and their stores, direct-to-LDS transfers.
+#pragma once
+#include "common.h"
+#include "mxfp4_device.h"
+#include <atomic>
+
+namespace realb {
+
+// Devices (bit = device index) on which a kernel instantiation has had its dynamic-LDS limit raised.
+inline bool first_use_on_device(std::atomic<unsigned long long>& seen, int device) {
+    const unsigned long long bit = 1ull << (device & 63);
+    return (seen.load(std::memory_order_acquire) & bit) == 0;
+}
+inline void mark_used_on_device(std::atomic<unsigned long long>& seen, int device) {
+    seen.fetch_or(1ull << (device & 63), std::memory_order_release);
+}
+
+typedef __attribute__((ext_vector_type(8))) int v8i_t;
+typedef __attribute__((ext_vector_type(16))) float v16f_t;
+typedef __attribute__((ext_vector_type(8))) __bf16 v8bf_t;
+typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
+
+struct GemmParams {
+    const uint8_t* A;        // activations: bf16 [rows,K] or fp4 codes [rows,K/2]
+    const uint8_t* As;       // fp4: scales [rows,K/32]
+    const uint8_t* W;        // weights: [n_local, w_rows, K] in the same encoding
+    const uint8_t* Ws;
+    uint8_t* out;            // gate/up: h (bf16 [rows,I] or codes [rows,I/2]); down: y bf16 [rows,H]
+    uint8_t* outs;           // gate/up fp4: h scales [rows,I/32]
+    const int32_t* offs;     // expert_offsets [n_local+1]
+    int n_local;
+    int K;                   // contraction length in elements
+    int w_rows;              // weight rows per expert (2I or H)
+    int n_out;               // output columns (I or H)
+    int n_tiles_n;           // column tiles (I/GC or H/BNW), register-staged kernel
+    const int32_t* row_src;  // gathering gate/up GEMM only: row_to_assign; row r's activations are A[row_src[r] / k]
+    uint32_t src_magic;      //   a / k == (a * src_magic) >> src_shift for 0 <= a < 2^31  (k = experts per token)
+    int src_shift;
+    int tile_mode;           // direct-to-LDS kernel: 0 = tile shapes chosen on the device, 4 / 2 / 1 = 256- / 128- / 64-row tiles of
+                             //   256 weight rows only, 5 = 64 x 128 tiles only
+};
+
+// Exact division of 0 <= a < 2^31 by a small constant k through one multiplication: with s = ceil(log2 k) and
+// m = floor(2^(31+s) / k) + 1 < 2^32, the excess m*k - 2^(31+s) is at most k <= 2^s, so a*m / 2^(31+s) exceeds
+// a/k by less than 1/k and the floors agree.
+inline void division_magic(int k, uint32_t* magic, int* shift) {
+    int s = 0;
+    while ((1 << s) < k) ++s;
+    *magic = (uint32_t)((1ull << (31 + s)) / (unsigned)k + 1);
+    *shift = 31 + s;
+}
+__device__ __forceinline__ int div_by_magic(int a, uint32_t magic, int shift) {
+    return (int)(((unsigned long long)(uint32_t)a * magic) >> shift);
+}
+
+// acc += W_tile (A operand, 32 weight rows) x X_tile^T (B operand, 32 activation rows)
+template <bool FP4, int OPSEL>
+__device__ __forceinline__ void mma(v16f_t& acc, const u32x4_t& w, const u32x4_t& x, int sw, int sx) {
+    if constexpr (FP4) {
+        v8i_t a8 = {(int)w.x, (int)w.y, (int)w.z, (int)w.w, 0, 0, 0, 0};
+        v8i_t b8 = {(int)x.x, (int)x.y, (int)x.z, (int)x.w, 0, 0, 0, 0};
+        acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a8, b8, acc, 4, 4, OPSEL, sw, OPSEL, sx);
+    } else {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf_t, w), __builtin_bit_cast(v8bf_t, x), acc, 0, 0, 0);
+    }
+}
+
+// two floats -> two BF16 (nearest even) in one dword, first in the low half
+__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
+    typedef __attribute__((ext_vector_type(2))) __bf16 bf2;
+    bf2 v = {(__bf16)lo, (__bf16)hi};
+    return __builtin_bit_cast(uint32_t, v);
+}
+
+// Weight row (within the expert) of row `br` of the block's weight tile.
+template <bool GATEUP, int GC>
+__device__ __forceinline__ int w_tile_row(int br, int n0, int I_up) {
+    if constexpr (GATEUP) return br < GC ? n0 + br : I_up + n0 + (br - GC);
+    else return n0 + br;
+}
+
+// LDS slot of weight-tile row br: inside each group of 32 rows, row 16h + 4g + q sits in slot
+// 8g + 4h + q.  MFMA output row i = 8g + 4h + q lands in lane half h, register 4g + q, so the
+// lane's 16 registers are weight rows 16h .. 16h+15 of the tile, in order.
+__device__ __forceinline__ int w_slot(int br) { return (br & ~31) | (((br >> 2) & 3) << 3) | (((br >> 4) & 1) << 2) | (br & 3); }
+// inverse: the weight-tile row that lane li (slot li) feeds to the MFMA
+__device__ __forceinline__ int w_row_of_lane(int li) { return (((li >> 2) & 1) << 4) | ((li >> 3) << 2) | (li & 3); }
+
+struct TileInfo {
+    int e;        // local expert
+    int row0;     // first activation row of the tile
+    int seg_hi;   // end of the expert's row segment
+    int n0;       // first output column of the tile
+};
+
+// BF16 outputs larger than what the memory-side cache would keep for the kernel that reads them next are
+// streamed past it with non-temporal stores (uniform per launch).
+__device__ __forceinline__ bool stream_output(const GemmParams& p) {
+    const long long rows = __builtin_amdgcn_readfirstlane(p.offs[p.n_local]);
+    return rows * p.n_out * 2 > (160ll << 20);
+}
+
+// Stores a 32-row x 32-column BF16 tile held as "lane (li, half) owns 16 consecutive columns of row li"
+// (c0 = its first 8 columns, c1 = the next 8).  Writing it as held would touch 32 rows with two
+// separate 16-byte pieces per instruction; a CU sustains only ~16 B/clk of such stores.  Neighbouring
+// lanes therefore swap halves (DPP quad permute), so that one instruction writes the even rows and the
+// next the odd rows, four lanes covering 64 contiguous bytes of a row: 16 rows per instruction, ~3x the
+// store rate measured.  `base` points at column 0 of tile row 0; rows >= rows_left are not written.
+// NT: non-temporal stores.  They drain faster, but the output then bypasses the memory-side cache, from
+// which the next kernel would otherwise read it back: worth it only for outputs too large to stay there.
+// Prepares the two store registers of store_tile_rows: ra = this lane's 16-byte piece of the even row of its
+// pair, rb = of the odd row.
+__device__ __forceinline__ void swap_halves(int lane, const u32x4_t& c0, const u32x4_t& c1, u32x4_t& ra, u32x4_t& rb) {
+    const bool odd = lane & 1;
+    const uint32_t a0[4] = {c0.x, c0.y, c0.z, c0.w}, a1[4] = {c1.x, c1.y, c1.z, c1.w};
+    uint32_t xa[4], xb[4];
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+        const uint32_t n0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)a0[d], 0xB1, 0xF, 0xF, true);   // the pair neighbour's c0
+        const uint32_t n1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)a1[d], 0xB1, 0xF, 0xF, true);   //                      c1
+        xa[d] = odd ? n1 : a0[d];          // even row of the pair: even lane gives its c0, odd lane the even lane's c1
+        xb[d] = odd ? a1[d] : n0;          // odd row of the pair:  even lane gives the odd lane's c0, odd lane its c1
+    }
+    ra = u32x4_t{xa[0], xa[1], xa[2], xa[3]};
+    rb = u32x4_t{xb[0], xb[1], xb[2], xb[3]};
+}
+template <bool NT>
+__device__ __forceinline__ void store16(uint8_t* dst, const u32x4_t& v, bool on) {
+    if constexpr (NT) {
+        if (on) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(dst));
+    } else {
+        if (on) *reinterpret_cast<u32x4_t*>(dst) = v;
+    }
+}
+template <bool NT>
+__device__ __forceinline__ void store_tile_rows(uint8_t* base, size_t row_pitch, int lane, int rows_left,
+                                                const u32x4_t& c0, const u32x4_t& c1) {
+    const int li = lane & 31, half = lane >> 5;
+    u32x4_t ra, rb;
+    swap_halves(lane, c0, c1, ra, rb);
+    const int row_a = li & ~1;
+    uint8_t* dst = base + (size_t)row_a * row_pitch + (half * 2 + (lane & 1)) * 16;
+    store16<NT>(dst, ra, row_a < rows_left);
+    store16<NT>(dst + row_pitch, rb, row_a + 1 < rows_left);
+}
+// Two neighbouring 32-column tiles of the same 32 rows (128 contiguous bytes per row).  The two 64-byte halves of
+// a row's line are written by consecutive instructions, so that they reach the memory side together (streamed
+// stores of half lines that arrive far apart cost extra write traffic).
+template <bool NT>
+__device__ __forceinline__ void store_tile_pair(uint8_t* base, size_t row_pitch, int lane, int rows_left, const u32x4_t& p0,
+                                                const u32x4_t& p1, const u32x4_t& q0, const u32x4_t& q1) {
+    const int li = lane & 31, half = lane >> 5;
+    u32x4_t pa, pb, qa, qb;
+    swap_halves(lane, p0, p1, pa, pb);
+    swap_halves(lane, q0, q1, qa, qb);
+    const int row_a = li & ~1;
+    uint8_t* dst = base + (size_t)row_a * row_pitch + (half * 2 + (lane & 1)) * 16;
+    store16<NT>(dst, pa, row_a < rows_left);
+    store16<NT>(dst + 64, qa, row_a < rows_left);
+    store16<NT>(dst + row_pitch, pb, row_a + 1 < rows_left);
+    store16<NT>(dst + row_pitch + 64, qb, row_a + 1 < rows_left);
+}
+
+// Epilogue of one 32-row tile of a wave, straight from registers.  a[t][r] belongs to activation row tile_row0 + li of the
+// block tile and to column 16*half + r of the wave's t-th 32-column tile (wn = the wave's place along the columns).
+// rows_valid = rows of the block tile that exist (may exceed the tile height).
+template <bool FP4, bool GATEUP, int WN, bool NT>
+__device__ __forceinline__ void epilogue_mt(const GemmParams& p, v16f_t (&a)[WN], int tile_row0, int row0, int rows_valid, int n0,
+                                            int wn, int li, int half) {
+    const int lane = half * 32 + li;
+    if constexpr (GATEUP) {
+        constexpr int HT = WN / 2;                     // h column tiles per wave
+        const int m = tile_row0 + li;
+        const bool valid = m < rows_valid;
+        const size_t grow = (size_t)(row0 + m);
+#pragma unroll
+        for (int t = 0; t < HT; ++t) {
+            const int ctile = n0 + wn * HT * 32 + t * 32;  // first h column of the 32-column tile
+            uint32_t hb[8];                                // 16 BF16 values: columns ctile + 16*half + 0..15
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const float g0 = a[t][2 * q], u0 = a[t + HT][2 * q];
+                const float g1 = a[t][2 * q + 1], u1 = a[t + HT][2 * q + 1];
+                hb[q] = pack_bf16x2(g0 * u0 * __builtin_amdgcn_rcpf(1.0f + __expf(-g0)),
+                                    g1 * u1 * __builtin_amdgcn_rcpf(1.0f + __expf(-g1)));
+            }
+            if constexpr (FP4) {
+                const u32x4_t v0 = {hb[0], hb[1], hb[2], hb[3]}, v1 = {hb[4], hb[5], hb[6], hb[7]};
+                uint32_t amax = max(amax_bits8(v0), amax_bits8(v1));
+                // the block's other 16 columns sit in lane^32: swapping the upper half of one copy with the lower half of
+                // another leaves {lo, lo} and {hi, hi}, whose maximum is the pair's -- one VALU instruction, no LDS round trip
+                const auto halves = __builtin_amdgcn_permlane32_swap(amax, amax, false, false);
+                amax = max(halves[0], halves[1]);
+                const uint32_t byte = e8m0_from_amax(amax);
+                const float scl = scale_operand(byte);
+                const u32x2_t codes = {encode8(v0, scl), encode8(v1, scl)};
+                if (valid) {
+                    *reinterpret_cast<u32x2_t*>(p.out + grow * (size_t)(p.n_out >> 1) + (ctile >> 1) + half * 8) = codes;
+                    if (half == 0) p.outs[scale_byte_offset((long long)grow, ctile >> 5, p.n_out >> 7)] = (uint8_t)byte;
+                }
+            } else {
+                store_tile_rows<NT>(p.out + ((size_t)(row0 + tile_row0) * p.n_out + ctile) * 2, (size_t)p.n_out * 2, lane,
+                                    rows_valid - tile_row0, u32x4_t{hb[0], hb[1], hb[2], hb[3]}, u32x4_t{hb[4], hb[5], hb[6], hb[7]});
+            }
+        }
+    } else {
+        auto lo8 = [&](int t) __attribute__((always_inline)) {
+            return u32x4_t{pack_bf16x2(a[t][0], a[t][1]), pack_bf16x2(a[t][2], a[t][3]),
+                           pack_bf16x2(a[t][4], a[t][5]), pack_bf16x2(a[t][6], a[t][7])};
+        };
+        auto hi8 = [&](int t) __attribute__((always_inline)) {
+            return u32x4_t{pack_bf16x2(a[t][8], a[t][9]), pack_bf16x2(a[t][10], a[t][11]),
+                           pack_bf16x2(a[t][12], a[t][13]), pack_bf16x2(a[t][14], a[t][15])};
+        };
+        static_assert(WN % 2 == 0, "column tiles are stored in pairs");
+#pragma unroll
+        for (int t = 0; t < WN; t += 2) {
+            const int col0 = n0 + wn * WN * 32 + t * 32;
+            store_tile_pair<NT>(p.out + ((size_t)(row0 + tile_row0) * p.n_out + col0) * 2, (size_t)p.n_out * 2, lane,
+                                rows_valid - tile_row0, lo8(t), hi8(t), lo8(t + 1), hi8(t + 1));
+        }
+    }
+}
+
+__device__ __forceinline__ void lds_dma16(const uint8_t* g, uint8_t* l) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                     (__attribute__((address_space(3))) void*)l, 16, 0, 0);
+}
+__device__ __forceinline__ void lds_dma4(const uint32_t* g, uint8_t* l) {
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g,
+                                     (__attribute__((address_space(3))) void*)l, 4, 0, 0);
+}
+
+}  // namespace realb

@@ -323,6 +323,49 @@ def test_ffn_other_block_tiles_give_the_same_rows(R, case, tile):
             assert np.array_equal(R.scales_to_canonical(b.h_s, Rr, case.cfg.I), ref_hs)
 
 
+@pytest.mark.parametrize("H,I,segments", [
+    (384, 384, [1, 0, 63, 64, 65]),                 # H an odd multiple of 128: half a column tile at the end of the down GEMM
+    (1024, 128, [127, 128, 129, 0, 255]),           # one column tile of h; K of the down GEMM shorter than the stages hold
+    (128, 1152, [256, 257, 511, 3, 0]),             # one K-step
+    (2048, 1408, [700, 1500, 40, 1, 300]),          # whole rounds of 256-row tiles and a remainder; a half K-step (FP4, K = 1408)
+    (256, 256, [0, 0, 0, 0, 0]),
+])
+def test_tile_shapes_give_the_same_rows(R, H, I, segments):
+    """Every tile shape of the direct-to-LDS kernel, and the shapes it picks by itself, on segment lengths at the edges of
+    the tiles: bit-identical to the register-staged kernel (same accumulation order along K), both precisions; rows
+    behind the last one stay unwritten."""
+    from paper_2604_19503_amd.binding import default_config, set_gemm_tile
+    nl, rows = len(segments), sum(segments)
+    rcfg = default_config(max(rows, 1), nl, 1, 1, H, I)
+    ctx = R.Context(rcfg)
+    b = R.LayerBuffers(rcfg, max(rows, 1))
+    gen = torch.Generator(device="cuda"); gen.manual_seed(H + I)
+    rnd = lambda std, *shape: (torch.randn(shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    x, w13, w2 = rnd(1.0, b.max_rows, H), rnd(0.02, nl, 2 * I, H), rnd(0.02, nl, H, I)
+    b.expert_offsets.copy_(torch.from_numpy(np.concatenate([[0], np.cumsum(segments)]).astype(np.int32)))
+    b.x_perm.copy_(x)
+    xq, xs = R.quantize_rows_fp4(x)
+    b.x_q.copy_(xq); b.x_s.view(-1).copy_(xs.view(-1))
+    ctx.quantize_experts_fp4(w13, w2, b)
+    for prec in (R.BF16, R.FP4):
+        ref = None
+        for tile in (2, 0, 16, 4, 1, 5):
+            _say(f"tile shapes H={H} I={I} prec={prec} tile={tile}")
+            b.y_rows.fill_(float("nan"))
+            try:
+                set_gemm_tile(tile)
+                ctx.grouped_moe_ffn(prec, w13, w2, b)
+                _sync()
+            finally:
+                set_gemm_tile(0)
+            got = b.y_rows.view(torch.int16).clone()
+            if ref is None:
+                ref = got
+                assert bool(torch.isfinite(b.y_rows[:rows].float()).all()) and bool(torch.isnan(b.y_rows[rows:].float()).all())
+            assert torch.equal(got, ref), tile
+    ctx.close()
+
+
 # ---------------------------------------------------------------------------- whole layer
 @pytest.mark.parametrize("force", [0, 1])
 def test_layer_forward_matches_step_calls_and_is_deterministic(R, case, force):
