@@ -80,7 +80,7 @@ int realb_destroy(realb_ctx* ctx);
 const char* realb_last_error(void);
 
 /* Device memory, in bytes, that realb_create allocates for this configuration (the permutation's per-chunk
- * counters and the routing kernel's per-block partial histograms); besides it a context holds 24*D bytes of
+ * counters and the routing kernel's per-block partial histograms); besides it a context holds 24*D + 8 bytes of
  * pinned host memory, one stream and its events.  Host-only, no GPU needed; 0 for an unsupported shape
  * (realb_last_error says why). */
 size_t realb_workspace_bytes(const realb_config* cfg);
@@ -235,19 +235,18 @@ typedef struct {
     const float* logits; const uint8_t* is_vision; const void* x; int T;
     const void* w13; const void* w2;            /* this rank's BF16 expert weights */
     int rank; int force;
-    int overlap;                                /* weight encoding: 0 = on `stream`, 1 = on the context's side stream,
+    int overlap;                                /* weight encoding: 0 and 1 = by this call, in the launches of its own routing and
+                                                       index kernels (from the first one on if the precision is known up front,
+                                                       else from the one that knows the decision; 0 and 1 no longer differ),
                                                    2 = skipped (w13_q .. w2_s already hold this layer's encoded weights),
-                                                   3 = speculative (realb_layer_forward only): W13's is issued on the side
-                                                       stream BEFORE routing, so that it fills the wait for the host's
-                                                       decision, W2's on `stream` once the decision is FP4; W13's is
-                                                       unused if the decision is BF16 (in modes 3 and 4 the activations
-                                                       of all T tokens are encoded there ahead of the decision as well),
+                                                   3 = speculative (realb_layer_forward only): like 1, but W13's goes beside the
+                                                       routing kernel, ahead of the decision, and is unused if that is BF16,
                                                    4 = prefetched: w13_q .. w2_s are being filled by the previous call's
                                                        cross-layer prefetch (see next_w13 below); the GEMMs wait for it */
     long long max_rows;
     /* cross-layer prefetch (optional, all NULL / 0 to disable): the NEXT layer's BF16 weights and the buffers that
-       receive their FP4 encoding.  The encoder for them is issued on the context's side stream right behind this
-       layer's gate/up GEMM launch and runs beside this layer's two GEMMs, which leave `reserve_cus` compute units
+       receive their FP4 encoding.  The encoder for them is issued on the context's side stream once this layer's
+       gate/up GEMM has started and runs beside this layer's two GEMMs, which leave `reserve_cus` compute units
        free for it (their persistent grids shrink by that many blocks).  The next call then passes those buffers as
        w13_q .. w2_s with overlap = 4.  The buffers must differ from this call's w13_q .. w2_s. */
     const void* next_w13; const void* next_w2;
@@ -270,16 +269,20 @@ typedef struct {
  * index, scales tiled by token index -- instead of one per permuted row.  realb_permute itself always
  * produces the permuted rows described above.) */
 
-/* Runs the whole path for one rank on `stream`: route_stats -> select_precision
- * (host decision: the calling thread spins until the routing statistics, which a kernel on `stream` writes to
- * host-coherent pinned memory, have arrived -- so the call returns only after everything that preceded it on `stream`
- * and its own routing kernels have run; an error of the stream ends the wait) -> [FP4 only: quantize_experts_fp4, on the
- * context's side stream when io->overlap, concurrent with] permute ->
- * grouped_moe_ffn -> combine.  The side stream is joined before the GEMMs.
+/* Runs the whole path for one rank on `stream`: route_stats -> select_precision -> [FP4 only: quantize_experts_fp4,
+ * concurrent with] permute -> grouped_moe_ffn -> combine.
+ * Everything is enqueued without waiting for the host: where the precision is not known up front (forced, or the LB gate
+ * closed), the kernels behind the routing evaluate the policy on the device from the routing statistics.  The calling thread
+ * then spins until the statistics, which a kernel on `stream` writes to host-coherent pinned memory, have arrived, and
+ * evaluates the same policy for prec_host, ib_global and M_after -- so the call returns only after everything that preceded
+ * it on `stream` and its own routing kernels have run; an error of the stream ends the wait.  (Batches whose token matrix
+ * exceeds 4 GiB, a forced GEMM kernel other than 16, and calls without FP4 buffers whose decision is open do wait for the
+ * decision before the rest is launched.)
  * With next_w13 set, the next layer's weights are encoded on the side stream beside this layer's GEMMs
  * (cross-layer form of the overlapping pipeline of Sec. "Overhead-Aware Pipeline Orchestration": the
  * GEMMs are compute-bound and leave the memory system idle, as the dispatch does in the paper); that
- * encoding is joined by the NEXT call (overlap = 4), or by realb_prefetch_join. */
+ * encoding is joined by the NEXT call (overlap = 4), or by realb_prefetch_join.  Such a call launches its GEMMs when the
+ * statistics are there, and returns when the gate/up GEMM has started. */
 int realb_layer_forward(realb_ctx* ctx, realb_layer_io* io, void* stream);
 
 /* Runs permute .. combine for one rank with a precision already decided and
@@ -290,9 +293,10 @@ int realb_rank_forward(realb_ctx* ctx, realb_layer_io* io, int prec, void* strea
  * realb_rank_forward record timing events on the caller's stream at their stage boundaries (a few
  * microseconds of overhead per call, so leave it off when timing whole steps); realb_stage_ms waits for
  * the last call and returns, in milliseconds, how long each stage of THAT call took on the GPU:
- *   [0] route_stats  [1] permutation indices (realb_layer_forward interleaves the two groups of kernels and reports
- *   their sum under [0])  [2] host decision + weight encoding on the caller's stream
- *   [3] gather / activation encoding, incl. any wait for the side stream's encoders  [4] gate/up GEMM  [5] down GEMM  [6] combine
+ *   [0] route_stats, permutation indices and the encoding that rides along in their launches (realb_layer_forward)
+ *   [1] permutation indices and encoding (realb_rank_forward)  [2] encoding in launches of its own
+ *   [3] permuted copy of the rows, where the gate/up GEMM cannot fetch them itself; any wait for a prefetch
+ *   [4] gate/up GEMM  [5] down GEMM  [6] combine
  * (realb_rank_forward: [0] holds only the few microseconds between two markers).  ms_host receives
  * REALB_N_STAGES floats.  REALB_EINVAL if timing is off or no call has been made since it was switched on. */
 enum { REALB_N_STAGES = 7 };

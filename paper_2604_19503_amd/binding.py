@@ -320,8 +320,8 @@ class Context:
 
     def make_io(self, logits, is_vision, x, w13, w2, b: LayerBuffers, rank: int, force: int = FORCE_NONE,
                 overlap=True) -> LayerIO:
-        """overlap: 0/False = weight encoding on the call's stream, 1/True = on the context's side stream,
-        2 = skipped (the buffers already hold this layer's encoded weights), 3 = speculative (before routing),
+        """overlap: 0/False, 1/True = weight encoding in the launches of the call's routing and index kernels,
+        2 = skipped (the buffers already hold this layer's encoded weights), 3 = speculative (W13 ahead of the decision),
         4 = prefetched by the previous call (see set_prefetch)."""
         io = LayerIO()
         g = lambda t: None if t is None else t.data_ptr()

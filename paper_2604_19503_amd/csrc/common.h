@@ -13,6 +13,7 @@ constexpr int kPermChunk = 256;    // assignments ranked by one wave in permute
 // Smallest group of chunks that one block of the permutation's count and rank kernels handles (the workspace holds one
 // per-expert sum per group).
 constexpr int kPermGroup = 4;
+constexpr int kTopkThreads = 1024;     // block size of the routing kernel
 constexpr int kRouteBlocksMax = 512;   // most blocks the routing kernel is launched with (two per CU on 256 CUs)
 
 struct Ctx {
@@ -30,9 +31,11 @@ struct Ctx {
     int32_t* stats_host;   // [2*D]: rank loads, rank vision loads (copy target of realb_select_precision)
     unsigned long long* stats_words;   // [2*D], host-coherent: the same, written by the layer call's reduce block, each word
                                        // tagged with the call's sequence number (see hist_reduce_body)
+    unsigned long long* start_word;    // behind them: c->start_seq once the gate/up GEMM of a prefetching call has started
+    int start_seq;
     int stats_seq;         // sequence number of the last layer call's statistics (never 0)
-    hipStream_t side;      // side stream for the weight encoder
-    hipEvent_t ev_fork, ev_join;
+    hipStream_t side;      // side stream for the cross-layer prefetch
+    hipEvent_t ev_fork;    // orders a rank call's prefetch behind the work before its GEMMs
     hipEvent_t ev_prefetch;   // end of the last cross-layer prefetch on the side stream
     bool prefetch_pending;    // ev_prefetch has been recorded and not yet been waited for by a caller's stream
     int gemm_reserve;         // compute units the grouped GEMMs' persistent grids leave free (set around a prefetching call)
@@ -46,20 +49,23 @@ void set_error(const char* fmt, ...);
 // Waits until the reduce block launched on `s` has written the statistics tagged `seq` to stats_words, then evaluates the policy.
 int select_precision_pinned(Ctx* c, int T, int force, int32_t* prec_host, double* ib_global_host, double* M_after_host,
                             int seq, hipStream_t s);
-int permute_indices(Ctx* c, const int32_t* topk_ids, int T, int rank, long long max_rows, int32_t* expert_offsets,
-                    int32_t* row_to_assign, int32_t* assign_to_row, hipStream_t s);
-int launch_gate_up_bf16_gather(Ctx* c, const int32_t* expert_offsets, int n_local, long long max_rows, const void* x, int T,
-                               const int32_t* row_to_assign, const void* w13, void* h_mid, hipStream_t s);
 bool gate_up_gather_supported(const Ctx* c, int T, bool fp4);
-int launch_gate_up_fp4_gather(Ctx* c, const int32_t* expert_offsets, int n_local, long long max_rows, const uint8_t* x_q,
-                              const uint8_t* x_s, int T, const int32_t* row_to_assign, const uint8_t* w13_q,
-                              const uint8_t* w13_s, uint8_t* h_q, uint8_t* h_s, hipStream_t s);
-int route_topk_only(Ctx* c, const float* logits, const uint8_t* is_vision, int T, int32_t* topk_ids, float* topk_w, hipStream_t s);
-int route_and_index(Ctx* c, const float* logits, const uint8_t* is_vision, int T, int rank, long long max_rows, int32_t* topk_ids,
-                    float* topk_w, int32_t* expert_cnt, int32_t* expert_vis, int32_t* rank_load, int32_t* rank_vis,
-                    int32_t* expert_offsets, int32_t* row_to_assign, int32_t* assign_to_row, int stats_seq, hipStream_t s);
+struct SideJobs;           // encode_device.h
+struct PrecisionSource;
+PrecisionSource precision_source(const Ctx* c, int T, int force, int rank, const int32_t* rank_load, const int32_t* rank_vis);
+// The layer call's two GEMMs, in the precision `prec` says or will say (gate/up: rows fetched through row_to_assign).
+int launch_layer_gate_up(Ctx* c, const PrecisionSource& prec, const realb_layer_io* io, bool announce, hipStream_t s);
+int launch_layer_down(Ctx* c, const PrecisionSource& prec, const realb_layer_io* io, hipStream_t s);
+int perm_block_threads(int T, int k);
+// Waits until the gate/up GEMM that was launched with start_seq has started.
+int wait_for_gemm_start(Ctx* c, hipStream_t s);
+int permute_indices(Ctx* c, const int32_t* topk_ids, int T, int rank, long long max_rows, int32_t* expert_offsets,
+                    int32_t* row_to_assign, int32_t* assign_to_row, const SideJobs& beside_count, const SideJobs& beside_rank, hipStream_t s);
+int route_topk_only(Ctx* c, const float* logits, const uint8_t* is_vision, int T, int32_t* topk_ids, float* topk_w, const SideJobs& jobs,
+                    int* per_block, int32_t** rank_part, hipStream_t s);
+int route_and_index(Ctx* c, const realb_layer_io* io, int stats_seq, const SideJobs& beside_topk, const SideJobs& beside_finish, hipStream_t s);
 int permute_gather(Ctx* c, const void* x, const int32_t* assign_to_row, int T, int prec, void* x_perm, uint8_t* x_q,
-                   uint8_t* x_s, hipStream_t s, int token_major);
+                   uint8_t* x_s, hipStream_t s);
 // BF16 -> MXFP4 encoder on one matrix [rows0, K0], or two when rows1 > 0, in a single launch.
 int launch_quantize_flat(const void* src0, long long rows0, int K0, uint8_t* q0, uint8_t* s0,
                          const void* src1, long long rows1, int K1, uint8_t* q1, uint8_t* s1, hipStream_t stream);

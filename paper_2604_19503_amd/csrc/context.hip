@@ -1,7 +1,7 @@
 // Context, error reporting and the host-side precision policy.
-#include "common.h"
-#include "mxfp4_device.h"
+#include "encode_device.h"
 #include <string.h>
+#include <chrono>
 #include <new>
 
 namespace realb {
@@ -42,6 +42,25 @@ static size_t wave_cnt_bytes(const realb_config* c) {      // chunk counts, then
 }
 static size_t hist_part_bytes(const realb_config* c) { return (size_t)kRouteBlocksMax * 2 * c->E * sizeof(int32_t); }
 
+static double aimd_update(const realb_config& c, double M, bool congested) {
+    if (congested) return c.aimd_mul * M;
+    return M + c.aimd_add > 1.0 ? 1.0 : M + c.aimd_add;
+}
+
+// The policy of a layer call whose statistics are still on the device: fixed if the host knows the outcome (forced, or the
+// LB gate is closed), else the rule with M as the AIMD update will leave it in either case.
+PrecisionSource precision_source(const Ctx* c, int T, int force, int rank, const int32_t* rank_load, const int32_t* rank_vis) {
+    PrecisionSource p{};
+    p.fixed = force != REALB_FORCE_NONE ? force : (long long)T > c->cfg.Gamma ? -1 : REALB_BF16;
+    p.rank = rank;
+    p.rank_load = rank_load;
+    p.rank_vis = rank_vis;
+    const bool updated = c->cfg.aimd_enabled && c->cfg.update_first;
+    p.rule = PolicyRule{c->cfg.C, updated ? aimd_update(c->cfg, c->M, true) : c->M, updated ? aimd_update(c->cfg, c->M, false) : c->M,
+                        c->cfg.tau, (double)((long long)T * c->cfg.k), c->cfg.D};
+    return p;
+}
+
 // Precision policy (paper Sec. "Real-time Modality-aware LB Scheduling" and "LB
 // Gate").  Ratios are never formed: IB_d > C is load_d*D > C*(T*k), IB_global >
 // tau is max_load*D > tau*(T*k), R_vd > M is vis_d > M*load_d, each side in double.
@@ -61,25 +80,43 @@ static void policy(const realb_config& c, const int32_t* load, const int32_t* vi
         for (int d = 0; d < D; ++d) prec[d] = REALB_BF16;
         return;
     }
-    double M = *M_inout, M_new = M;
-    if (c.aimd_enabled) {
-        const bool congested = max_ld > c.tau * total;
-        if (congested) M_new = c.aimd_mul * M;
-        else { M_new = M + c.aimd_add; if (M_new > 1.0) M_new = 1.0; }
-    }
+    const double M = *M_inout;
+    const double M_new = !c.aimd_enabled ? M : aimd_update(c, M, policy_congested(max_load, D, c.tau, total));
     const double M_dec = c.update_first ? M_new : M;
-    for (int d = 0; d < D; ++d) {
-        const bool hot = (double)((long long)load[d] * D) > c.C * total;
-        const bool vision_heavy = (double)vis[d] > M_dec * (double)load[d];
-        prec[d] = (hot && vision_heavy && load[d] > 0) ? REALB_FP4 : REALB_BF16;
-    }
+    for (int d = 0; d < D; ++d) prec[d] = policy_fp4(load[d], vis[d], D, c.C, M_dec, total) ? REALB_FP4 : REALB_BF16;
     *M_inout = M_new;
 }
 
+// Spins until arrived() says that words which a kernel on `s` writes to host-coherent memory are there.  Twenty times a
+// second it also asks the stream: a stream that has drained (or failed) without the words arriving ends the wait with an
+// error instead of a hang.  (Not more often: hipStreamQuery puts a marker behind whatever is enqueued, which costs the
+// stream 6-8 us -- and the layer call polls with its whole layer enqueued.)
+template <typename F>
+static int poll_words(const F& arrived, hipStream_t s, const char* lost) {
+    auto asked = std::chrono::steady_clock::now();
+    for (unsigned spin = 1; !arrived(); ++spin) {
+        if ((spin & 0xFFF) == 0 && std::chrono::steady_clock::now() - asked > std::chrono::milliseconds(50)) {
+            asked = std::chrono::steady_clock::now();
+            const hipError_t q = hipStreamQuery(s);
+            if (q == hipSuccess) {                        // everything enqueued has run: the words must be there now
+                REALB_REQUIRE(arrived(), REALB_EHIP, "%s", lost);
+                break;
+            }
+            if (q != hipErrorNotReady) REALB_HIP(q);
+            (void)hipGetLastError();                      // (not-ready is no error of this call)
+        }
+        __builtin_ia32_pause();
+    }
+    return REALB_OK;
+}
+
+int wait_for_gemm_start(Ctx* c, hipStream_t s) {
+    return poll_words([&] { return __atomic_load_n(c->start_word, __ATOMIC_ACQUIRE) == (unsigned long long)c->start_seq; }, s,
+                      "the gate/up GEMM never announced itself");
+}
+
 // Policy on the pinned host copy of the statistics.  The reduce block of the kernel launched on `s` writes them as
-// 64-bit words whose upper halves carry `seq`; the host polls until every word shows it.  Every few thousand polls it
-// also asks the stream: a stream that has drained (or failed) without the words arriving ends the wait with an
-// error instead of a hang.
+// 64-bit words whose upper halves carry `seq`; the host polls until every word shows it.
 int select_precision_pinned(Ctx* c, int T, int force, int32_t* prec_host, double* ib_global_host, double* M_after_host,
                             int seq, hipStream_t s) {
     const int n = 2 * c->cfg.D;
@@ -91,17 +128,8 @@ int select_precision_pinned(Ctx* c, int T, int force, int32_t* prec_host, double
         }
         return true;
     };
-    for (unsigned spin = 1; !arrived(); ++spin) {
-        if ((spin & 0xFFF) == 0) {
-            const hipError_t q = hipStreamQuery(s);
-            if (q == hipSuccess) {                        // everything enqueued has run: the words must be there now
-                REALB_REQUIRE(arrived(), REALB_EHIP, "routing statistics never reached the host");
-                break;
-            }
-            if (q != hipErrorNotReady) REALB_HIP(q);
-        }
-        __builtin_ia32_pause();
-    }
+    const int rc = poll_words(arrived, s, "routing statistics never reached the host");
+    if (rc != REALB_OK) return rc;
     policy(c->cfg, c->stats_host, c->stats_host + c->cfg.D, T, force, &c->M, prec_host, ib_global_host);
     if (M_after_host) *M_after_host = c->M;
     return REALB_OK;
@@ -133,7 +161,7 @@ int realb_create(const realb_config* cfg, realb_ctx** out) {
     c->cfg = *cfg;
     c->n_local = cfg->E / cfg->D;
     c->M = cfg->M_init;
-    c->wave_cnt = nullptr; c->group_cnt = nullptr; c->hist_part = nullptr; c->stats_host = nullptr; c->stats_words = nullptr; c->side = nullptr; c->ev_fork = nullptr; c->ev_join = nullptr; c->stats_seq = 0; c->ev_prefetch = nullptr; c->prefetch_pending = false; c->gemm_reserve = 0; c->stage_timing = false; c->stage_valid = false;
+    c->wave_cnt = nullptr; c->group_cnt = nullptr; c->hist_part = nullptr; c->stats_host = nullptr; c->stats_words = nullptr; c->side = nullptr; c->ev_fork = nullptr; c->stats_seq = 0; c->start_seq = 0; c->start_word = nullptr; c->ev_prefetch = nullptr; c->prefetch_pending = false; c->gemm_reserve = 0; c->stage_timing = false; c->stage_valid = false;
     for (auto& ev : c->stage_ev) ev = nullptr;
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&c->num_cus, hipDeviceAttributeMultiprocessorCount, c->device);
@@ -142,11 +170,11 @@ int realb_create(const realb_config* cfg, realb_ctx** out) {
     if (e == hipSuccess) c->group_cnt = c->wave_cnt + (size_t)c->n_chunks_max * c->n_local;
     if (e == hipSuccess) e = hipMalloc((void**)&c->hist_part, hist_part_bytes(cfg));
     if (e == hipSuccess) e = hipHostMalloc((void**)&c->stats_host, 2 * cfg->D * sizeof(int32_t), hipHostMallocDefault);
-    if (e == hipSuccess) e = hipHostMalloc((void**)&c->stats_words, 2 * cfg->D * sizeof(unsigned long long), hipHostMallocCoherent);
-    if (e == hipSuccess) memset(c->stats_words, 0, 2 * cfg->D * sizeof(unsigned long long));
+    if (e == hipSuccess) e = hipHostMalloc((void**)&c->stats_words, (2 * cfg->D + 1) * sizeof(unsigned long long), hipHostMallocCoherent);
+    if (e == hipSuccess) memset(c->stats_words, 0, (2 * cfg->D + 1) * sizeof(unsigned long long));
+    if (e == hipSuccess) c->start_word = c->stats_words + 2 * cfg->D;
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_fork, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_join, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_prefetch, hipEventDisableTiming);
     if (e != hipSuccess) {
         realb_destroy(reinterpret_cast<realb_ctx*>(c));
@@ -170,7 +198,6 @@ int realb_destroy(realb_ctx* ctx) {
     if (c->stats_host) (void)hipHostFree(c->stats_host);
     if (c->stats_words) (void)hipHostFree(c->stats_words);
     if (c->ev_fork) (void)hipEventDestroy(c->ev_fork);
-    if (c->ev_join) (void)hipEventDestroy(c->ev_join);
     if (c->ev_prefetch) (void)hipEventDestroy(c->ev_prefetch);
     for (auto& ev : c->stage_ev)
         if (ev) (void)hipEventDestroy(ev);

@@ -24,6 +24,7 @@
 // Tiles never straddle experts; row tails are clamped on load and masked on
 // store.  expert_offsets is read on the device, so no host round trip.
 #include "ffn_device.h"
+#include "encode_device.h"
 
 namespace realb {
 
@@ -679,8 +680,9 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 // there they are used only when they hold all rows.  64 x 128 tiles need at least four K-steps: their producer may run
 // five steps ahead, and a tile's gather entries are fetched one tile ahead.
 template <bool FP4, bool GATEUP, bool GATHER>
-__global__ void __launch_bounds__(512, 1) ffn_tile_kernel(const GemmParams p) {
-    extern __shared__ __align__(16) uint8_t smem[];
+__device__ __forceinline__ void tile_body(const GemmParams& p, uint8_t* smem) {
+    if (p.start_word && blockIdx.x == 0 && threadIdx.x == 0)
+        __hip_atomic_store(p.start_word, (unsigned long long)p.start_seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const int lane = threadIdx.x & 63;
     int lo = 0, hi = 0;
     if (lane < p.n_local) { lo = p.offs[lane]; hi = p.offs[lane + 1]; }
@@ -714,27 +716,60 @@ __global__ void __launch_bounds__(512, 1) ffn_tile_kernel(const GemmParams p) {
     }
 }
 
+template <bool FP4, bool GATEUP, bool GATHER>
+__global__ void __launch_bounds__(512, 1) ffn_tile_kernel(const GemmParams p) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    tile_body<FP4, GATEUP, GATHER>(p, smem);
+}
+
+// The same, in the precision that the routing statistics will ask for: launched before the host knows it, so that the GPU
+// does not idle while the host waits for the statistics, decides and launches.
+template <bool GATEUP, bool GATHER>
+__global__ void __launch_bounds__(512, 1) ffn_tile_either_kernel(const GemmParams bf16, const GemmParams fp4, const PrecisionSource prec) {
+    extern __shared__ __align__(16) uint8_t smem[];
+    if (precision_is_fp4(prec)) tile_body<true, GATEUP, GATHER>(fp4, smem);
+    else tile_body<false, GATEUP, GATHER>(bf16, smem);
+}
+
+// One persistent block per CU, a multiple of 8 (XCDs); a prefetching layer call leaves some CUs to the weight encoder.
+static unsigned tile_grid(const GemmParams& p, bool gate_up, long long max_rows, const Ctx* c) {
+    const long long narrowest = gate_up ? p.n_out / 64 : p.n_out / 128;    // column tiles of the narrowest shape
+    const long long total_max = ((max_rows + 63) / 64 + p.n_local) * narrowest;
+    const long long avail = (long long)c->num_cus - c->gemm_reserve;
+    const long long slots = avail >= 16 ? 8ll * (c->gemm_reserve > 0 ? avail / 8 : (avail + 7) / 8) : 8;
+    return (unsigned)(total_max < slots ? 8 * ((total_max + 7) / 8) : slots);
+}
+constexpr size_t max_size(size_t a, size_t b) { return a > b ? a : b; }
+constexpr size_t kTileLds = max_size(TileGeo<4, 256>::LDS_BYTES, max_size(TileGeo<2, 256>::LDS_BYTES, TileGeo<1, 128>::LDS_BYTES));
+static_assert(TileGeo<1, 256>::LDS_BYTES <= kTileLds && kTileLds <= 160 * 1024, "LDS");
+
+template <typename K>
+static int raise_lds_limit(K kernel, std::atomic<unsigned long long>& seen, const Ctx* c) {
+    if (first_use_on_device(seen, c->device)) {                     // (setting it twice from two threads is harmless)
+        REALB_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
+        mark_used_on_device(seen, c->device);
+    }
+    return REALB_OK;
+}
+
 // mode: GemmParams::tile_mode
 template <bool FP4, bool GATEUP, bool GATHER>
 static int launch_tile(GemmParams p, long long max_rows, const Ctx* c, hipStream_t s, int mode) {
     p.tile_mode = mode;
-    const int nt = GATEUP ? p.n_out / 64 : p.n_out / 128;           // column tiles of the narrowest shape
-    constexpr size_t lds_a = TileGeo<4, 256>::LDS_BYTES, lds_b = TileGeo<2, 256>::LDS_BYTES, lds_c = TileGeo<1, 128>::LDS_BYTES;
-    constexpr size_t lds = lds_a > lds_b ? (lds_a > lds_c ? lds_a : lds_c) : (lds_b > lds_c ? lds_b : lds_c);
-    static_assert(TileGeo<1, 256>::LDS_BYTES <= lds && lds <= 160 * 1024, "LDS");
-    static std::atomic<unsigned long long> attr_seen{0};            // per instantiation, one bit per device
-    if (first_use_on_device(attr_seen, c->device)) {                // (setting it twice from two threads is harmless)
-        REALB_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&ffn_tile_kernel<FP4, GATEUP, GATHER>),
-                                      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024));
-        mark_used_on_device(attr_seen, c->device);
-    }
-    const long long m_tiles_max = (max_rows + 63) / 64 + p.n_local;
-    const long long total_max = m_tiles_max * nt;
-    // one persistent block per CU, a multiple of 8 (XCDs); a prefetching layer call leaves some CUs to the weight encoder
-    const long long avail = (long long)c->num_cus - c->gemm_reserve;
-    const long long slots = avail >= 16 ? 8ll * (c->gemm_reserve > 0 ? avail / 8 : (avail + 7) / 8) : 8;
-    const long long grid = total_max < slots ? 8 * ((total_max + 7) / 8) : slots;
-    hipLaunchKernelGGL((ffn_tile_kernel<FP4, GATEUP, GATHER>), dim3((unsigned)grid), dim3(512), lds, s, p);
+    static std::atomic<unsigned long long> seen{0};                 // per instantiation, one bit per device
+    const int rc = raise_lds_limit(&ffn_tile_kernel<FP4, GATEUP, GATHER>, seen, c);
+    if (rc != REALB_OK) return rc;
+    hipLaunchKernelGGL((ffn_tile_kernel<FP4, GATEUP, GATHER>), dim3(tile_grid(p, GATEUP, max_rows, c)), dim3(512), kTileLds, s, p);
+    REALB_HIP(hipGetLastError());
+    return REALB_OK;
+}
+template <bool GATEUP, bool GATHER>
+static int launch_tile_either(GemmParams b, GemmParams f, const PrecisionSource& prec, long long max_rows, const Ctx* c, hipStream_t s, int mode) {
+    b.tile_mode = f.tile_mode = mode;
+    static std::atomic<unsigned long long> seen{0};
+    const int rc = raise_lds_limit(&ffn_tile_either_kernel<GATEUP, GATHER>, seen, c);
+    if (rc != REALB_OK) return rc;
+    hipLaunchKernelGGL((ffn_tile_either_kernel<GATEUP, GATHER>), dim3(tile_grid(b, GATEUP, max_rows, c)), dim3(512), kTileLds, s, b, f, prec);
     REALB_HIP(hipGetLastError());
     return REALB_OK;
 }
@@ -777,37 +812,40 @@ static int launch_gemm(const GemmParams& p, long long max_rows, const Ctx* c, hi
     return launch_gemm_geo<FP4, GATEUP, 2, 2, 2>(p, max_rows, c, s);
 }
 
-static int gather_tile_mode() { return g_tile.load(std::memory_order_relaxed) == 16 ? 4 : 0; }
+static int layer_tile_mode() { return g_tile.load(std::memory_order_relaxed) == 16 ? 4 : 0; }
 
-// Whether the gathering gate/up GEMM below applies (kernel selection, 32-bit row offsets).
+// Whether the layer call's gate/up GEMM can fetch its activation rows from the token matrix (kernel selection, 32-bit row
+// offsets); if not, the caller materialises the permuted rows and uses the plain GEMMs.
 bool gate_up_gather_supported(const Ctx* c, int T, bool fp4) {
     const long long bytes = (long long)T * c->cfg.H * (fp4 ? 1 : 4) / 2;
     const int forced = g_tile.load(std::memory_order_relaxed);
-    return (forced == 0 || forced == 16) && c->cfg.I % 128 == 0 && T > 0 && bytes < (1ll << 32);
+    return (forced == 0 || forced == 16) && T > 0 && bytes < (1ll << 32);
 }
 
-// BF16 gate/up GEMM that gathers its activation rows from the token matrix x [T,H] through row_to_assign
-// (the permutation's gather fused into the GEMM's loads).  Returns REALB_ESHAPE if this shape or the
-// selected kernel cannot do it; the caller then materialises the permuted rows and uses the plain GEMM.
-int launch_gate_up_bf16_gather(Ctx* c, const int32_t* expert_offsets, int n_local, long long max_rows, const void* x, int T,
-                               const int32_t* row_to_assign, const void* w13, void* h_mid, hipStream_t s) {
+// Gate/up GEMM of a layer call: activation rows come from x [T,H], or from the tokens' codes and scales (row index = token
+// index), through row_to_assign.
+int launch_layer_gate_up(Ctx* c, const PrecisionSource& prec, const realb_layer_io* io, bool announce, hipStream_t s) {
     const int H = c->cfg.H, I = c->cfg.I;
-    if (!gate_up_gather_supported(c, T, false)) return REALB_ESHAPE;
-    GemmParams g{(const uint8_t*)x, nullptr, (const uint8_t*)w13, nullptr, (uint8_t*)h_mid, nullptr, expert_offsets, n_local,
-                 H, 2 * I, I, 0, row_to_assign, 0, 0, 0};
-    division_magic(c->cfg.k, &g.src_magic, &g.src_shift);
-    return launch_tile<false, true, true>(g, max_rows, c, s, gather_tile_mode());
+    GemmParams b{(const uint8_t*)io->x, nullptr, (const uint8_t*)io->w13, nullptr, (uint8_t*)io->h_mid, nullptr, io->expert_offsets, c->n_local,
+                 H, 2 * I, I, 0, io->row_to_assign, 0, 0, nullptr, 0, 0};
+    division_magic(c->cfg.k, &b.src_magic, &b.src_shift);
+    if (announce) { b.start_word = c->start_word; b.start_seq = c->start_seq; }
+    GemmParams f = b;
+    f.A = io->x_q; f.As = io->x_s; f.W = io->w13_q; f.Ws = io->w13_s; f.outs = io->h_s;
+    if (prec.fixed < 0) return launch_tile_either<true, true>(b, f, prec, io->max_rows, c, s, layer_tile_mode());
+    return prec.fixed == REALB_FP4 ? launch_tile<true, true, true>(f, io->max_rows, c, s, layer_tile_mode())
+                                   : launch_tile<false, true, true>(b, io->max_rows, c, s, layer_tile_mode());
 }
 
-// The same for the FP4 path: x_q / x_s hold one encoded row per TOKEN (row index = token index).
-int launch_gate_up_fp4_gather(Ctx* c, const int32_t* expert_offsets, int n_local, long long max_rows, const uint8_t* x_q,
-                              const uint8_t* x_s, int T, const int32_t* row_to_assign, const uint8_t* w13_q,
-                              const uint8_t* w13_s, uint8_t* h_q, uint8_t* h_s, hipStream_t s) {
+int launch_layer_down(Ctx* c, const PrecisionSource& prec, const realb_layer_io* io, hipStream_t s) {
     const int H = c->cfg.H, I = c->cfg.I;
-    if (!gate_up_gather_supported(c, T, true)) return REALB_ESHAPE;
-    GemmParams g{x_q, x_s, w13_q, w13_s, h_q, h_s, expert_offsets, n_local, H, 2 * I, I, 0, row_to_assign, 0, 0, 0};
-    division_magic(c->cfg.k, &g.src_magic, &g.src_shift);
-    return launch_tile<true, true, true>(g, max_rows, c, s, gather_tile_mode());
+    GemmParams b{(const uint8_t*)io->h_mid, nullptr, (const uint8_t*)io->w2, nullptr, (uint8_t*)io->y_rows, nullptr, io->expert_offsets, c->n_local,
+                 I, H, H, 0, nullptr, 0, 0, nullptr, 0, 0};
+    GemmParams f = b;
+    f.As = io->h_s; f.W = io->w2_q; f.Ws = io->w2_s;
+    if (prec.fixed < 0) return launch_tile_either<false, false>(b, f, prec, io->max_rows, c, s, layer_tile_mode());
+    return prec.fixed == REALB_FP4 ? launch_tile<true, false, false>(f, io->max_rows, c, s, layer_tile_mode())
+                                   : launch_tile<false, false, false>(b, io->max_rows, c, s, layer_tile_mode());
 }
 
 }  // namespace realb
@@ -835,8 +873,8 @@ static int ffn_stages(realb_ctx* ctx, int prec, int stages, const int32_t* exper
                   "NULL scale tensor on the FP4 path");
     const int H = c->cfg.H, I = c->cfg.I;
     hipStream_t s = as_stream(stream);
-    GemmParams g1{(const uint8_t*)x, x_s, (const uint8_t*)w13, w13_s, (uint8_t*)h_mid, h_s, expert_offsets, n_local, H, 2 * I, I, 0, nullptr, 0, 0, 0};
-    GemmParams g2{(const uint8_t*)h_mid, h_s, (const uint8_t*)w2, w2_s, (uint8_t*)y_rows, nullptr, expert_offsets, n_local, I, H, H, 0, nullptr, 0, 0, 0};
+    GemmParams g1{(const uint8_t*)x, x_s, (const uint8_t*)w13, w13_s, (uint8_t*)h_mid, h_s, expert_offsets, n_local, H, 2 * I, I, 0, nullptr, 0, 0, nullptr, 0, 0};
+    GemmParams g2{(const uint8_t*)h_mid, h_s, (const uint8_t*)w2, w2_s, (uint8_t*)y_rows, nullptr, expert_offsets, n_local, I, H, H, 0, nullptr, 0, 0, nullptr, 0, 0};
     int rc = REALB_OK;
     if (prec == REALB_FP4) {
         if (s1) rc = launch_gemm<true, true>(g1, max_rows, c, s);

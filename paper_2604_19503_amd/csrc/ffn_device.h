@@ -37,6 +37,8 @@ struct GemmParams {
     const int32_t* row_src;  // gathering gate/up GEMM only: row_to_assign; row r's activations are A[row_src[r] / k]
     uint32_t src_magic;      //   a / k == (a * src_magic) >> src_shift for 0 <= a < 2^31  (k = experts per token)
     int src_shift;
+    unsigned long long* start_word;   // host-coherent, or NULL: the kernel's first block writes start_seq there
+    int start_seq;
     int tile_mode;           // direct-to-LDS kernel: 0 = tile shapes chosen on the device, 4 / 2 / 1 = 256- / 128- / 64-row tiles of
                              //   256 weight rows only, 5 = 64 x 128 tiles only
 };

@@ -34,12 +34,12 @@ __device__ __forceinline__ void hist_reduce_body(int32_t* tot, const int32_t* __
         const int col = c < n_local ? d * n_local + c : E + d * n_local + (c - n_local);
         int sum = 0;
         int b = slice;
-        for (; b + 31 * n_slices < n_part; b += 32 * n_slices) {       // 32 independent loads in flight per thread
-            int v[32];
+        for (; b + 15 * n_slices < n_part; b += 16 * n_slices) {       // 16 independent loads in flight per thread
+            int v[16];
 #pragma unroll
-            for (int i = 0; i < 32; ++i) v[i] = hist_part[(size_t)(b + i * n_slices) * pitch + col];
+            for (int i = 0; i < 16; ++i) v[i] = hist_part[(size_t)(b + i * n_slices) * pitch + col];
 #pragma unroll
-            for (int i = 0; i < 32; ++i) sum += v[i];
+            for (int i = 0; i < 16; ++i) sum += v[i];
         }
         for (; b < n_part; b += n_slices) sum += hist_part[(size_t)b * pitch + col];
         if (sum) atomicAdd(&tot[c], sum);

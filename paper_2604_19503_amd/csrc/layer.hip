@@ -1,11 +1,14 @@
 // The rank layer end to end: the paper's four-stage pipeline (Sec. "System
 // Overview") with the weight transformation overlapped with other work
-// (Sec. "Overhead-Aware Pipeline Orchestration"): the encoders run on the
-// context's side stream -- after the decision beside the permutation, ahead of
-// the decision beside the routing and index kernels, or, for the NEXT layer's
-// weights, beside this layer's GEMMs -- and are joined before the kernels that
-// read their output.
-#include "common.h"
+// (Sec. "Overhead-Aware Pipeline Orchestration"): the encoders ride along in the
+// launches of the routing and permutation kernels, which are bound by latency
+// and leave the memory system idle, or, for the NEXT layer's weights, run on the
+// context's side stream beside this layer's GEMMs.
+//
+// A layer call does not wait for the host between its kernels: where the precision is not known up front (forced, or the
+// LB gate closed), the encoders and GEMMs evaluate the policy on the device from the routing statistics.  The host waits
+// for the statistics last, with everything enqueued, and then evaluates the same rule for its results.
+#include "encode_device.h"
 
 using namespace realb;
 
@@ -29,114 +32,141 @@ static int validate_io(const Ctx* c, const realb_layer_io* io) {
     return REALB_OK;
 }
 
-// quant_in_flight: the weight encoding was already issued on the side stream (speculative mode);
-// act_in_flight: so was the FP4 encoding of every token's activations (one row per token, the form the
-// gathering gate/up GEMM reads); ev_join marks the end of both.  indices_done: the permutation's index
-// kernels are already on the stream.
-static int rank_forward_steps(realb_ctx* ctx, realb_layer_io* io, int prec, void* stream, bool quant_in_flight, bool act_in_flight,
-                              bool indices_done, bool* forked, bool* prefetched) {
+static bool fp4_buffers(const realb_layer_io* io) {
+    return io->w13_q && io->w13_s && io->w2_q && io->w2_s && io->x_q && io->x_s && io->h_s;
+}
+
+// Parts of the encoding work of a layer call, as side jobs for launches with blocks of `threads` threads.
+static int add_w13(const Ctx* c, const realb_layer_io* io, int threads, SideJobs* jobs) {
+    return add_quant_tensor(&jobs->w, io->w13, (long long)c->n_local * 2 * c->cfg.I, c->cfg.H, io->w13_q, io->w13_s, threads);
+}
+static int add_w2(const Ctx* c, const realb_layer_io* io, int threads, SideJobs* jobs) {
+    return add_quant_tensor(&jobs->w, io->w2, (long long)c->n_local * c->cfg.H, c->cfg.I, io->w2_q, io->w2_s, threads);
+}
+static void add_tokens(const Ctx* c, const realb_layer_io* io, int threads, SideJobs* jobs) {
+    jobs->x = TokenJob{(const u32x4_t*)io->x, io->topk_ids, (uint32_t*)io->x_q, io->x_s, io->T, c->cfg.k, c->cfg.H / 8,
+                       io->rank * c->n_local, c->n_local, (unsigned)ceil_div(io->T, threads / 64)};
+}
+
+// Makes `s` wait for the pending cross-layer prefetch.  An event that has completed is not waited for: a wait costs the
+// stream microseconds even then, and by the time a call's statistics have arrived the previous call's prefetch has ended.
+static int join_prefetch(Ctx* c, hipStream_t s) {
+    if (!c->prefetch_pending) return REALB_OK;
+    const hipError_t q = hipEventQuery(c->ev_prefetch);
+    if (q != hipSuccess) {
+        (void)hipGetLastError();                          // (not-ready is no error of this call)
+        REALB_HIP(hipStreamWaitEvent(s, c->ev_prefetch, 0));
+    }
+    c->prefetch_pending = false;
+    return REALB_OK;
+}
+
+// The next layer's weights, on the side stream.  The caller has made sure that the buffers' readers (the previous call's
+// GEMMs) are done or waited for.
+static int issue_prefetch(Ctx* c, const realb_layer_io* io) {
+    const int rc = launch_quantize_flat(io->next_w13, (long long)c->n_local * 2 * c->cfg.I, c->cfg.H, io->next_w13_q, io->next_w13_s,
+                                        io->next_w2, (long long)c->n_local * c->cfg.H, c->cfg.I, io->next_w2_q, io->next_w2_s, c->side);
+    REALB_HIP(hipEventRecord(c->ev_prefetch, c->side));
+    c->prefetch_pending = true;
+    return rc;
+}
+
+// gate/up, down and combine of a layer call whose activations (and weights, FP4) are in place.
+// prefetch: what starts the next layer's encoder -- ON_START: the host, when it sees the gate/up GEMM start; ON_EVENT: an
+// event in front of that GEMM (for calls that do not wait for the GPU).
+enum class Prefetch { NONE, ON_START, ON_EVENT };
+static int gemms_and_combine(realb_ctx* ctx, realb_layer_io* io, const PrecisionSource& prec, Prefetch prefetch, void* stream) {
+    Ctx* c = reinterpret_cast<Ctx*>(ctx);
+    hipStream_t s = as_stream(stream);
+    struct ReserveReset { Ctx* c; ~ReserveReset() { c->gemm_reserve = 0; } } reserve_reset{c};
+    if (prefetch != Prefetch::NONE) {
+        c->gemm_reserve = io->reserve_cus;
+        c->start_seq = c->start_seq >= 0x7FFFFFFF ? 1 : c->start_seq + 1;
+    }
+    if (prefetch == Prefetch::ON_EVENT) REALB_HIP(hipEventRecord(c->ev_fork, s));
+    stage_mark(c, s, 4);
+    int rc = launch_layer_gate_up(c, prec, io, prefetch == Prefetch::ON_START, s);
+    if (rc != REALB_OK) return rc;
+    stage_mark(c, s, 5);
+    if (prefetch == Prefetch::ON_EVENT) {
+        REALB_HIP(hipStreamWaitEvent(c->side, c->ev_fork, 0));
+        rc = issue_prefetch(c, io);
+        if (rc != REALB_OK) return rc;
+    }
+    rc = launch_layer_down(c, prec, io, s);
+    if (rc != REALB_OK) return rc;
+    stage_mark(c, s, 6);
+    rc = realb_combine(ctx, io->y_rows, io->assign_to_row, io->topk_w, io->T, io->out, stream);
+    if (rc != REALB_OK) return rc;
+    stage_mark(c, s, 7);
+    c->stage_valid = c->stage_timing;
+    if (prefetch != Prefetch::ON_START) return REALB_OK;
+    // The next layer's encoder is launched when the gate/up GEMM has started (a word that its first block writes): earlier it
+    // would compete with this layer's own encoding for the memory the GEMM leaves idle, and an event to order the two would
+    // cost the caller's stream microseconds.
+    rc = wait_for_gemm_start(c, s);
+    return rc != REALB_OK ? rc : issue_prefetch(c, io);
+}
+
+// permute .. combine in a precision the host knows; indices_done: the permutation's index kernels are already on the stream.
+static int rank_forward_steps(realb_ctx* ctx, realb_layer_io* io, int prec, void* stream, bool indices_done) {
     REALB_REQUIRE(ctx && io, REALB_EINVAL, "NULL argument");
     Ctx* c = reinterpret_cast<Ctx*>(ctx);
     REALB_REQUIRE(prec == REALB_BF16 || prec == REALB_FP4, REALB_EINVAL, "bad precision %d", prec);
     hipStream_t s = as_stream(stream);
-    int rc;
-    const bool fp4 = prec == REALB_FP4;
-    const bool side = io->overlap == 1 || quant_in_flight;
-    // everything that can be refused is checked before any work goes to the side stream
-    rc = validate_io(c, io);
+    // everything that can be refused is checked before anything is enqueued
+    int rc = validate_io(c, io);
     if (rc != REALB_OK) return rc;
-    if (fp4) REALB_REQUIRE(io->w13_q && io->w13_s && io->w2_q && io->w2_s && io->x_q && io->x_s && io->h_s, REALB_EINVAL, "NULL FP4 buffer");
-    const bool prefetch = io->next_w13 != nullptr;       // cross-layer prefetch of the NEXT layer's weights, beside this layer's GEMMs
-    // weights encoded by the previous call's prefetch: everything this call enqueues from here on comes after it.
-    // With the activations in flight on the side stream no wait of its own is needed (each cross-stream wait costs the
-    // caller's stream microseconds): their encoding was issued behind that prefetch on the same stream, and this call
-    // waits for it (ev_join) whatever the precision (the next prefetch goes to that same stream, behind both).
-    if (c->prefetch_pending && (io->overlap == 4 || prefetch)) {
-        if (!act_in_flight) REALB_HIP(hipStreamWaitEvent(s, c->ev_prefetch, 0));
-        c->prefetch_pending = false;
-    }
-    const bool encoded = io->overlap == 2 || io->overlap == 4;
-    auto issue_prefetch = [&]() -> int {                  // called right behind the launch of the first GEMM
-        if (!prefetch) return REALB_OK;
-        REALB_HIP(hipStreamWaitEvent(c->side, c->ev_fork, 0));
-        *prefetched = true;
-        const int prc = realb_quantize_experts_fp4(ctx, io->next_w13, io->next_w2, c->n_local, io->next_w13_q, io->next_w13_s,
-                                                   io->next_w2_q, io->next_w2_s, c->side);
-        REALB_HIP(hipEventRecord(c->ev_prefetch, c->side));
-        c->prefetch_pending = true;
-        return prc;
-    };
-    const bool encode_now = fp4 && !encoded && !quant_in_flight;
-    if (encode_now && side) {
-        REALB_HIP(hipEventRecord(c->ev_fork, s));
-        REALB_HIP(hipStreamWaitEvent(c->side, c->ev_fork, 0));
-        *forked = true;                                  // from here on an error return must still join the side stream
-        rc = realb_quantize_experts_fp4(ctx, io->w13, io->w2, c->n_local, io->w13_q, io->w13_s, io->w2_q, io->w2_s, c->side);
-        REALB_HIP(hipEventRecord(c->ev_join, c->side));
+    const bool fp4 = prec == REALB_FP4;
+    if (fp4) REALB_REQUIRE(fp4_buffers(io), REALB_EINVAL, "NULL FP4 buffer");
+    const bool prefetch = io->next_w13 != nullptr;
+    const bool encode_weights = fp4 && io->overlap != 2 && io->overlap != 4;
+    const bool gather = gate_up_gather_supported(c, io->T, fp4);
+    if (io->overlap == 4 || prefetch) {                   // weights encoded by the previous call's prefetch, or its buffers reused
+        rc = join_prefetch(c, s);
         if (rc != REALB_OK) return rc;
     }
+    // FP4: the encoding rides along with the index kernels -- W13 beside the counting, tokens and W2 beside the ranking
+    const int threads = indices_done ? kSideThreads : perm_block_threads(io->T, c->cfg.k);
+    PrecisionSource known{};
+    known.fixed = prec;
+    SideJobs first{}, second{};
+    first.when = second.when = known;
+    if (encode_weights) {
+        rc = add_w13(c, io, threads, &first);
+        if (rc == REALB_OK) rc = add_w2(c, io, threads, &second);
+        if (rc != REALB_OK) return rc;
+    }
+    if (fp4 && gather) add_tokens(c, io, threads, &second);
     if (!indices_done) {
         stage_mark(c, s, 0);
         stage_mark(c, s, 1);
         rc = permute_indices(c, io->topk_ids, io->T, io->rank, io->max_rows, io->expert_offsets, io->row_to_assign,
-                             io->assign_to_row, s);
-        if (rc != REALB_OK) return rc;
+                             io->assign_to_row, first, second, s);
         stage_mark(c, s, 2);
-    }
-    if (encode_now && !side) {
-        rc = realb_quantize_experts_fp4(ctx, io->w13, io->w2, c->n_local, io->w13_q, io->w13_s, io->w2_q, io->w2_s, stream);
-        if (rc != REALB_OK) return rc;
-    }
-    stage_mark(c, s, 3);
-    // Where the gate/up GEMM can fetch its rows through row_to_assign, the permuted copy of the activations is
-    // not materialised: BF16 rows come straight from x; FP4 rows from codes and scales written once per TOKEN.
-    const bool gather = io->row_to_assign && io->x && gate_up_gather_supported(c, io->T, fp4);
-    if ((fp4 && !(act_in_flight && gather)) || !gather) {
-        rc = permute_gather(c, io->x, io->assign_to_row, io->T, prec, io->x_perm, io->x_q, io->x_s, s, gather ? 1 : 0);
-        if (rc != REALB_OK) return rc;
-    }
-    // speculative mode: what went to the side stream ahead of the decision is what the gate/up GEMM needs (activations, W13);
-    // W2 is encoded here, on the caller's stream, while that is still in flight -- the caller's stream would idle until the join
-    // anyway, a BF16 decision never pays for it, and the down GEMM then needs no second cross-stream wait (each costs microseconds).
-    if (fp4 && quant_in_flight) {
-        rc = launch_quantize_flat(io->w2, (long long)c->n_local * c->cfg.H, c->cfg.I, io->w2_q, io->w2_s, nullptr, 0, 0, nullptr, nullptr, s);
-        if (rc != REALB_OK) return rc;
-    }
-    if (fp4 && ((side && !encoded) || act_in_flight)) REALB_HIP(hipStreamWaitEvent(s, c->ev_join, 0));
-    if (prefetch) {
-        REALB_HIP(hipEventRecord(c->ev_fork, s));         // the prefetch may start once the stream is here, beside the GEMMs
-        c->gemm_reserve = io->reserve_cus;
-    }
-    struct ReserveReset { Ctx* c; ~ReserveReset() { c->gemm_reserve = 0; } } reserve_reset{c};
-    stage_mark(c, s, 4);                              // (behind the joins: waiting for the side stream counts as stage [3])
-    if (gather) {
-        REALB_REQUIRE(io->h_mid && io->w2 && io->y_rows, REALB_EINVAL, "NULL argument");
-        if (fp4) {
-            REALB_REQUIRE(io->x_q && io->x_s && io->h_s, REALB_EINVAL, "NULL argument");
-            rc = launch_gate_up_fp4_gather(c, io->expert_offsets, c->n_local, io->max_rows, io->x_q, io->x_s, io->T,
-                                           io->row_to_assign, io->w13_q, io->w13_s, (uint8_t*)io->h_mid, io->h_s, s);
-        } else {
-            REALB_REQUIRE(io->w13 != nullptr, REALB_EINVAL, "NULL argument");
-            rc = launch_gate_up_bf16_gather(c, io->expert_offsets, c->n_local, io->max_rows, io->x, io->T, io->row_to_assign,
-                                            io->w13, io->h_mid, s);
-        }
-        if (rc != REALB_OK) return rc;
-        stage_mark(c, s, 5);
-        rc = issue_prefetch();
-        if (rc != REALB_OK) return rc;
-        rc = realb_grouped_moe_ffn_down(ctx, prec, io->expert_offsets, c->n_local, io->max_rows, io->h_mid, fp4 ? io->h_s : nullptr,
-                                        fp4 ? (const void*)io->w2_q : io->w2, fp4 ? io->w2_s : nullptr, io->y_rows, stream);
-    } else if (fp4) {
-        rc = realb_grouped_moe_ffn(ctx, prec, io->expert_offsets, c->n_local, io->max_rows, io->x_q, io->x_s, io->w13_q,
-                                   io->w13_s, io->w2_q, io->w2_s, io->h_mid, io->h_s, io->y_rows, stream);
     } else {
-        rc = realb_grouped_moe_ffn(ctx, prec, io->expert_offsets, c->n_local, io->max_rows, io->x_perm, nullptr, io->w13,
-                                   nullptr, io->w2, nullptr, io->h_mid, nullptr, io->y_rows, stream);
+        rc = launch_side_jobs(first, s);
+        if (rc == REALB_OK) rc = launch_side_jobs(second, s);
     }
     if (rc != REALB_OK) return rc;
-    if (!gather) {
-        stage_mark(c, s, 5);                             // (the two GEMMs went out in one call: their time is reported under [4])
-        rc = issue_prefetch();
+    stage_mark(c, s, 3);
+    if (gather) return gemms_and_combine(ctx, io, known, prefetch ? Prefetch::ON_EVENT : Prefetch::NONE, stream);
+    // rows the gate/up GEMM cannot fetch through row_to_assign: the permuted copy, then the plain GEMMs
+    rc = permute_gather(c, io->x, io->assign_to_row, io->T, prec, io->x_perm, io->x_q, io->x_s, s);
+    if (rc != REALB_OK) return rc;
+    stage_mark(c, s, 4);
+    if (fp4)
+        rc = realb_grouped_moe_ffn(ctx, prec, io->expert_offsets, c->n_local, io->max_rows, io->x_q, io->x_s, io->w13_q,
+                                   io->w13_s, io->w2_q, io->w2_s, io->h_mid, io->h_s, io->y_rows, stream);
+    else
+        rc = realb_grouped_moe_ffn(ctx, prec, io->expert_offsets, c->n_local, io->max_rows, io->x_perm, nullptr, io->w13,
+                                   nullptr, io->w2, nullptr, io->h_mid, nullptr, io->y_rows, stream);
+    if (rc != REALB_OK) return rc;
+    stage_mark(c, s, 5);                                 // (the two GEMMs went out in one call: their time is reported under [4])
+    if (prefetch) {                                      // its buffers' last readers come before this point of the stream
+        REALB_HIP(hipEventRecord(c->ev_fork, s));
+        REALB_HIP(hipStreamWaitEvent(c->side, c->ev_fork, 0));
+        rc = issue_prefetch(c, io);
         if (rc != REALB_OK) return rc;
     }
     stage_mark(c, s, 6);
@@ -144,33 +174,26 @@ static int rank_forward_steps(realb_ctx* ctx, realb_layer_io* io, int prec, void
     if (rc != REALB_OK) return rc;
     stage_mark(c, s, 7);
     c->stage_valid = c->stage_timing;
-    // a speculative encoding that was not used still has to end before the caller's stream moves on
-    if ((quant_in_flight || act_in_flight) && !fp4) REALB_HIP(hipStreamWaitEvent(s, c->ev_join, 0));
     return REALB_OK;
 }
 
-// Runs the steps; if one of them fails while the weight encoder is in flight on the side stream, the caller's
-// stream is still made to wait for it, so that the caller may free or reuse the FP4 weight buffers after its
-// stream has drained, whatever this call returned.
-static int rank_forward_impl(realb_ctx* ctx, realb_layer_io* io, int prec, void* stream, bool quant_in_flight, bool act_in_flight,
-                             bool indices_done) {
-    bool forked = quant_in_flight || act_in_flight, prefetched = false;
-    const int rc = rank_forward_steps(ctx, io, prec, stream, quant_in_flight, act_in_flight, indices_done, &forked, &prefetched);
-    if (rc != REALB_OK && ctx) {
-        Ctx* c = reinterpret_cast<Ctx*>(ctx);
-        if (forked) (void)hipStreamWaitEvent(as_stream(stream), c->ev_join, 0);
-        if (prefetched) { (void)hipStreamWaitEvent(as_stream(stream), c->ev_prefetch, 0); c->prefetch_pending = false; }
+// If a step fails while a prefetch is in flight on the side stream, the caller's stream is still made to wait for it, so
+// that the caller may free or reuse the buffers after its stream has drained, whatever the call returned.
+static int joined_on_error(Ctx* c, int rc, void* stream) {
+    if (rc != REALB_OK && c && c->prefetch_pending) {
+        (void)hipStreamWaitEvent(as_stream(stream), c->ev_prefetch, 0);
+        c->prefetch_pending = false;
     }
     return rc;
 }
 
 extern "C" int realb_rank_forward(realb_ctx* ctx, realb_layer_io* io, int prec, void* stream) {
-    return rank_forward_impl(ctx, io, prec, stream, false, false, false);
+    return joined_on_error(reinterpret_cast<Ctx*>(ctx), rank_forward_steps(ctx, io, prec, stream, false), stream);
 }
 
-extern "C" int realb_layer_forward(realb_ctx* ctx, realb_layer_io* io, void* stream) {
-    REALB_REQUIRE(ctx && io, REALB_EINVAL, "NULL argument");
+static int layer_forward_steps(realb_ctx* ctx, realb_layer_io* io, void* stream) {
     Ctx* c = reinterpret_cast<Ctx*>(ctx);
+    hipStream_t s = as_stream(stream);
     // Everything that can be refused is checked before anything is enqueued.
     int rc = validate_io(c, io);
     if (rc != REALB_OK) return rc;
@@ -178,57 +201,67 @@ extern "C" int realb_layer_forward(realb_ctx* ctx, realb_layer_io* io, void* str
                   "bad force value %d", io->force);
     REALB_REQUIRE(io->expert_cnt && io->expert_vis && io->rank_load && io->rank_vis, REALB_EINVAL, "NULL argument");
     REALB_REQUIRE(io->T == 0 || (io->logits && io->is_vision), REALB_EINVAL, "NULL argument");
-    if (io->force == REALB_FP4)
-        REALB_REQUIRE(io->w13_q && io->w13_s && io->w2_q && io->w2_s && io->x_q && io->x_s && io->h_s, REALB_EINVAL, "NULL FP4 buffer");
-    // Speculative mode: the weight encoding depends on the weights only, so it can start on the
-    // side stream before routing and fill the window in which the GPU waits for the host's
-    // precision decision.  If the decision is BF16 its output is simply not used.
-    // In the two modes in which the caller already bets on FP4 (speculative, prefetched) the activations are encoded
-    // ahead of the decision as well: every token once, on the side stream, beside the latency-bound routing and index
-    // kernels -- the form the gathering gate/up GEMM reads (row index = token index), so the gather kernel disappears.
-    const bool spec_w = io->overlap == 3 && io->force != REALB_BF16;
-    const bool spec_x = (io->overlap == 3 || io->overlap == 4) && io->force != REALB_BF16 && io->T > 0 && io->x && io->x_q && io->x_s &&
-                        gate_up_gather_supported(c, io->T, true);
-    const bool speculative = spec_w || spec_x;
-    if (speculative) {
-        if (spec_w) REALB_REQUIRE(io->w13 && io->w2 && io->w13_q && io->w13_s && io->w2_q && io->w2_s, REALB_EINVAL, "NULL FP4 weight buffer");
-        hipStream_t s = as_stream(stream);
-        REALB_HIP(hipEventRecord(c->ev_fork, s));
-        REALB_HIP(hipStreamWaitEvent(c->side, c->ev_fork, 0));
-        rc = REALB_OK;
-        // side stream: what the gate/up GEMM needs -- the activations and W13 (W2 follows on the caller's stream, after the decision)
-        if (spec_x) rc = launch_quantize_flat(io->x, io->T, c->cfg.H, io->x_q, io->x_s, nullptr, 0, 0, nullptr, nullptr, c->side);
-        if (rc == REALB_OK && spec_w)
-            rc = launch_quantize_flat(io->w13, (long long)c->n_local * 2 * c->cfg.I, c->cfg.H, io->w13_q, io->w13_s, nullptr, 0, 0, nullptr,
-                                      nullptr, c->side);
-        REALB_HIP(hipEventRecord(c->ev_join, c->side));
-        if (rc != REALB_OK) { (void)hipStreamWaitEvent(s, c->ev_join, 0); return rc; }
+    if (io->force == REALB_FP4) REALB_REQUIRE(fp4_buffers(io), REALB_EINVAL, "NULL FP4 buffer");
+    const PrecisionSource prec = precision_source(c, io->T, io->force, io->rank, io->rank_load, io->rank_vis);
+    const bool can_fp4 = prec.fixed != REALB_BF16, can_bf16 = prec.fixed != REALB_FP4;
+    const bool prefetch = io->next_w13 != nullptr;
+    // The whole layer goes out before the statistics are known, unless the GEMMs need a permuted copy of the rows (its form
+    // depends on the precision) or the FP4 buffers are there only if the caller knows that the decision will be BF16.
+    const bool ahead = (!can_fp4 || (fp4_buffers(io) && gate_up_gather_supported(c, io->T, true))) &&
+                       (!can_bf16 || gate_up_gather_supported(c, io->T, false));
+    // Side jobs: W13 beside the routing kernel if it is certain to be used, or speculated on (overlap = 3); the rest in the
+    // next launch, which can evaluate the policy.
+    SideJobs beside_topk{}, beside_finish{};
+    if (ahead && can_fp4) {
+        beside_topk.when.fixed = REALB_FP4;
+        beside_finish.when = prec;
+        add_tokens(c, io, kSideThreads, &beside_finish);
+        if (io->overlap != 2 && io->overlap != 4) {
+            if (prec.fixed == REALB_FP4 || io->overlap == 3) rc = add_w13(c, io, kTopkThreads, &beside_topk);
+            else rc = add_w13(c, io, kSideThreads, &beside_finish);
+            if (rc == REALB_OK) rc = add_w2(c, io, kSideThreads, &beside_finish);
+            if (rc != REALB_OK) return rc;
+        }
     }
-    // an error between here and rank_forward_impl (which joins by itself) still joins the side stream
-    auto fail = [&](int code) { if (speculative) (void)hipStreamWaitEvent(as_stream(stream), c->ev_join, 0); return code; };
-    stage_mark(c, as_stream(stream), 0);
-    // The statistics reach pinned host memory with the histogram reduce, which then publishes this call's sequence
-    // number there.  The permutation's index kernels do not depend on the precision, so they are interleaved with the
-    // routing kernels (the reduce shares a launch with the permutation's count kernel) and the ranking kernel runs
-    // while the host polls for the number, takes the decision and launches the rest.
+    stage_mark(c, s, 0);
+    // The statistics reach pinned host memory with the histogram reduce, tagged with this call's sequence number.
     if (++c->stats_seq <= 0) c->stats_seq = 1;
-    rc = route_and_index(c, io->logits, io->is_vision, io->T, io->rank, io->max_rows, io->topk_ids, io->topk_w, io->expert_cnt,
-                         io->expert_vis, io->rank_load, io->rank_vis, io->expert_offsets, io->row_to_assign, io->assign_to_row,
-                         c->stats_seq, as_stream(stream));
-    if (rc != REALB_OK) return fail(rc);
-    stage_mark(c, as_stream(stream), 1);
-    stage_mark(c, as_stream(stream), 2);
-    rc = select_precision_pinned(c, io->T, io->force, io->prec_host, &io->ib_global, &io->M_after, c->stats_seq, as_stream(stream));
-    if (rc != REALB_OK) return fail(rc);
-    return rank_forward_impl(ctx, io, io->prec_host[io->rank], stream, spec_w, spec_x, true);
+    rc = route_and_index(c, io, c->stats_seq, beside_topk, beside_finish, s);
+    if (rc != REALB_OK) return rc;
+    stage_mark(c, s, 1);
+    stage_mark(c, s, 2);
+    auto wait_for_statistics = [&]() {
+        return select_precision_pinned(c, io->T, io->force, io->prec_host, &io->ib_global, &io->M_after, c->stats_seq, s);
+    };
+    if (!ahead) {
+        rc = wait_for_statistics();
+        if (rc != REALB_OK) return rc;
+        return rank_forward_steps(ctx, io, io->prec_host[io->rank], stream, true);
+    }
+    stage_mark(c, s, 3);
+    if (io->overlap != 4 && !prefetch) {
+        rc = gemms_and_combine(ctx, io, prec, Prefetch::NONE, stream);
+        const int rc2 = wait_for_statistics();
+        return rc != REALB_OK ? rc : rc2;
+    }
+    // A prefetching pipeline launches its GEMMs once the statistics are there (the ranking kernel runs meanwhile): by then
+    // everything the previous call enqueued has run, so the prefetch that filled this call's weights has ended and the
+    // buffers of the next one have no reader left -- neither needs an event on the caller's stream.
+    rc = wait_for_statistics();
+    if (rc == REALB_OK) rc = join_prefetch(c, s);
+    if (rc != REALB_OK) return rc;
+    PrecisionSource known = prec;
+    known.fixed = io->prec_host[io->rank];
+    return gemms_and_combine(ctx, io, known, prefetch ? Prefetch::ON_START : Prefetch::NONE, stream);
+}
+
+extern "C" int realb_layer_forward(realb_ctx* ctx, realb_layer_io* io, void* stream) {
+    REALB_REQUIRE(ctx && io, REALB_EINVAL, "NULL argument");
+    return joined_on_error(reinterpret_cast<Ctx*>(ctx), layer_forward_steps(ctx, io, stream), stream);
 }
 
 extern "C" int realb_prefetch_join(realb_ctx* ctx, void* stream) {
     REALB_REQUIRE(ctx != nullptr, REALB_EINVAL, "ctx is NULL");
     Ctx* c = reinterpret_cast<Ctx*>(ctx);
-    if (c->prefetch_pending) {
-        REALB_HIP(hipStreamWaitEvent(as_stream(stream), c->ev_prefetch, 0));
-        c->prefetch_pending = false;
-    }
-    return REALB_OK;
+    return join_prefetch(c, as_stream(stream));
 }

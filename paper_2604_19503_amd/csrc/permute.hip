@@ -3,9 +3,8 @@
 // then a row gather that either copies BF16 rows or encodes them to MXFP4.
 // Stands in for the all-to-all dispatch of the paper's pipeline (Sec.
 // "Overhead-Aware Pipeline Orchestration"); the weight encoder overlaps it.
-#include "common.h"
+#include "encode_device.h"
 #include "hist_reduce.h"
-#include "mxfp4_device.h"
 #include <type_traits>
 
 namespace realb {
@@ -60,28 +59,11 @@ __device__ __forceinline__ void perm_count_body(int* gsum, int group, const int3
 
 template <int G>
 __global__ void __launch_bounds__(64 * G) perm_count_kernel(const int32_t* __restrict__ topk_ids, int A, int lo, int n_local,
-                                                                  int n_chunks, int n_groups, int32_t* __restrict__ wave_cnt,
-                                                                  int32_t* __restrict__ group_cnt) {
+                                                            int n_chunks, int n_groups, int32_t* __restrict__ wave_cnt,
+                                                            int32_t* __restrict__ group_cnt, const SideJobs jobs) {
     __shared__ int gsum[64];
+    if ((int)blockIdx.x >= n_groups) return run_side_jobs<64 * G>(jobs, blockIdx.x - n_groups);
     perm_count_body<G>(gsum, blockIdx.x, topk_ids, A, lo, n_local, n_chunks, n_groups, wave_cnt, group_cnt);
-}
-
-// The layer call's histogram reduce shares a launch with the permutation's count kernel: the first D blocks add up the
-// routing kernel's partial histograms, one EP rank each (and hand the per-rank statistics to the host), the other
-// blocks count their groups of chunks.  One kernel boundary less on a path made of short, latency-bound kernels.
-template <int G>
-__global__ void __launch_bounds__(64 * G) reduce_and_count_kernel(const int32_t* __restrict__ hist_part, int n_part, int E, int D,
-                                                                        int32_t* __restrict__ expert_cnt, int32_t* __restrict__ expert_vis,
-                                                                        int32_t* __restrict__ rank_load, int32_t* __restrict__ rank_vis,
-                                                                        unsigned long long* __restrict__ stats_words, int stats_seq,
-                                                                        const int32_t* __restrict__ topk_ids,
-                                                                        int A, int lo, int n_local, int n_chunks, int n_groups,
-                                                                        int32_t* __restrict__ wave_cnt, int32_t* __restrict__ group_cnt) {
-    extern __shared__ int32_t dyn[];                  // 2*E/D ints (reduce blocks only)
-    __shared__ int gsum[64];
-    if ((int)blockIdx.x < D)
-        hist_reduce_body(dyn, hist_part, n_part, E, D, blockIdx.x, expert_cnt, expert_vis, rank_load, rank_vis, stats_words, stats_seq);
-    else perm_count_body<G>(gsum, blockIdx.x - D, topk_ids, A, lo, n_local, n_chunks, n_groups, wave_cnt, group_cnt);
 }
 
 // Phase 2 (same blocks): every block first works out, from the group sums, each expert's total (whose exclusive scan
@@ -94,10 +76,12 @@ __global__ void __launch_bounds__(64 * G) perm_rank_kernel(const int32_t* __rest
                                                                  int n_chunks, int n_groups, const int32_t* __restrict__ wave_cnt,
                                                                  const int32_t* __restrict__ group_cnt,
                                                                  int32_t* __restrict__ expert_offsets,
-                                                                 int32_t* __restrict__ row_to_assign, int32_t* __restrict__ assign_to_row) {
+                                                                 int32_t* __restrict__ row_to_assign, int32_t* __restrict__ assign_to_row,
+                                                                 const SideJobs jobs) {
     __shared__ int before[64], total[64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int group = blockIdx.x;
+    const int group = blockIdx.x, n_front = max(n_groups, 1);
+    if (group >= n_front) return run_side_jobs<64 * G>(jobs, blockIdx.x - n_front);
     const int chunk = group * G + wave;
     int le[kIters];
     load_chunk(le, topk_ids, chunk, n_chunks, A, lo, lane);
@@ -149,15 +133,125 @@ __global__ void __launch_bounds__(64 * G) perm_rank_kernel(const int32_t* __rest
     }
 }
 
+// The layer call's index kernel.  There the routing kernel has just written, for each of its blocks of per_block consecutive
+// tokens, a histogram over all experts -- which is what the count kernel would count again.  So one launch finishes the
+// routing: the first D blocks add up the partial histograms, one EP rank each, and hand the statistics to the host; block
+// D + b ranks the assignments of routing block b (expert_offsets and its own base from the partial histograms of all blocks
+// and of the blocks before it); the blocks behind those run the side jobs, whose precision they evaluate from the per-rank
+// partial counts, since the reduced ones are being written beside them.
+// Bound by latency: two dependent memory round trips and n_local ballots per 64 assignments, twice.
+constexpr int kFinishThreads = 256, kFinishWaves = kFinishThreads / 64, kFinishRegs = 8;
+struct FinishArgs {
+    const int32_t* hist_part;
+    const int32_t* rank_part;
+    int n_part, per_block, E, D;
+    int32_t *expert_cnt, *expert_vis, *rank_load, *rank_vis;
+    unsigned long long* stats_words;
+    int stats_seq;
+    const int32_t* topk_ids;
+    int A, k, lo, n_local;
+    int32_t *expert_offsets, *row_to_assign, *assign_to_row;
+    unsigned side_blocks;        // blocks launched for the side jobs: they share the jobs' own blocks out among themselves
+};
+
+__global__ void __launch_bounds__(kFinishThreads) route_finish_kernel(const FinishArgs p, const SideJobs jobs) {
+    extern __shared__ int32_t dyn[];                  // 2*E/D ints (reduce blocks), 2*D ints (side blocks)
+    __shared__ int before[64], total[64], wcnt[kFinishWaves][64];
+    const int front = p.D + max(p.n_part, 1);
+    if ((int)blockIdx.x < p.D)
+        return hist_reduce_body(dyn, p.hist_part, p.n_part, p.E, p.D, blockIdx.x, p.expert_cnt, p.expert_vis, p.rank_load, p.rank_vis,
+                                p.stats_words, p.stats_seq);
+    if ((int)blockIdx.x >= front) {
+        if (!precision_from_parts<kFinishThreads>(jobs.when, p.rank_part, p.n_part, dyn)) return;
+        for (unsigned b = blockIdx.x - front; b < jobs.blocks(); b += p.side_blocks) do_side_job<kFinishThreads>(jobs, b);
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int b = blockIdx.x - p.D, n_local = p.n_local;
+    // this wave's share of the block's assignments: `iters` pieces of 64
+    const int a_lo = b * p.per_block * p.k, n = min(p.per_block * p.k, p.A - a_lo);
+    const int iters = (n + 64 * kFinishWaves - 1) / (64 * kFinishWaves);
+    const int w_lo = wave * iters * 64;
+    auto local_expert = [&](int i) __attribute__((always_inline)) {
+        const int q = w_lo + i * 64 + lane;
+        return q < n ? p.topk_ids[a_lo + q] - p.lo : -1;
+    };
+    int le[kFinishRegs];
+#pragma unroll
+    for (int i = 0; i < kFinishRegs; ++i) le[i] = i < iters ? local_expert(i) : -1;
+    // expert totals and the counts of earlier blocks: thread (r, e) walks the partials r, r + R, ..
+    if (threadIdx.x < 64) before[threadIdx.x] = total[threadIdx.x] = 0;
+    __syncthreads();
+    {
+        const int cols = n_local <= 8 ? 8 : n_local <= 16 ? 16 : n_local <= 32 ? 32 : 64, e = threadIdx.x % cols;
+        if (e < n_local) {
+            int bsum = 0, tsum = 0;
+            const int step = kFinishThreads / cols;
+            for (int q = threadIdx.x / cols; q < p.n_part; q += 8 * step) {
+                int v[8];                                     // 8 independent loads in flight
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = q + i * step < p.n_part ? p.hist_part[(size_t)(q + i * step) * 2 * p.E + p.lo + e] : 0;
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    tsum += v[i];
+                    bsum += q + i * step < b ? v[i] : 0;
+                }
+            }
+            atomicAdd(&total[e], tsum);
+            atomicAdd(&before[e], bsum);
+        }
+    }
+    int cnt = 0;
+    for (int i = 0; i < iters; ++i) {
+        int v = -1;
+        if (iters <= kFinishRegs) {
+#pragma unroll
+            for (int r = 0; r < kFinishRegs; ++r) v = r == i ? le[r] : v;
+        } else v = local_expert(i);
+        for (int e = 0; e < n_local; ++e) {
+            const unsigned long long m = __ballot(v == e);
+            if (lane == e) cnt += __popcll(m);
+        }
+    }
+    wcnt[wave][lane] = cnt;
+    __syncthreads();
+    const int tot = lane < n_local ? total[lane] : 0;
+    const int incl = wave_inclusive_scan(tot);
+    if (b == 0 && wave == 0) {
+        if (lane < n_local) p.expert_offsets[lane] = incl - tot;
+        if (lane == n_local - 1) p.expert_offsets[n_local] = incl;
+    }
+    int running = lane < n_local ? incl - tot + before[lane] : 0;
+    for (int w = 0; w < wave; ++w) running += wcnt[w][lane];
+    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    for (int i = 0; i < iters; ++i) {
+        int v = -1;
+        if (iters <= kFinishRegs) {
+#pragma unroll
+            for (int r = 0; r < kFinishRegs; ++r) v = r == i ? le[r] : v;
+        } else v = local_expert(i);
+        int row = -1;
+        for (int e = 0; e < n_local; ++e) {
+            const unsigned long long m = __ballot(v == e);
+            const int base = __builtin_amdgcn_readlane(running, e);
+            if (v == e) row = base + __popcll(m & lt_mask);
+            if (lane == e) running += __popcll(m);
+        }
+        const int q = w_lo + i * 64 + lane;
+        if (q < n) {
+            p.assign_to_row[a_lo + q] = row;
+            if (row >= 0) p.row_to_assign[row] = a_lo + q;
+        }
+    }
+}
+
 // Phase 4: one wave per TOKEN, grid-strided: a token routed to several local experts
 // is read (and, on the FP4 path, encoded) once and written to each of its rows.
 // H/8 chunks of 16 B per row; FP4: quads of lanes share one 32-element block.
 template <bool FP4, int CPL>   // CPL = 16-byte chunks per lane = H / 512 rounded up
 __global__ void __launch_bounds__(256) perm_gather_kernel(const u32x4_t* __restrict__ x, const int32_t* __restrict__ assign_to_row,
                                                           int T, int k, int H, u32x4_t* __restrict__ x_perm,
-                                                          uint32_t* __restrict__ x_q, uint8_t* __restrict__ x_s, int token_major) {
-    // token_major: a token with a local expert is written once, at row index t (the consuming GEMM then
-    // fetches rows through row_to_assign), instead of once per row it occupies.
+                                                          uint32_t* __restrict__ x_q, uint8_t* __restrict__ x_s) {
     const int lane = threadIdx.x & 63;
     const int chunks = H >> 3;                             // 16-B chunks per row, multiple of 16
     // A block takes a contiguous range of tokens: the rows of one 32-row group of an expert come from
@@ -192,9 +286,8 @@ __global__ void __launch_bounds__(256) perm_gather_kernel(const u32x4_t* __restr
                           ((uint32_t)__shfl_down((int)byte[u], 12) << 24);
             }
         }
-        const int n_writes = token_major ? 1 : k;
-        for (int j = 0; j < n_writes; ++j) {
-            const int r = token_major ? t : __builtin_amdgcn_readlane(my_row, j);
+        for (int j = 0; j < k; ++j) {
+            const int r = __builtin_amdgcn_readlane(my_row, j);
             if (r < 0) continue;
 #pragma unroll
             for (int u = 0; u < CPL; ++u) {
@@ -217,11 +310,11 @@ __global__ void __launch_bounds__(256) perm_gather_kernel(const u32x4_t* __restr
 
 template <bool FP4>
 static void launch_gather(int blocks, hipStream_t s, const void* x, const int32_t* a2r, int T, int k, int H, void* x_perm,
-                          uint8_t* x_q, uint8_t* x_s, int token_major = 0) {
+                          uint8_t* x_q, uint8_t* x_s) {
     const int cpl = (H / 8 + 63) / 64;
 #define REALB_GATHER(CPL)                                                                                              \
     hipLaunchKernelGGL((perm_gather_kernel<FP4, CPL>), dim3(blocks), dim3(256), 0, s, (const u32x4_t*)x, a2r, T, k, H, \
-                       (u32x4_t*)x_perm, (uint32_t*)x_q, x_s, token_major)
+                       (u32x4_t*)x_perm, (uint32_t*)x_q, x_s)
     if (cpl <= 1) REALB_GATHER(1);
     else if (cpl <= 2) REALB_GATHER(2);
     else if (cpl <= 4) REALB_GATHER(4);
@@ -236,29 +329,38 @@ using namespace realb;
 
 namespace realb {
 
-// The two halves of realb_permute.  The index half (count / rank) does not depend on the
-// precision, so the layer can run it while the host is still taking the precision decision.
-int permute_indices(Ctx* c, const int32_t* topk_ids, int T, int rank, long long max_rows, int32_t* expert_offsets,
-                    int32_t* row_to_assign, int32_t* assign_to_row, hipStream_t s) {
+int perm_block_threads(int T, int k) { return 64 * perm_group(ceil_div((long long)T * k, kPermChunk)); }
+
+static int check_permute(const Ctx* c, const int32_t* topk_ids, int T, int rank, long long max_rows, const int32_t* expert_offsets,
+                         const int32_t* row_to_assign, const int32_t* assign_to_row) {
     REALB_REQUIRE(c && expert_offsets, REALB_EINVAL, "NULL argument");
     REALB_REQUIRE(T >= 0 && T <= c->cfg.T_max, REALB_ECAP, "T=%d outside [0, T_max=%d]", T, c->cfg.T_max);
     REALB_REQUIRE(rank >= 0 && rank < c->cfg.D, REALB_EINVAL, "rank=%d outside [0,%d)", rank, c->cfg.D);
     const int k = c->cfg.k, n_local = c->n_local;
-    const long long A = (long long)T * k;
     const long long worst = (long long)T * (k < n_local ? k : n_local);
     REALB_REQUIRE(max_rows >= worst, REALB_EINVAL, "max_rows=%lld is below the worst case %lld", max_rows, worst);
     REALB_REQUIRE(T == 0 || (topk_ids && row_to_assign && assign_to_row), REALB_EINVAL, "NULL argument");
+    return REALB_OK;
+}
+
+// The index half of realb_permute (count / rank); the side jobs' blocks have perm_block_threads(T, k) threads.
+int permute_indices(Ctx* c, const int32_t* topk_ids, int T, int rank, long long max_rows, int32_t* expert_offsets,
+                    int32_t* row_to_assign, int32_t* assign_to_row, const SideJobs& beside_count, const SideJobs& beside_rank, hipStream_t s) {
+    const int rc = check_permute(c, topk_ids, T, rank, max_rows, expert_offsets, row_to_assign, assign_to_row);
+    if (rc != REALB_OK) return rc;
+    const int n_local = c->n_local, lo = rank * n_local;
+    const long long A = (long long)T * c->cfg.k;
     const int n_chunks = ceil_div(A, kPermChunk);
     const int G = perm_group(n_chunks);
     const int n_groups = ceil_div(n_chunks, G);
-    const int lo = rank * n_local;
     auto launch = [&](auto g) {
         constexpr int GG = decltype(g)::value;
-        if (n_groups > 0)
-            hipLaunchKernelGGL(perm_count_kernel<GG>, dim3(n_groups), dim3(64 * GG), 0, s, topk_ids, (int)A, lo, n_local, n_chunks,
-                               n_groups, c->wave_cnt, c->group_cnt);
-        hipLaunchKernelGGL(perm_rank_kernel<GG>, dim3(n_groups > 0 ? n_groups : 1), dim3(64 * GG), 0, s, topk_ids, (int)A, lo, n_local,
-                           n_chunks, n_groups, c->wave_cnt, c->group_cnt, expert_offsets, row_to_assign, assign_to_row);
+        if (n_groups + beside_count.blocks() > 0)
+            hipLaunchKernelGGL(perm_count_kernel<GG>, dim3(n_groups + beside_count.blocks()), dim3(64 * GG), 0, s, topk_ids, (int)A, lo, n_local,
+                               n_chunks, n_groups, c->wave_cnt, c->group_cnt, beside_count);
+        hipLaunchKernelGGL(perm_rank_kernel<GG>, dim3((n_groups > 0 ? n_groups : 1) + beside_rank.blocks()), dim3(64 * GG), 0, s, topk_ids,
+                           (int)A, lo, n_local, n_chunks, n_groups, c->wave_cnt, c->group_cnt, expert_offsets, row_to_assign,
+                           assign_to_row, beside_rank);
     };
     if (G == kGroupLong) launch(std::integral_constant<int, kGroupLong>{});
     else launch(std::integral_constant<int, kGroupShort>{});
@@ -266,42 +368,34 @@ int permute_indices(Ctx* c, const int32_t* topk_ids, int T, int rank, long long 
     return REALB_OK;
 }
 
-// Routing and the permutation's index kernels as the layer call issues them: top-k + histograms, then
-// [histogram reduce | chunk counts] in one launch -- whose reduce block writes the statistics, tagged with stats_seq,
-// to pinned memory -- then the ranking kernel, which runs while the host takes the decision.
-int route_and_index(Ctx* c, const float* logits, const uint8_t* is_vision, int T, int rank, long long max_rows, int32_t* topk_ids,
-                    float* topk_w, int32_t* expert_cnt, int32_t* expert_vis, int32_t* rank_load, int32_t* rank_vis,
-                    int32_t* expert_offsets, int32_t* row_to_assign, int32_t* assign_to_row, int stats_seq, hipStream_t s) {
-    REALB_REQUIRE(c && expert_cnt && expert_vis && rank_load && rank_vis && expert_offsets, REALB_EINVAL, "NULL argument");
-    REALB_REQUIRE(T >= 0 && T <= c->cfg.T_max, REALB_ECAP, "T=%d outside [0, T_max=%d]", T, c->cfg.T_max);
-    REALB_REQUIRE(rank >= 0 && rank < c->cfg.D, REALB_EINVAL, "rank=%d outside [0,%d)", rank, c->cfg.D);
-    const int E = c->cfg.E, D = c->cfg.D, k = c->cfg.k, n_local = c->n_local;
-    const long long A = (long long)T * k;
-    const long long worst = (long long)T * (k < n_local ? k : n_local);
-    REALB_REQUIRE(max_rows >= worst, REALB_EINVAL, "max_rows=%lld is below the worst case %lld", max_rows, worst);
-    REALB_REQUIRE(T == 0 || (topk_ids && row_to_assign && assign_to_row), REALB_EINVAL, "NULL argument");
-    const int n_part = route_topk_only(c, logits, is_vision, T, topk_ids, topk_w, s);
+// Routing and the permutation's indices as the layer call issues them: top-k + histograms, then route_finish_kernel, whose
+// reduce blocks write the statistics, tagged with stats_seq, to pinned memory.  Both launches carry side jobs (blocks of
+// kTopkThreads and kSideThreads threads).
+int route_and_index(Ctx* c, const realb_layer_io* io, int stats_seq, const SideJobs& beside_topk, const SideJobs& beside_finish, hipStream_t s) {
+    REALB_REQUIRE(io->expert_cnt && io->expert_vis && io->rank_load && io->rank_vis, REALB_EINVAL, "NULL argument");
+    const int rc = check_permute(c, io->topk_ids, io->T, io->rank, io->max_rows, io->expert_offsets, io->row_to_assign, io->assign_to_row);
+    if (rc != REALB_OK) return rc;
+    FinishArgs p{};
+    int32_t* rank_part = nullptr;
+    const int n_part = route_topk_only(c, io->logits, io->is_vision, io->T, io->topk_ids, io->topk_w, beside_topk, &p.per_block, &rank_part, s);
     if (n_part < 0) return n_part;
-    const int n_chunks = ceil_div(A, kPermChunk);
-    const int G = perm_group(n_chunks);
-    const int n_groups = ceil_div(n_chunks, G);
-    const int lo = rank * n_local;
-    auto launch = [&](auto g) {
-        constexpr int GG = decltype(g)::value;
-        hipLaunchKernelGGL(reduce_and_count_kernel<GG>, dim3(D + n_groups), dim3(64 * GG), 2 * (size_t)(E / D) * sizeof(int32_t), s,
-                           c->hist_part, n_part, E, D, expert_cnt, expert_vis, rank_load, rank_vis, c->stats_words, stats_seq, topk_ids,
-                           (int)A, lo, n_local, n_chunks, n_groups, c->wave_cnt, c->group_cnt);
-        hipLaunchKernelGGL(perm_rank_kernel<GG>, dim3(n_groups > 0 ? n_groups : 1), dim3(64 * GG), 0, s, topk_ids, (int)A, lo, n_local,
-                           n_chunks, n_groups, c->wave_cnt, c->group_cnt, expert_offsets, row_to_assign, assign_to_row);
-    };
-    if (G == kGroupLong) launch(std::integral_constant<int, kGroupLong>{});
-    else launch(std::integral_constant<int, kGroupShort>{});
+    const int E = c->cfg.E, D = c->cfg.D;
+    p.hist_part = c->hist_part; p.rank_part = rank_part; p.n_part = n_part; p.E = E; p.D = D;
+    p.expert_cnt = io->expert_cnt; p.expert_vis = io->expert_vis; p.rank_load = io->rank_load; p.rank_vis = io->rank_vis;
+    p.stats_words = c->stats_words; p.stats_seq = stats_seq;
+    p.topk_ids = io->topk_ids; p.A = io->T * c->cfg.k; p.k = c->cfg.k; p.lo = io->rank * c->n_local; p.n_local = c->n_local;
+    p.expert_offsets = io->expert_offsets; p.row_to_assign = io->row_to_assign; p.assign_to_row = io->assign_to_row;
+    // blocks that evaluate the policy (a microsecond each) are few enough to be resident at once and take several jobs
+    const unsigned jobs = beside_finish.blocks(), resident = 8u * (unsigned)c->num_cus;
+    p.side_blocks = beside_finish.when.fixed >= 0 || jobs < resident ? jobs : resident;
+    hipLaunchKernelGGL(route_finish_kernel, dim3(D + (n_part > 0 ? n_part : 1) + p.side_blocks), dim3(kFinishThreads),
+                       2 * (size_t)(c->n_local > D ? c->n_local : D) * sizeof(int32_t), s, p, beside_finish);
     REALB_HIP(hipGetLastError());
     return REALB_OK;
 }
 
 int permute_gather(Ctx* c, const void* x, const int32_t* assign_to_row, int T, int prec, void* x_perm, uint8_t* x_q,
-                   uint8_t* x_s, hipStream_t s, int token_major) {
+                   uint8_t* x_s, hipStream_t s) {
     REALB_REQUIRE(c != nullptr, REALB_EINVAL, "NULL argument");
     REALB_REQUIRE(prec == REALB_BF16 || prec == REALB_FP4, REALB_EINVAL, "bad precision %d", prec);
     REALB_REQUIRE(T >= 0 && T <= c->cfg.T_max, REALB_ECAP, "T=%d outside [0, T_max=%d]", T, c->cfg.T_max);
@@ -310,7 +404,7 @@ int permute_gather(Ctx* c, const void* x, const int32_t* assign_to_row, int T, i
     REALB_REQUIRE(prec == REALB_BF16 ? x_perm != nullptr : (x_q && x_s), REALB_EINVAL, "NULL row buffer");
     const int k = c->cfg.k, H = c->cfg.H;
     const int blocks = 8 * (T < 32 ? 1 : (T / 32 < 512 ? T / 32 : 512));      // a multiple of 8 (XCDs), 4 waves each
-    if (prec == REALB_FP4) launch_gather<true>(blocks, s, x, assign_to_row, T, k, H, nullptr, x_q, x_s, token_major);
+    if (prec == REALB_FP4) launch_gather<true>(blocks, s, x, assign_to_row, T, k, H, nullptr, x_q, x_s);
     else launch_gather<false>(blocks, s, x, assign_to_row, T, k, H, x_perm, nullptr, nullptr);
     REALB_HIP(hipGetLastError());
     return REALB_OK;
@@ -325,7 +419,7 @@ extern "C" int realb_permute(realb_ctx* ctx, const void* x, const int32_t* topk_
     Ctx* c = reinterpret_cast<Ctx*>(ctx);
     REALB_REQUIRE(prec == REALB_BF16 || prec == REALB_FP4, REALB_EINVAL, "bad precision %d", prec);
     REALB_REQUIRE(T <= 0 || (x && (prec == REALB_BF16 ? x_perm != nullptr : (x_q && x_s))), REALB_EINVAL, "NULL row buffer");
-    int rc = permute_indices(c, topk_ids, T, rank, max_rows, expert_offsets, row_to_assign, assign_to_row, as_stream(stream));
+    int rc = permute_indices(c, topk_ids, T, rank, max_rows, expert_offsets, row_to_assign, assign_to_row, SideJobs{}, SideJobs{}, as_stream(stream));
     if (rc != REALB_OK) return rc;
-    return permute_gather(c, x, assign_to_row, T, prec, x_perm, x_q, x_s, as_stream(stream), 0);
+    return permute_gather(c, x, assign_to_row, T, prec, x_perm, x_q, x_s, as_stream(stream));
 }

@@ -1,92 +1,46 @@
 // On-the-fly BF16 -> MXFP4 weight transformation (paper Sec. "Overhead-Aware
 // Pipeline Orchestration", Overlapping Pipeline): a pure HBM stream, 2 B read
 // and 17/32 B written per element.  Scale bytes go to their K-step-tiled positions.
-#include "common.h"
-#include "mxfp4_device.h"
+#include "encode_device.h"
 
 namespace realb {
 
-// A tensor is a flat sequence of 32-element blocks (rows are multiples of 128 long and
-// contiguous).  A quad of lanes encodes one block: each lane loads 16 B (8 values), the quad
-// shares the maximum, each lane stores 4 B of codes and the quad's first lane stores the scale
-// byte at its K-step-tiled position.  UNROLL independent loads per lane keep enough bytes in flight.
-// One launch covers up to two tensors (the rank's W13 and W2): the first `blocks0` blocks take
-// tensor 0, the rest tensor 1, so that the second tensor's stream starts while the first one's last
-// blocks drain instead of behind a kernel boundary.
-struct QuantTensor {
-    const u32x4_t* src;      // BF16 values, 16-byte chunks
-    uint32_t* q;             // codes, one dword per chunk
-    uint8_t* s;              // scales, K-step tiled
-    long long n_chunks;
-    int cpr;                 // chunks per row = K / 8
-    float inv_cpr;
-};
-struct QuantJob { QuantTensor t[2]; unsigned blocks0; };
+template <int NT>
+__global__ void __launch_bounds__(NT) quantize_flat_kernel(const QuantJob job) { quantize_block<NT, REALB_QUANT_UNROLL>(job, blockIdx.x); }
 
-#ifndef REALB_QUANT_UNROLL
-#define REALB_QUANT_UNROLL 4
-#endif
+template <int NT>
+__global__ void __launch_bounds__(NT) side_jobs_kernel(const SideJobs jobs) { run_side_jobs<NT>(jobs, blockIdx.x); }
 
-template <int UNROLL>
-__global__ void __launch_bounds__(256) quantize_flat_kernel(const QuantJob job) {
-    const bool second = blockIdx.x >= job.blocks0;                                // uniform per block
-    const QuantTensor& t = job.t[second ? 1 : 0];
-    const u32x4_t* __restrict__ src = t.src;
-    uint32_t* __restrict__ q = t.q;
-    uint8_t* __restrict__ s = t.s;
-    const long long n_chunks = t.n_chunks;
-    const int cpr = t.cpr;
-    const long long block_base = ((long long)(blockIdx.x - (second ? job.blocks0 : 0u)) * UNROLL) * 256;
-    const int KD = cpr >> 4;                                  // K-steps per row (128 elements = 16 chunks)
-    const unsigned row_b = (unsigned)block_base / (unsigned)cpr;             // one division per thread; n_chunks < 2^31
-    const int in_row0 = (int)((unsigned)block_base - row_b * (unsigned)cpr);
-    u32x4_t v[UNROLL];
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-        const long long c = block_base + (long long)u * 256 + threadIdx.x;
-        v[u] = c < n_chunks ? __builtin_nontemporal_load(src + c) : u32x4_t{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int u = 0; u < UNROLL; ++u) {
-        const long long cb = block_base + (long long)u * 256;     // uniform: first chunk of this pass
-        const long long c = cb + threadIdx.x;
-        uint32_t byte;
-        const uint32_t codes = encode_block_quad(v[u], &byte);    // whole quads are in or out of range together
-        if (c < n_chunks) {
-            __builtin_nontemporal_store(codes, q + c);
-            if ((threadIdx.x & 3) == 0) {
-                const int in_row = in_row0 + u * 256 + threadIdx.x;                  // < cpr + 256 * UNROLL
-                const int dr = (int)(((float)in_row + 0.5f) * t.inv_cpr);            // exact: in_row < 2^16
-                s[scale_byte_offset(row_b + dr, (in_row - dr * cpr) >> 2, KD)] = (uint8_t)byte;
-            }
-        }
-    }
-}
-
-static int fill_tensor(QuantTensor* t, const void* src, long long rows, int K, uint8_t* q, uint8_t* s, unsigned* blocks) {
-    constexpr long long per_block = 256ll * REALB_QUANT_UNROLL;
-    const long long n_chunks = rows * (K / 8);
-    REALB_REQUIRE(n_chunks < (1ll << 31), REALB_ECAP, "tensor too large for one launch");
-    *t = QuantTensor{(const u32x4_t*)src, (uint32_t*)q, s, n_chunks, K / 8, 1.0f / (float)(K / 8)};
-    *blocks = (unsigned)((n_chunks + per_block - 1) / per_block);
+int launch_side_jobs(const SideJobs& jobs, hipStream_t stream) {
+    if (jobs.blocks() == 0) return REALB_OK;
+    hipLaunchKernelGGL(side_jobs_kernel<kSideThreads>, dim3(jobs.blocks()), dim3(kSideThreads), 0, stream, jobs);
+    REALB_HIP(hipGetLastError());
     return REALB_OK;
 }
 
-// Encodes one tensor [rows0, K0], or two when rows1 > 0, in a single launch.
+int add_quant_tensor(QuantJob* job, const void* src, long long rows, int K, uint8_t* q, uint8_t* s, int NT) {
+    const long long per_block = (long long)NT * REALB_QUANT_UNROLL;
+    const long long n_chunks = rows * (K / 8);
+    REALB_REQUIRE(n_chunks < (1ll << 31), REALB_ECAP, "tensor too large for one launch");
+    const unsigned blocks = (unsigned)((n_chunks + per_block - 1) / per_block);
+    QuantTensor& t = job->t[job->blocks > 0 ? 1 : 0];
+    t = QuantTensor{(const u32x4_t*)src, (uint32_t*)q, s, n_chunks, K / 8, 1.0f / (float)(K / 8)};
+    if (job->blocks == 0) job->blocks0 = blocks;
+    job->blocks += blocks;
+    return REALB_OK;
+}
+
+// Encodes one tensor [rows0, K0], or two when rows1 > 0, in a single launch (the second tensor's stream starts while the
+// first one's last blocks drain instead of behind a kernel boundary).
 int launch_quantize_flat(const void* src0, long long rows0, int K0, uint8_t* q0, uint8_t* s0,
                          const void* src1, long long rows1, int K1, uint8_t* q1, uint8_t* s1, hipStream_t stream) {
+    constexpr int NT = 256;
     QuantJob job{};
-    unsigned b0 = 0, b1 = 0;
-    int rc = fill_tensor(&job.t[0], src0, rows0, K0, q0, s0, &b0);
+    int rc = add_quant_tensor(&job, src0, rows0, K0, q0, s0, NT);
+    if (rc == REALB_OK && rows1 > 0) rc = add_quant_tensor(&job, src1, rows1, K1, q1, s1, NT);
     if (rc != REALB_OK) return rc;
-    if (rows1 > 0) {
-        rc = fill_tensor(&job.t[1], src1, rows1, K1, q1, s1, &b1);
-        if (rc != REALB_OK) return rc;
-    }
-    job.blocks0 = b0;
-    if (b0 + b1 == 0) return REALB_OK;
-    REALB_REQUIRE((unsigned long long)b0 + b1 < (1ull << 31), REALB_ECAP, "too many blocks");
-    hipLaunchKernelGGL(quantize_flat_kernel<REALB_QUANT_UNROLL>, dim3(b0 + b1), dim3(256), 0, stream, job);
+    if (job.blocks == 0) return REALB_OK;
+    hipLaunchKernelGGL(quantize_flat_kernel<NT>, dim3(job.blocks), dim3(NT), 0, stream, job);
     REALB_HIP(hipGetLastError());
     return REALB_OK;
 }

@@ -2,7 +2,7 @@
 // Load_d, N_vd of Sec. "Real-time Modality-aware LB Scheduling"): top-k gating
 // with gates renormalised over the selected experts, per-expert and per-rank
 // assignment counts, split by modality.
-#include "common.h"
+#include "encode_device.h"
 #include "hist_reduce.h"
 #include <math.h>
 #include <mutex>
@@ -38,6 +38,18 @@ __device__ __forceinline__ float wave_max(float v) {
     return fmaxf(fmaxf(r0, r1), fmaxf(r2, r3));
 }
 
+// The block's counts per EP rank (loads, then vision loads) at rank_part[block][2*D], from its LDS histogram: what a kernel
+// needs to evaluate the precision policy before the partial histograms have been reduced.
+__device__ __forceinline__ void store_rank_part(const int32_t* hist, int E, int D, int32_t* __restrict__ rank_part) {
+    const int n_local = E / D;
+    if (rank_part && (int)threadIdx.x < 2 * D) {
+        const int32_t* h = hist + threadIdx.x * n_local;         // (vision counts of rank d: hist + E + d * n_local)
+        int sum = 0;
+        for (int e = 0; e < n_local; ++e) sum += h[e];
+        rank_part[(size_t)blockIdx.x * 2 * D + threadIdx.x] = sum;
+    }
+}
+
 // One wave per token.  Lane l holds the EPL consecutive experts l*EPL .. l*EPL+EPL-1,
 // so that among equal logits the lowest (lane, slot) is the lowest expert index.
 // k rounds of: per-lane best -> wave maximum -> lowest lane holding it wins.
@@ -46,7 +58,9 @@ __device__ __forceinline__ float wave_max(float v) {
 template <int EPL>
 __global__ void __launch_bounds__(1024, 2) topk_hist_kernel(const float* __restrict__ logits, const uint8_t* __restrict__ is_vision,
                                                         int T, int E, int k, int32_t* __restrict__ topk_ids,
-                                                        float* __restrict__ topk_w, int32_t* __restrict__ hist_part) {
+                                                        float* __restrict__ topk_w, int32_t* __restrict__ hist_part,
+                                                        int n_front, int per_block, int D, int32_t* __restrict__ rank_part, const SideJobs jobs) {
+    if ((int)blockIdx.x >= n_front) return run_side_jobs<kTopkThreads, false>(jobs, blockIdx.x - n_front);
     extern __shared__ int32_t hist[];                 // [2*E]: counts, vision counts
     for (int i = threadIdx.x; i < 2 * E; i += blockDim.x) hist[i] = 0;
     __syncthreads();
@@ -56,12 +70,12 @@ __global__ void __launch_bounds__(1024, 2) topk_hist_kernel(const float* __restr
     const float NEG = -INFINITY;
     // The wave's next token is fetched while the current one is being ranked (one load latency per
     // wave instead of one per token).
-    const int stride = gridDim.x * waves_per_block;
-    int t = blockIdx.x * waves_per_block + wave;
+    const int stride = waves_per_block, t_end = min(T, ((int)blockIdx.x + 1) * per_block);
+    int t = blockIdx.x * per_block + wave;
     float nx[EPL];
     int nx_vision = 0;
     auto fetch = [&](int tok) __attribute__((always_inline)) {
-        if (tok < T) {
+        if (tok < t_end) {
             const float* row = logits + (size_t)tok * E + lane * EPL;
 #pragma unroll
             for (int j = 0; j < EPL; ++j) nx[j] = (lane * EPL + j < E) ? row[j] : NEG;
@@ -69,7 +83,7 @@ __global__ void __launch_bounds__(1024, 2) topk_hist_kernel(const float* __restr
         }
     };
     fetch(t);
-    for (; t < T; t += stride) {
+    for (; t < t_end; t += stride) {
         float v[EPL];
 #pragma unroll
         for (int j = 0; j < EPL; ++j) v[j] = nx[j];
@@ -107,6 +121,7 @@ __global__ void __launch_bounds__(1024, 2) topk_hist_kernel(const float* __restr
     }
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * E; i += blockDim.x) hist_part[(size_t)blockIdx.x * 2 * E + i] = hist[i];
+    store_rank_part(hist, E, D, rank_part);
 }
 
 __device__ __forceinline__ int row_min_i(int v) {
@@ -124,7 +139,9 @@ __device__ __forceinline__ int row_min_i(int v) {
 template <int EPL>
 __global__ void __launch_bounds__(1024, 2) topk_hist_rows_kernel(const float* __restrict__ logits, const uint8_t* __restrict__ is_vision,
                                                                  int T, int E, int k, int32_t* __restrict__ topk_ids,
-                                                                 float* __restrict__ topk_w, int32_t* __restrict__ hist_part) {
+                                                                 float* __restrict__ topk_w, int32_t* __restrict__ hist_part,
+                                                        int n_front, int per_block, int D, int32_t* __restrict__ rank_part, const SideJobs jobs) {
+    if ((int)blockIdx.x >= n_front) return run_side_jobs<kTopkThreads, false>(jobs, blockIdx.x - n_front);
     extern __shared__ int32_t hist[];                 // [2*E]: counts, vision counts
     for (int i = threadIdx.x; i < 2 * E; i += blockDim.x) hist[i] = 0;
     __syncthreads();
@@ -133,12 +150,12 @@ __global__ void __launch_bounds__(1024, 2) topk_hist_rows_kernel(const float* __
     const int wave = threadIdx.x >> 6;
     const int waves_per_block = blockDim.x >> 6;
     const float NEG = -INFINITY;
-    const int stride = gridDim.x * waves_per_block * 4;
-    int t = (blockIdx.x * waves_per_block + wave) * 4 + r;
+    const int stride = waves_per_block * 4, t_end = min(T, ((int)blockIdx.x + 1) * per_block);
+    int t = blockIdx.x * per_block + wave * 4 + r;
     float nx[EPL];
     int nx_vision = 0;
     auto fetch = [&](int tok) __attribute__((always_inline)) {
-        if (tok < T) {
+        if (tok < t_end) {
             const float* row = logits + (size_t)tok * E + j * EPL;
 #pragma unroll
             for (int q = 0; q < EPL; ++q) nx[q] = row[q];
@@ -146,12 +163,12 @@ __global__ void __launch_bounds__(1024, 2) topk_hist_rows_kernel(const float* __
         }
     };
     fetch(t);
-    for (int t0 = t - r; t0 < T; t0 += stride, t += stride) {      // uniform trip count: rows past T idle but take part in the DPP steps
+    for (int t0 = t - r; t0 < t_end; t0 += stride, t += stride) {  // uniform trip count: rows past the end idle but take part in the DPP steps
         float v[EPL];
 #pragma unroll
         for (int q = 0; q < EPL; ++q) v[q] = nx[q];
         const int vision = nx_vision;
-        const bool live = t < T;
+        const bool live = t < t_end;
         fetch(t + stride);
         float my_val = NEG;                           // lane j keeps the j-th selected logit of its row's token
         int my_id = 0;
@@ -181,6 +198,7 @@ __global__ void __launch_bounds__(1024, 2) topk_hist_rows_kernel(const float* __
     }
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * E; i += blockDim.x) hist_part[(size_t)blockIdx.x * 2 * E + i] = hist[i];
+    store_rank_part(hist, E, D, rank_part);
 }
 
 __global__ void __launch_bounds__(1024) hist_reduce_kernel(const int32_t* __restrict__ hist_part, int n_part, int E, int D,
@@ -190,42 +208,42 @@ __global__ void __launch_bounds__(1024) hist_reduce_kernel(const int32_t* __rest
     hist_reduce_body(tot, hist_part, n_part, E, D, blockIdx.x, expert_cnt, expert_vis, rank_load, rank_vis, nullptr, 0);
 }
 
-// Launches the top-k + histogram kernel; returns the number of blocks (= partial histograms written).
-// hist_part must hold max_blocks * 2E counters.
+// Launches the top-k + histogram kernel, with `jobs` (blocks of 1024 threads) behind its own blocks.  Every routing block
+// takes *per_block consecutive tokens; returns the number of routing blocks (= partial histograms written).  hist_part must
+// hold max_blocks * 2E counters, rank_part (optional) max_blocks * 2D.
 static int launch_topk(int num_cus, int max_blocks, int32_t* hist_part, const float* logits, const uint8_t* is_vision, int T,
-                       int E, int k, int32_t* topk_ids, float* topk_w, hipStream_t s) {
-    int blocks = 0;
-    if (T > 0) {
-        const size_t lds = 2 * (size_t)E * sizeof(int32_t);
-        if (E <= 128 && E % 16 == 0) {                          // four tokens per wave
-            blocks = min(min(ceil_div(T, 64), 2 * num_cus), max_blocks);      // 16 waves x 4 tokens in flight per block, two blocks per CU
-#define REALB_TOPK_ROWS(EPL)                                                                                      \
-    hipLaunchKernelGGL(topk_hist_rows_kernel<EPL>, dim3(blocks), dim3(1024), lds, s, logits, is_vision, T, E, k, \
-                       topk_ids, topk_w, hist_part)
-            switch (E / 16) {
-                case 1: REALB_TOPK_ROWS(1); break;
-                case 2: REALB_TOPK_ROWS(2); break;
-                case 3: REALB_TOPK_ROWS(3); break;
-                case 4: REALB_TOPK_ROWS(4); break;
-                case 5: REALB_TOPK_ROWS(5); break;
-                case 6: REALB_TOPK_ROWS(6); break;
-                case 7: REALB_TOPK_ROWS(7); break;
-                default: REALB_TOPK_ROWS(8); break;
-            }
-#undef REALB_TOPK_ROWS
-        } else {
-            blocks = min(min(ceil_div(T, 16), 2 * num_cus), max_blocks);      // 16 waves (tokens in flight) per block, two blocks per CU
-            const int epl = ceil_div(E, 64);
-#define REALB_TOPK(EPL)                                                                                      \
-    hipLaunchKernelGGL(topk_hist_kernel<EPL>, dim3(blocks), dim3(1024), lds, s, logits, is_vision, T, E, k, \
-                       topk_ids, topk_w, hist_part)
-            if (epl == 1) REALB_TOPK(1);
-            else if (epl == 2) REALB_TOPK(2);
-            else if (epl <= 4) REALB_TOPK(4);
-            else REALB_TOPK(8);
-#undef REALB_TOPK
+                       int E, int k, int D, int32_t* topk_ids, float* topk_w, int32_t* rank_part, const SideJobs& jobs, int* per_block,
+                       hipStream_t s) {
+    *per_block = 0;
+    if (T <= 0) return 0;
+    const bool rows = E <= 128 && E % 16 == 0;                  // four tokens per wave
+    const int unit = rows ? 64 : 16;                            // tokens in flight per block of 16 waves
+    const int most = min(min(ceil_div(T, unit), 2 * num_cus), max_blocks);      // two blocks per CU
+    const int pb = *per_block = ceil_div(ceil_div(T, most), unit) * unit;
+    const int blocks = ceil_div(T, pb);
+    const size_t lds = 2 * (size_t)E * sizeof(int32_t);
+    const dim3 grid(blocks + jobs.blocks()), threads(kTopkThreads);
+#define REALB_TOPK(KERNEL) \
+    hipLaunchKernelGGL(KERNEL, grid, threads, lds, s, logits, is_vision, T, E, k, topk_ids, topk_w, hist_part, blocks, pb, D, rank_part, jobs)
+    if (rows) {
+        switch (E / 16) {
+            case 1: REALB_TOPK(topk_hist_rows_kernel<1>); break;
+            case 2: REALB_TOPK(topk_hist_rows_kernel<2>); break;
+            case 3: REALB_TOPK(topk_hist_rows_kernel<3>); break;
+            case 4: REALB_TOPK(topk_hist_rows_kernel<4>); break;
+            case 5: REALB_TOPK(topk_hist_rows_kernel<5>); break;
+            case 6: REALB_TOPK(topk_hist_rows_kernel<6>); break;
+            case 7: REALB_TOPK(topk_hist_rows_kernel<7>); break;
+            default: REALB_TOPK(topk_hist_rows_kernel<8>); break;
         }
+    } else {
+        const int epl = ceil_div(E, 64);
+        if (epl == 1) REALB_TOPK(topk_hist_kernel<1>);
+        else if (epl == 2) REALB_TOPK(topk_hist_kernel<2>);
+        else if (epl <= 4) REALB_TOPK(topk_hist_kernel<4>);
+        else REALB_TOPK(topk_hist_kernel<8>);
     }
+#undef REALB_TOPK
     return blocks;
 }
 
@@ -233,19 +251,28 @@ static int launch_topk(int num_cus, int max_blocks, int32_t* hist_part, const fl
 static int launch_route_stats(int num_cus, int max_blocks, int32_t* hist_part, const float* logits,
                               const uint8_t* is_vision, int T, int E, int k, int D, int32_t* topk_ids, float* topk_w,
                               int32_t* expert_cnt, int32_t* expert_vis, int32_t* rank_load, int32_t* rank_vis, hipStream_t s) {
-    const int blocks = launch_topk(num_cus, max_blocks, hist_part, logits, is_vision, T, E, k, topk_ids, topk_w, s);
+    int per_block = 0;
+    const int blocks = launch_topk(num_cus, max_blocks, hist_part, logits, is_vision, T, E, k, D, topk_ids, topk_w, nullptr, SideJobs{},
+                                   &per_block, s);
     hipLaunchKernelGGL(hist_reduce_kernel, dim3(D), dim3(1024), 2 * (size_t)(E / D) * sizeof(int32_t), s, hist_part, blocks, E, D,
                        expert_cnt, expert_vis, rank_load, rank_vis);
     REALB_HIP(hipGetLastError());
     return REALB_OK;
 }
 
-// Routing for the layer call: only the top-k + histogram kernel; the reduce is fused with the permutation's count kernel
-// (route_and_index in permute.hip).  Returns the number of partial histograms, or a negative error code.
-int route_topk_only(Ctx* c, const float* logits, const uint8_t* is_vision, int T, int32_t* topk_ids, float* topk_w, hipStream_t s) {
+// Routing for the layer call: only the top-k + histogram kernel; what follows it is route_finish_kernel (permute.hip).  The
+// per-rank partial counts (*rank_part) go to the permutation's chunk counters, which this path does not use, or, where
+// those are too few (many ranks, few assignments), behind as many partial histograms as then fit.  Returns the number of partial histograms, or a negative error code.
+int route_topk_only(Ctx* c, const float* logits, const uint8_t* is_vision, int T, int32_t* topk_ids, float* topk_w, const SideJobs& jobs,
+                    int* per_block, int32_t** rank_part, hipStream_t s) {
     REALB_REQUIRE(T >= 0 && T <= c->cfg.T_max, REALB_ECAP, "T=%d outside [0, T_max=%d]", T, c->cfg.T_max);
     REALB_REQUIRE(T == 0 || (logits && is_vision && topk_ids && topk_w), REALB_EINVAL, "NULL argument");
-    const int blocks = launch_topk(c->num_cus, kRouteBlocksMax, c->hist_part, logits, is_vision, T, c->cfg.E, c->cfg.k, topk_ids, topk_w, s);
+    const int E = c->cfg.E, D = c->cfg.D;
+    const bool roomy = (size_t)c->n_chunks_max * c->n_local >= (size_t)kRouteBlocksMax * 2 * D;
+    const int max_blocks = roomy ? kRouteBlocksMax : kRouteBlocksMax * E / (E + D);
+    *rank_part = roomy ? c->wave_cnt : c->hist_part + (size_t)max_blocks * 2 * E;
+    const int blocks = launch_topk(c->num_cus, max_blocks, c->hist_part, logits, is_vision, T, E, c->cfg.k, D, topk_ids, topk_w, *rank_part, jobs,
+                                   per_block, s);
     REALB_HIP(hipGetLastError());
     return blocks;
 }

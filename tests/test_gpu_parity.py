@@ -400,6 +400,52 @@ def test_layer_forward_policy_decides(R, case):
     assert rel_fro(obf.bits_to_f64(R.bits_from_bf16(b.out)), oo["out"]) <= tol
 
 
+@pytest.mark.parametrize("shape,T,rank,reached", [
+    (dict(), 2049, 0, {1}), (dict(), 2500, 5, {0}),                  # the policy says FP4 on the hot rank, BF16 on a cold one
+    (dict(E=64, k=2, D=64), 2100, 0, {1}),                           # one expert per rank
+    (dict(E=24, k=3, D=2), 4133, 0, {0, 1}),                         # depends on M; a wave per token, ragged routing blocks
+])
+def test_layer_call_decides_on_the_device_as_the_host_does(R, shape, T, rank, reached):
+    """With the decision open the layer call enqueues its encoders and GEMMs before the host knows the statistics, and they
+    evaluate the policy on the device: outputs must be, bit for bit, those of the call that is forced to the precision the
+    host reports, in every placement of the encoder and from every value of M that makes a difference."""
+    from paper_2604_19503_amd.binding import default_config
+    cfg = W.scaled(W.CONFIGS["c2"], T=T, H=256, I=128, **shape)
+    rcfg = default_config(cfg.T, cfg.E, cfg.k, cfg.D, cfg.H, cfg.I)
+    ctx = R.Context(rcfg)
+    inp = W.gen_layer(cfg, 51)
+    x, w13, w2 = (R.bf16_from_bits(inp[n]) for n in ("x", "w13", "w2"))
+    lg = torch.from_numpy(inp["logits"]).cuda(); isv = torch.from_numpy(inp["is_vision"]).cuda()
+    ids, _ = orouter.topk_route(inp["logits"], cfg.k)
+    _, _, load, vis = orouter.route_counts(ids, inp["is_vision"], cfg.E, cfg.D)
+    b = R.LayerBuffers(rcfg, cfg.T)
+    ref = {}
+    for prec in (R.BF16, R.FP4):
+        ctx.layer_forward(ctx.make_io(lg, isv, x, w13, w2, b, rank, force=prec, overlap=0))
+        _sync()
+        ref[prec] = (b.out.clone(), b.assign_to_row.clone(), b.expert_offsets.clone())
+    seen = set()
+    for overlap in (0, 1, 3, 2):
+        for M in (0.9, 1.0, 0.0):
+            _say(f"device decision {shape} T={T} rank={rank} overlap={overlap} M={M}")
+            want = opol.select_precision(load, vis, cfg.T, cfg.k, M)
+            ctx.M = M
+            io = ctx.make_io(lg, isv, x, w13, w2, b, rank, overlap=overlap)
+            b.out.fill_(float("nan")); b.x_q.fill_(0x77); b.h_mid.fill_(float("nan"))
+            if overlap != 2:
+                b.w13_q.fill_(0x77); b.w2_q.fill_(0x77)
+            else:
+                ctx.quantize_experts_fp4(w13, w2, b)
+            prec = ctx.layer_forward(io)
+            _sync()
+            assert list(io.prec_host[:cfg.D]) == list(want[0]) and io.M_after == want[2] == ctx.M and io.ib_global == want[1]
+            seen.add(prec)
+            for got, r in zip((b.out, b.assign_to_row, b.expert_offsets), ref[prec]):
+                assert torch.equal(got.view(torch.int16), r.view(torch.int16))
+    assert seen == reached
+    ctx.close()
+
+
 @pytest.mark.parametrize("T", [1, 5, 63, 257, 1000])
 def test_fused_gather_layer_equals_step_calls_for_odd_batch_sizes(R, T):
     """realb_layer_forward fuses the permutation's gather into the gate/up GEMM (rows fetched through
