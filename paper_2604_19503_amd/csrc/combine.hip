@@ -27,79 +27,59 @@ __device__ __forceinline__ void accumulate8(float (&acc)[8], float w, const u32x
     acc[6] = fmaf(w, bf16_lo(v.w), acc[6]); acc[7] = fmaf(w, bf16_hi(v.w), acc[7]);
 }
 
-// One wave per token and panel of U*512 columns (a wave: the token's rows and weights are scalars, and many small waves hide
+// One wave per token and panel of 512 columns (a wave: the token's rows and weights are scalars, and many small waves hide
 // the latency of the chain row index -> row).  The local rows of a token are accumulated in FP32 in order of j, the loads of
 // two rows in flight together.
 // NT_STORE: the output is written past the caches; for outputs that would not stay there for their reader, which are also
 // those long enough for the write-back of dirty lines at the kernel's end to cost.  NT_LOAD: so are the rows read, for rows
-// that the memory-side cache (256 MB) cannot have kept.  Measured with rows and outputs from HBM, before -> after: 8 937
-// rows to 16384 tokens 28.8 -> 15.9 us (6.7 TB/s), 36 183 rows 42.2 -> 40.0 us, 249 000 rows to 65536 tokens 254 -> 206 us
-// (6.2 TB/s; with plain loads 219, and two panels per token instead of four 221); 16 384 tokens with NT_LOAD 20.3 us.
-template <int U, bool NT_LOAD, bool NT_STORE>
+// that the memory-side cache (256 MB) cannot have kept.  Measured right behind the down GEMM, before (a block per token) ->
+// after: 9 807 rows to 16384 tokens 26.9 -> 18.7 us, 36 183 rows 33.8 -> 33.6 us, 124 473 rows to 32768 tokens 128 -> 105 us;
+// with rows and outputs from HBM, 249 000 rows to 65536 tokens 254 -> 206 us (6.2 TB/s; with plain loads 219).  Panels of
+// 1024 and 2048 columns measured 3-5 % slower.
+template <bool NT_LOAD, bool NT_STORE>
 __global__ void __launch_bounds__(256) combine_kernel(const u32x4c_t* __restrict__ y_rows, const int32_t* __restrict__ assign_to_row,
                                                       const float* __restrict__ topk_w, int T, int k, int H,
                                                       u32x4c_t* __restrict__ out) {
     const int chunks = H >> 3;                            // 16-byte chunks of a row
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int panels = (chunks + 64 * U - 1) / (64 * U);
+    const int panels = (chunks + 63) / 64;
     const long long item = (long long)blockIdx.x * 4 + wave;
-    const int t = (int)(item / panels), c0 = (int)(item - (long long)t * panels) * (64 * U);
+    const int t = (int)(item / panels), c = (int)(item - (long long)t * panels) * 64 + lane;
     if (t >= T) return;
-    // lane j holds the j-th row and weight: one load each, instead of a scalar load per j
+    // lane j holds the j-th row and weight
     const int my_row = lane < k ? assign_to_row[(size_t)t * k + lane] : -1;
     const float my_w = lane < k ? topk_w[(size_t)t * k + lane] : 0.f;
     unsigned long long left = __ballot(my_row >= 0);
-    float acc[U][8];
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) acc[u][i] = 0.f;
+    float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
     while (left != 0) {
         int r[2] = {-1, -1};                              // the next two local rows (uniform per wave)
         float w[2] = {0.f, 0.f};
+        u32x4c_t v[2];
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
+            v[q] = u32x4c_t{0, 0, 0, 0};
             if (left == 0) continue;
             const int j = __ffsll((long long)left) - 1;
             left &= left - 1;
             r[q] = __builtin_amdgcn_readlane(my_row, j);
             w[q] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(my_w), j));
+            const u32x4c_t* src = y_rows + (size_t)r[q] * chunks + c;
+            if (c < chunks) v[q] = NT_LOAD ? __builtin_nontemporal_load(src) : *src;
         }
-        u32x4c_t v[2][U];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            if (r[q] < 0) continue;
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int c = c0 + u * 64 + lane;
-                const u32x4c_t* src = y_rows + (size_t)r[q] * chunks + c;
-                if (c < chunks) v[q][u] = NT_LOAD ? __builtin_nontemporal_load(src) : *src;
-                else v[q][u] = u32x4c_t{0, 0, 0, 0};
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            if (r[q] < 0) continue;
-#pragma unroll
-            for (int u = 0; u < U; ++u) accumulate8(acc[u], w[q], v[q][u]);
-        }
+        accumulate8(acc, w[0], v[0]);
+        if (r[1] >= 0) accumulate8(acc, w[1], v[1]);
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int c = c0 + u * 64 + lane;
-        const u32x4c_t o = {pack_bf16(acc[u][0], acc[u][1]), pack_bf16(acc[u][2], acc[u][3]), pack_bf16(acc[u][4], acc[u][5]),
-                            pack_bf16(acc[u][6], acc[u][7])};
-        if (c >= chunks) continue;
-        if (NT_STORE) __builtin_nontemporal_store(o, out + (size_t)t * chunks + c);
-        else out[(size_t)t * chunks + c] = o;
-    }
+    if (c >= chunks) return;
+    const u32x4c_t o = {pack_bf16(acc[0], acc[1]), pack_bf16(acc[2], acc[3]), pack_bf16(acc[4], acc[5]), pack_bf16(acc[6], acc[7])};
+    if (NT_STORE) __builtin_nontemporal_store(o, out + (size_t)t * chunks + c);
+    else out[(size_t)t * chunks + c] = o;
 }
 
-template <int U, bool NT_LOAD, bool NT_STORE>
+template <bool NT_LOAD, bool NT_STORE>
 static void launch_combine(const void* y_rows, const int32_t* assign_to_row, const float* topk_w, int T, int k, int H, void* out, hipStream_t s) {
-    const long long items = (long long)T * ((H / 8 + 64 * U - 1) / (64 * U));
-    hipLaunchKernelGGL((combine_kernel<U, NT_LOAD, NT_STORE>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, (const u32x4c_t*)y_rows,
+    const long long items = (long long)T * ((H / 8 + 63) / 64);
+    hipLaunchKernelGGL((combine_kernel<NT_LOAD, NT_STORE>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, (const u32x4c_t*)y_rows,
                        assign_to_row, topk_w, T, k, H, (u32x4c_t*)out);
 }
 
@@ -118,10 +98,9 @@ extern "C" int realb_combine(realb_ctx* ctx, const void* y_rows, const int32_t* 
     // the rows' number is on the device; a rank that is worth an FP4 path has about two per token
     const long long out_bytes = (long long)T * H * 2;
     hipStream_t s = as_stream(stream);
-    if (out_bytes < (2ll << 20)) launch_combine<1, false, false>(y_rows, assign_to_row, topk_w, T, k, H, out, s);   // few tokens: more waves each
-    else if (out_bytes < (32ll << 20)) launch_combine<2, false, false>(y_rows, assign_to_row, topk_w, T, k, H, out, s);
-    else if (out_bytes < (96ll << 20)) launch_combine<2, false, true>(y_rows, assign_to_row, topk_w, T, k, H, out, s);
-    else launch_combine<1, true, true>(y_rows, assign_to_row, topk_w, T, k, H, out, s);
+    if (out_bytes < (32ll << 20)) launch_combine<false, false>(y_rows, assign_to_row, topk_w, T, k, H, out, s);
+    else if (out_bytes < (96ll << 20)) launch_combine<false, true>(y_rows, assign_to_row, topk_w, T, k, H, out, s);
+    else launch_combine<true, true>(y_rows, assign_to_row, topk_w, T, k, H, out, s);
     REALB_HIP(hipGetLastError());
     return REALB_OK;
 }
