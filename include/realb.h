@@ -129,8 +129,9 @@ int realb_route_stats_static(const float* logits, const uint8_t* is_vision, int 
  * hotspot set {d : IB_d > C}, FP4 iff hotspot and R_vd > M (Sec. "Real-time
  * Modality-aware LB Scheduling", "LB Gate").  force = REALB_BF16 / REALB_FP4
  * overrides the policy for every rank and leaves M untouched.
- * Copies rank_load / rank_vis (device, [D]) to the host and SYNCHRONISES the
- * stream; evaluates the policy on the host; updates the context's M.
+ * Brings rank_load / rank_vis (device, [D]) to the host and waits for them, i.e. for
+ * everything enqueued on the stream before the call; evaluates the policy on the host;
+ * updates the context's M.
  *   prec_host [D] out, ib_global_host / M_after_host: optional (may be NULL). */
 int realb_select_precision(realb_ctx* ctx, const int32_t* rank_load, const int32_t* rank_vis, int T,
                            int force, int32_t* prec_host, double* ib_global_host, double* M_after_host,

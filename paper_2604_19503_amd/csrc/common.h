@@ -28,12 +28,13 @@ struct Ctx {
     int n_chunks_max;
     int32_t* hist_part;    // [kRouteBlocksMax, 2*E]  per-block partial histograms of route_stats
     // pinned host staging for the policy's inputs
-    int32_t* stats_host;   // [2*D]: rank loads, rank vision loads (copy target of realb_select_precision)
-    unsigned long long* stats_words;   // [2*D], host-coherent: the same, written by the layer call's reduce block, each word
-                                       // tagged with the call's sequence number (see hist_reduce_body)
+    int32_t* stats_host;   // [2*D]: rank loads, rank vision loads
+    unsigned long long* stats_words;   // [2*D], host-coherent: the same, written by the layer call's reduce blocks or for
+                                       // realb_select_precision, each word tagged with the call's sequence number
+                                       // (see hist_reduce_body)
     unsigned long long* start_word;    // behind them: c->start_seq once the gate/up GEMM of a prefetching call has started
     int start_seq;
-    int stats_seq;         // sequence number of the last layer call's statistics (never 0)
+    int stats_seq;         // sequence number of the last set of statistics words (never 0)
     hipStream_t side;      // side stream for the cross-layer prefetch
     hipEvent_t ev_fork;    // orders a rank call's prefetch behind the work before its GEMMs
     hipEvent_t ev_prefetch;   // end of the last cross-layer prefetch on the side stream
@@ -56,6 +57,7 @@ PrecisionSource precision_source(const Ctx* c, int T, int force, int rank, const
 // The layer call's two GEMMs, in the precision `prec` says or will say (gate/up: rows fetched through row_to_assign).
 int launch_layer_gate_up(Ctx* c, const PrecisionSource& prec, const realb_layer_io* io, bool announce, hipStream_t s);
 int launch_layer_down(Ctx* c, const PrecisionSource& prec, const realb_layer_io* io, hipStream_t s);
+int next_stats_seq(Ctx* c);      // sequence number of the next set of statistics words
 int perm_block_threads(int T, int k);
 // Waits until the gate/up GEMM that was launched with start_seq has started.
 int wait_for_gemm_start(Ctx* c, hipStream_t s);

@@ -225,13 +225,13 @@ static int layer_forward_steps(realb_ctx* ctx, realb_layer_io* io, void* stream)
     }
     stage_mark(c, s, 0);
     // The statistics reach pinned host memory with the histogram reduce, tagged with this call's sequence number.
-    if (++c->stats_seq <= 0) c->stats_seq = 1;
-    rc = route_and_index(c, io, c->stats_seq, beside_topk, beside_finish, s);
+    const int seq = next_stats_seq(c);
+    rc = route_and_index(c, io, seq, beside_topk, beside_finish, s);
     if (rc != REALB_OK) return rc;
     stage_mark(c, s, 1);
     stage_mark(c, s, 2);
     auto wait_for_statistics = [&]() {
-        return select_precision_pinned(c, io->T, io->force, io->prec_host, &io->ib_global, &io->M_after, c->stats_seq, s);
+        return select_precision_pinned(c, io->T, io->force, io->prec_host, &io->ib_global, &io->M_after, seq, s);
     };
     if (!ahead) {
         rc = wait_for_statistics();
