@@ -312,21 +312,22 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 // 92 MB of W13 is a matter of bytes in flight.  So:
 //   - 128- and 64-row tiles have three LDS stages (48 or 40 KB each), and the barrier of a K-step waits only for the next
 //     step's transfers (s_waitcnt vmcnt(n), n > 0), leaving those of the step behind it in flight;
-//   - 64 x 128 tiles double the number of blocks and have six stages (five steps in flight); four waves multiply, eight
-//     move data.
-// Measured, BF16, weights from HBM, gate/up + down us: 24 tokens (61 rows) 49.9 + 27.8 -> 18.8 + 13.4 (138 MB: 4.3 TB/s);
-// 192 tokens 50.9 + 28.2 -> 22 + 14; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.  A split of the contraction over the
+//   - 64 x 128 and (BF16) 64 x 64 tiles double the number of blocks once or twice and have six or nine stages (five or
+//     eight steps in flight); four or two waves multiply, eight move data.
+// Measured, BF16, weights from HBM, gate/up + down us: 24 tokens (61 rows) 49.9 + 27.8 -> 19.6 + 11.6 (138 MB: 4.4 TB/s);
+// 192 tokens 50.9 + 28.2 -> 22.5 + 13.2; 1 token 19 + 14 with 64 x 256 tiles -> 13.3 + 10.2; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.  A split of the contraction over the
 // waves of a block with operands straight in registers (no LDS) measured 34 + 18 at 24 tokens and was dropped.
 // The accumulation order along K is the same for every shape and that of the other kernel, so results are bit-identical.
 constexpr int KB = 128;                    // bytes of each operand row per K-step
 // Geometry of a block tile: 64*MT activation rows x TW weight rows, 8 waves.  TW = 256: a 2 x 4 grid of waves of 32*MT x 64
-// each.  TW = 128 (MT = 1 only): waves 0..3 are that grid's first two columns, waves 4..7 only move data.
+// each.  TW = 128 and 64 (MT = 1 only): waves 0..3 (0..1) are that grid's first two columns (first column), the others only
+// move data.
 template <int MT, int TW>
 struct TileGeo {
-    static_assert(TW == 256 || (TW == 128 && MT == 1), "tile shapes");
+    static_assert(TW == 256 || ((TW == 128 || TW == 64) && MT == 1), "tile shapes");
     static constexpr int TA = 64 * MT;                 // activation rows of the block tile
     static constexpr int WN = TW / 64;                 // waves along the weight rows
-    static constexpr int NS = MT == 4 ? 2 : TW == 256 ? 3 : 6;   // LDS stages: 2 x 64 KB, 3 x 48 or 40 KB, 6 x 24 KB
+    static constexpr int NS = MT == 4 ? 2 : TW == 256 ? 3 : TW == 128 ? 6 : 9;   // LDS stages: 2 x 64 KB, 3 x 48 or 40 KB, 6 x 24 KB, 9 x 16 KB
     static constexpr int OPS_A = MT;                   // 8-row transfers per wave and K-step: activations
     static constexpr int OPS_W = TW / 64;              //                                    : weights
     static constexpr int W_ROWS = TW / 8;              // weight rows a wave moves
@@ -352,8 +353,8 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = TW == 256 ? wave >> 2 : (wave >> 1) & 1, wn = wave & (G::WN - 1);
-    const bool multiplies = TW == 256 || wave < 4;
+    const int wm = TW == 256 ? wave >> 2 : (wave / G::WN) & 1, wn = wave & (G::WN - 1);
+    const bool multiplies = TW == 256 || wave < 2 * G::WN;
     const int n_tiles_n = GATEUP ? p.n_out / COLS : (p.n_out + COLS - 1) / COLS;
     const int li = lane & 31, half = lane >> 5;
 
@@ -404,20 +405,22 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     // 16-byte part a lane fetches in instruction j: (lane&7) ^ key, key = (R>>1)&7 = (4*(j&1) + (lane>>4)) & 7
     // for LDS row R = 8*j + prow (mod 16) of the j-th 8-row group of the tile.
     auto part16 = [&](int q) __attribute__((always_inline)) { return (uint32_t)(((lane & 7) ^ ((q * 4 + (lane >> 4)) & 7)) << 4); };
+    auto part_w = [&](int j) __attribute__((always_inline)) { return (wave * G::OPS_W + j) & 1; };
     auto part_a = [&](int j) __attribute__((always_inline)) { return (wave * MT + j) & 1; };   // activations: 8-row group wave*MT + j
     // Weights: LDS position R holds weight-tile row (R & ~31) | w_row_of_lane(R & 31), which for
     // R & 31 = 8*j + prow is 16*((prow>>2)&1) + 4*j + (prow&3): instruction j is 4*j rows below
     // instruction 0, a scalar offset.  Per lane only the two part offsets differ (by parity of j).
     uint32_t b_voff[2];
     {
-        // (W_ROWS = 16: a wave's two instructions are the first or the last two of a 32-row group, by its parity)
-        const int br0 = (TW == 256 ? wave * 32 : (wave >> 1) * 32 + (wave & 1) * 8) + (((prow >> 2) & 1) << 4) + (prow & 3);
+        // (a wave's first 8-row group is the g-th of a 32-row group, g = wave * OPS_W mod 4)
+        const int br0 = (wave * G::OPS_W >> 2) * 32 + (wave * G::OPS_W & 3) * 4 + (((prow >> 2) & 1) << 4) + (prow & 3);
 #pragma unroll
         for (int q = 0; q < 2; ++q) b_voff[q] = (uint32_t)w_tile_row<GATEUP, TW / 2>(br0, 0, I_up) * rowbytes + part16(q);
     }
     int a_last = 0;                                       // scalar: last existing row of the tile being fetched
     uint32_t a_goff[GATHER ? G::OPS_A : 1];               // GATHER: byte offset of this lane's source row, per instruction
-    const int srow = (TW == 256 ? wave : wave & 3) * 32 + (lane >> 1), swhich = lane & 1;
+    const int wgrp = TW == 256 ? wave : wave & (TW / 32 - 1);              // the group of 32 weight rows whose scales this wave moves
+    const int srow = wgrp * 32 + (lane >> 1), swhich = lane & 1;
     const int sgrp = wave & (2 * MT - 1);                 // the group of 32 activation rows whose scales this wave moves
     int sa_idx = 0, sb_idx = 0;                           // FP4: dword index of this lane's scale word, K-step 0
     const uint8_t* a_tile = nullptr;                      // scalar: first activation row / weight row of the tile being fetched
@@ -469,13 +472,13 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
                 const int ko = min(2 * k + swhich, kd - 1) * 32;
                 uint8_t* l = smem + G::SC_BASE + dstg * G::SC_STAGE;
                 if (op == 0) lds_dma4(reinterpret_cast<const uint32_t*>(p.As) + (uint32_t)(sa_idx + ko), l + sgrp * 256);
-                else lds_dma4(reinterpret_cast<const uint32_t*>(p.Ws) + (uint32_t)(sb_idx + ko), l + G::SC_W + (TW == 256 ? wave : wave & 3) * 256);
+                else lds_dma4(reinterpret_cast<const uint32_t*>(p.Ws) + (uint32_t)(sb_idx + ko), l + G::SC_W + wgrp * 256);
             }
         } else {
             const int j = (op - 2) & 3;
             const bool halfstep = tail_half && k == nks - 1;
             // half step: lanes of parts 4..7 fetch parts 0..3 again (the row has only 64 bytes left)
-            const int q = op < 6 ? part_a(j) : j & 1;
+            const int q = op < 6 ? part_a(j) : part_w(j);
             const uint32_t koff = (uint32_t)(k * KB) - (halfstep ? (uint32_t)(((lane << 4) ^ (q << 6)) & 64) : 0u);
             uint8_t* l = smem + dstg * G::STAGE;
             if (op < 6) {
@@ -485,7 +488,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
                 else v = (uint32_t)min(wave * (8 * MT) + j * 8 + prow, a_last) * rowbytes + part16(part_a(j));   // rows past the segment: its last row again
                 lds_dma16(a_tile + (v + koff), l);
             } else {
-                lds_dma16(b_tile + (size_t)(j * 4) * rowbytes + (b_voff[j & 1] + koff), l + G::REGION_W + (wave * G::OPS_W + j) * 1024);
+                lds_dma16(b_tile + (size_t)(j * 4) * rowbytes + (b_voff[q] + koff), l + G::REGION_W + (wave * G::OPS_W + j) * 1024);
             }
         }
     };
@@ -517,14 +520,25 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         for (int op = 0; op < 10; ++op)
             if (op < 2 + G::OPS_A || (op >= 6 && op < 6 + G::OPS_W)) issue(op, k, dstg);
     };
+    // Fill the stages, then wait for the first step only: draining them all here would leave the memory system idle for a
+    // latency.  (Where the producer crosses a tile boundary already here, the gather entries it then reads must have landed.)
+    constexpr int OPS = G::OPS_A + G::OPS_W + (FP4 ? 2 : 0);             // transfers per wave and step
+    auto step_forward = [&]() __attribute__((always_inline)) {
+        if (GATHER && nks < G::NS) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        advance();
+    };
     issue_step(0, 0);
 #pragma unroll
-    for (int q = 1; q < G::NS - 1; ++q) { advance(); issue_step(pk, q); }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    advance();
+    for (int q = 1; q < G::NS - 1; ++q) { step_forward(); issue_step(pk, q); }
+    step_forward();
+    if constexpr (TW < 256) {
+        issue_step(pk, G::NS - 1);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 1) * OPS) : "memory");
+    } else {
 #pragma unroll
-    for (int j = 0; j < G::OPS_A; ++j) issue(2 + j, pk, G::NS - 1);      // first half of the step that fills the last stage (see below)
+        for (int j = 0; j < G::OPS_A; ++j) issue(2 + j, pk, G::NS - 1);  // first half of the step that fills the last stage (see below)
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 2) * OPS + G::OPS_A) : "memory");
+    }
 
     // One flat loop over the (tile, K-step) pairs of this block, with a single copy of the K-step code:
     // the steps of a tile follow each other without a seam, and the producer runs ahead across tile
@@ -544,6 +558,86 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
     int cur_row0 = ti.row0, cur_rows = ti.seg_hi - ti.row0, cur_n0 = ti.n0;
+
+    // Ends a tile: epilogue, accumulators back to zero, the block's next tile; false if there is none.
+    auto finish_tile = [&]() __attribute__((always_inline)) {
+        if (!multiplies || (!GATEUP && cur_n0 + wn * 64 >= p.n_out)) {}   // columns behind the output's end
+        else if (nt_out) epilogue<FP4, GATEUP, MT, 2, true>(p, acc, cur_row0, cur_rows, cur_n0, wm, wn, li, half);
+        else epilogue<FP4, GATEUP, MT, 2, false>(p, acc, cur_row0, cur_rows, cur_n0, wm, wn, li, half);
+        tile += nslots;
+        if (tile >= tile_hi) return false;
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        ti = decode(tile);
+        cur_row0 = ti.row0; cur_rows = ti.seg_hi - ti.row0; cur_n0 = ti.n0;
+        ks = 0;
+        return true;
+    };
+
+    if constexpr (TW < 256) {
+        // One multiplying wave per SIMD, and a K-slice is two MFMAs (64 cycles), less than the latency of an LDS read: reading
+        // a slice ahead would expose that latency four times per step (24 tokens, down GEMM: 12.8 against 11.6 us).  Here a wave reads all of the next step's fragments
+        // right behind the barrier that publishes it, into the other register set, and multiplies this step meanwhile.
+        u32x4_t xa[2][4], xb[2][4][2];
+        u32x2_t xra[2], xrb[2][2];
+        auto read_step = [&](int set, int stage) __attribute__((always_inline)) {
+            if (!multiplies) return;
+            const uint8_t* st = smem + stage * G::STAGE;
+            if constexpr (FP4) {
+                const uint8_t* sc = smem + G::SC_BASE + stage * G::SC_STAGE;
+                xra[set] = *reinterpret_cast<const u32x2_t*>(sc + (wm * 32 + li) * 8);
+#pragma unroll
+                for (int t = 0; t < 2; ++t) xrb[set][t] = *reinterpret_cast<const u32x2_t*>(sc + G::SC_W + (b_pos[t] + li) * 8);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                xa[set][q] = *reinterpret_cast<const u32x4_t*>(st + a_base + (f_off0 ^ (q << 5)));
+#pragma unroll
+                for (int t = 0; t < 2; ++t) xb[set][q][t] = *reinterpret_cast<const u32x4_t*>(st + G::REGION_W + b_pos[t] * KB + (f_off0 ^ (q << 5)));
+            }
+        };
+        read_step(0, 0);
+        auto step = [&](int set) __attribute__((always_inline)) {
+            const bool last = ks == nks - 1;
+            const bool full = !(last && tail_half);
+            // the next step has landed, this wave's reads of the current stage are done: its transfers may be replaced
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 2) * OPS) : "memory");
+            left = stg;
+            stg = stg + 1 == G::NS ? 0 : stg + 1;
+            advance();
+            read_step(set ^ 1, stg);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (multiplies && (q < 2 || full)) {
+                    const int wa = FP4 ? (int)((q < 2 ? xra[set].x : xra[set].y) >> (half * 8)) : 0;
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) {
+                        const int wb = FP4 ? (int)((q < 2 ? xrb[set][t].x : xrb[set][t].y) >> (half * 8)) : 0;
+                        if (q & 1) mma<FP4, 2>(acc[0][t], xb[set][q][t], xa[set][q], wb, wa);
+                        else mma<FP4, 0>(acc[0][t], xb[set][q][t], xa[set][q], wb, wa);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                if (q == 0) {
+#pragma unroll
+                    for (int op = FP4 ? 0 : 2; op < 3; ++op) issue(op, pk, left);
+                } else if (q - 1 < G::OPS_W) {
+                    issue(6 + q - 1, pk, left);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            ++ks;
+            return !last || finish_tile();
+        };
+        while (step(0) && step(1)) {}
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no transfer may still be writing this block's LDS when it ends
+        return;
+    }
 
     u32x4_t fa[2][MT], fb[2][2];                           // fragment double buffer (slice parity)
     int sa[MT][2], sb[2][2];                               // FP4: scale words of the step, [.][0] slices 0-1, [.][1] slices 2-3
@@ -642,7 +736,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         __builtin_amdgcn_sched_barrier(0);
         // the next step has landed; with more than two stages the transfers of those behind it stay in flight (hence no
         // __syncthreads(), whose release waits for every transfer); this wave's reads of the released stage are done
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 2) * (G::OPS_A + G::OPS_W + (FP4 ? 2 : 0))) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 2) * OPS) : "memory");
         left = stg;
         stg = stg + 1 == G::NS ? 0 : stg + 1;
         advance();
@@ -652,22 +746,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         take_scales();
 
         ++ks;
-        if (last) {
-            if (!multiplies || (!GATEUP && cur_n0 + wn * 64 >= p.n_out)) {}   // columns behind the output's end
-            else if (nt_out) epilogue<FP4, GATEUP, MT, 2, true>(p, acc, cur_row0, cur_rows, cur_n0, wm, wn, li, half);
-            else epilogue<FP4, GATEUP, MT, 2, false>(p, acc, cur_row0, cur_rows, cur_n0, wm, wn, li, half);
-            tile += nslots;
-            if (tile >= tile_hi) break;
-#pragma unroll
-            for (int i = 0; i < MT; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-            ti = decode(tile);
-            cur_row0 = ti.row0; cur_rows = ti.seg_hi - ti.row0; cur_n0 = ti.n0;
-            ks = 0;
-        }
+        if (last && !finish_tile()) break;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no transfer may still be writing this block's LDS when it ends
 }
@@ -677,8 +756,9 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 // as a full one, however empty it is; a round of 128-row tiles lasts 0.6 of it, 64-row tiles 0.4 (BF16, K = 2048: 50, 30
 // and 22 us).  Measured, BF16 gate/up: 13 162 rows 171 -> 149 us, 36 183 rows 377 -> 355 us.  With FP4 operands a round is
 // 13 us and the second pipeline start (3 us) eats what 128-row tiles would save behind whole rounds (50.6 -> 52.4 us), so
-// there they are used only when they hold all rows.  64 x 128 tiles need at least four K-steps: their producer may run
-// five steps ahead, and a tile's gather entries are fetched one tile ahead.
+// there they are used only when they hold all rows.  A block has at most one tile of a chosen small shape; forced to take
+// several, 64 x 128 tiles need at least four K-steps: their producer runs up to five steps ahead, and a tile's gather entries
+// are fetched one tile ahead.
 template <bool FP4, bool GATEUP, bool GATHER>
 __device__ __forceinline__ void tile_body(const GemmParams& p, uint8_t* smem) {
     if (p.start_word && blockIdx.x == 0 && threadIdx.x == 0)
@@ -700,8 +780,9 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, uint8_t* smem) {
         const unsigned long long holds = __ballot(before <= m_keep && m_keep < cum);
         const int c = holds == 0 ? 0x7FFFFFFF : __builtin_amdgcn_readlane(lo + (m_keep - before) * 256, __ffsll((long long)holds) - 1);
         const int n128 = wave_sum(tiles_of<128>(max(lo, c), hi)), n64 = wave_sum(tiles_of<64>(max(lo, c), hi));
-        const int nt128 = GATEUP ? p.n_out / 64 : p.n_out / 128;       // column tiles of 128 weight rows
-        if (n64 * nt128 <= slots && p.K >= (FP4 ? 1024 : 256)) { cut = c; rest = 0; }
+        const int nt64 = GATEUP ? p.n_out / 32 : p.n_out / 64, nt128 = nt64 / 2;      // column tiles of 64 and 128 weight rows
+        if (!FP4 && n64 * nt64 <= slots) { cut = c; rest = 3; }        // (FP4 weights are a quarter of the bytes)
+        else if (n64 * nt128 <= slots) { cut = c; rest = 0; }
         else if (n64 * nt <= slots) { cut = c; rest = 1; }
         else if (n128 * nt <= slots && (!FP4 || rounds == 0)) { cut = c; rest = 2; }
     } else if (p.tile_mode != 4) {
@@ -712,7 +793,8 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, uint8_t* smem) {
     if (cut < 0x7FFFFFFF) {
         if (rest == 2) tile_phase<FP4, GATEUP, GATHER, 2, 256>(p, smem, max(lo, cut), max(hi, cut), nt_out);
         else if (rest == 1) tile_phase<FP4, GATEUP, GATHER, 1, 256>(p, smem, max(lo, cut), max(hi, cut), nt_out);
-        else tile_phase<FP4, GATEUP, GATHER, 1, 128>(p, smem, max(lo, cut), max(hi, cut), nt_out);
+        else if (rest == 0) tile_phase<FP4, GATEUP, GATHER, 1, 128>(p, smem, max(lo, cut), max(hi, cut), nt_out);
+        else if constexpr (!FP4) tile_phase<FP4, GATEUP, GATHER, 1, 64>(p, smem, max(lo, cut), max(hi, cut), nt_out);
     }
 }
 
@@ -733,14 +815,14 @@ __global__ void __launch_bounds__(512, 1) ffn_tile_either_kernel(const GemmParam
 
 // One persistent block per CU, a multiple of 8 (XCDs); a prefetching layer call leaves some CUs to the weight encoder.
 static unsigned tile_grid(const GemmParams& p, bool gate_up, long long max_rows, const Ctx* c) {
-    const long long narrowest = gate_up ? p.n_out / 64 : p.n_out / 128;    // column tiles of the narrowest shape
+    const long long narrowest = gate_up ? p.n_out / 32 : p.n_out / 64;    // column tiles of the narrowest shape
     const long long total_max = ((max_rows + 63) / 64 + p.n_local) * narrowest;
     const long long avail = (long long)c->num_cus - c->gemm_reserve;
     const long long slots = avail >= 16 ? 8ll * (c->gemm_reserve > 0 ? avail / 8 : (avail + 7) / 8) : 8;
     return (unsigned)(total_max < slots ? 8 * ((total_max + 7) / 8) : slots);
 }
 constexpr size_t max_size(size_t a, size_t b) { return a > b ? a : b; }
-constexpr size_t kTileLds = max_size(TileGeo<4, 256>::LDS_BYTES, max_size(TileGeo<2, 256>::LDS_BYTES, TileGeo<1, 128>::LDS_BYTES));
+constexpr size_t kTileLds = max_size(TileGeo<4, 256>::LDS_BYTES, max_size(TileGeo<2, 256>::LDS_BYTES, max_size(TileGeo<1, 128>::LDS_BYTES, TileGeo<1, 64>::LDS_BYTES)));
 static_assert(TileGeo<1, 256>::LDS_BYTES <= kTileLds && kTileLds <= 160 * 1024, "LDS");
 
 template <typename K>
