@@ -219,8 +219,8 @@ int realb_grouped_moe_ffn_down(realb_ctx* ctx, int prec, const int32_t* expert_o
  * four K-steps: K >= 1024 on the FP4 path, K >= 256 on the BF16 path, else 1 is used),
  * 2 = register-staged 256x128 tiles with two blocks per CU, 8 = register-staged 256x256 tiles with
  * one block per CU (where the output width is a multiple of its tile, else 2).
- * Process-wide; outputs are bit-identical for every choice (the accumulation order along K
- * does not change).  REALB_EINVAL for any other value. */
+ * Process-wide; outputs are bit-identical for every choice but 0, which may sum the K-steps of some
+ * shapes in another order (FP32 rounding).  REALB_EINVAL for any other value. */
 int realb_set_gemm_tile(int wn);
 
 /* Unpermute + weighted combine (local part of the result combination):

@@ -332,8 +332,11 @@ def test_ffn_other_block_tiles_give_the_same_rows(R, case, tile):
 ])
 def test_tile_shapes_give_the_same_rows(R, H, I, segments):
     """Every tile shape of the direct-to-LDS kernel, and the shapes it picks by itself, on segment lengths at the edges of
-    the tiles: bit-identical to the register-staged kernel (same accumulation order along K), both precisions; rows
-    behind the last one stay unwritten."""
+    the tiles, both precisions: bit-identical to the register-staged kernel (same accumulation order along K), or, for the
+    shapes it picks, which may start at another K-step, within what FP32 sums in another order can do to a BF16 result: an
+    element whose two sums fall on different sides of a rounding boundary moves by one step, 2^-7 of its value at most
+    (2^-8 rms), and FP32 sums of 2048 products differ by some 1e-6 of the sum's terms, i.e. cross a boundary (spaced 2^-8)
+    for about one element in a thousand -- h included, 5e-4 in the norm; rows behind the last one stay unwritten."""
     from paper_2604_19503_amd.binding import default_config, set_gemm_tile
     nl, rows = len(segments), sum(segments)
     rcfg = default_config(max(rows, 1), nl, 1, 1, H, I)
@@ -362,7 +365,11 @@ def test_tile_shapes_give_the_same_rows(R, H, I, segments):
             if ref is None:
                 ref = got
                 assert bool(torch.isfinite(b.y_rows[:rows].float()).all()) and bool(torch.isnan(b.y_rows[rows:].float()).all())
-            assert torch.equal(got, ref), tile
+            if tile != 0:
+                assert torch.equal(got, ref), tile
+            elif rows:
+                a, r = got[:rows].view(torch.bfloat16).float(), ref[:rows].view(torch.bfloat16).float()
+                assert float((a - r).norm() / r.norm()) <= 5e-4 and bool(torch.isnan(b.y_rows[rows:].float()).all())
     ctx.close()
 
 
