@@ -328,7 +328,7 @@ struct TileGeo {
     static_assert(TW == 256 || ((TW == 128 || TW == 64) && MT == 1), "tile shapes");
     static constexpr int TA = 64 * MT;                 // activation rows of the block tile
     static constexpr int WN = TW / 64;                 // waves along the weight rows
-    static constexpr int NS = MT == 4 ? 2 : TW == 256 ? 3 : TW == 128 ? 6 : 9;   // LDS stages: 2 x 64 KB, 3 x 48 or 40 KB, 6 x 24 KB, 9 x 16 KB
+    static constexpr int NS = MT >= 3 ? 2 : TW == 256 ? 3 : TW == 128 ? 6 : 9;   // LDS stages: 2 x 64 or 56 KB, 3 x 48 or 40 KB, 6 x 24 KB, 9 x 16 KB
     static constexpr int OPS_A = MT;                   // 8-row transfers per wave and K-step: activations
     static constexpr int OPS_W = TW / 64;              //                                    : weights
     static constexpr int W_ROWS = TW / 8;              // weight rows a wave moves
@@ -422,7 +422,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     uint32_t a_goff[GATHER ? G::OPS_A : 1];               // GATHER: byte offset of this lane's source row, per instruction
     const int wgrp = TW == 256 ? wave : wave & (TW / 32 - 1);              // the group of 32 weight rows whose scales this wave moves
     const int srow = wgrp * 32 + (lane >> 1), swhich = lane & 1;
-    const int sgrp = wave & (2 * MT - 1);                 // the group of 32 activation rows whose scales this wave moves
+    const int sgrp = MT == 3 ? (wave < 6 ? wave : wave - 6) : wave & (2 * MT - 1);      // the group of 32 activation rows whose scales this wave moves
     int sa_idx = 0, sb_idx = 0;                           // FP4: dword index of this lane's scale word, K-step 0
     const uint8_t* a_tile = nullptr;                      // scalar: first activation row / weight row of the tile being fetched
     const uint8_t* b_tile = nullptr;
@@ -745,7 +745,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
                     if (FP4 && mt < 2) issue(mt, pk, left);
                     if (FP4 && MT == 1) issue(1, pk, left);
 #pragma unroll
-                    for (int q = 0; q < G::OPS_W / MT; ++q) issue(6 + mt * (G::OPS_W / MT) + q, pk, left);
+                    for (int q = mt * G::OPS_W / MT; q < (mt + 1) * G::OPS_W / MT; ++q) issue(6 + q, pk, left);
                 } else if (produce == 2) {
                     issue(2 + mt, pk, left);              // (left: the stage this step has just left)
                 }
@@ -776,10 +776,11 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
 // Which tiles: the whole rounds of 256 x 256 tiles first (a round = one tile on every block; the 256-row tile costs the least
 // per row), then what is left in the smallest shape that still fits ONE round.  A last round of 256-row tiles lasts as long
-// as a full one, however empty it is; a round of 128-row tiles lasts 0.6 of it, 64-row tiles 0.4 (BF16, K = 2048: 50, 30
-// and 22 us).  Measured, BF16 gate/up: 13 162 rows 171 -> 149 us, 36 183 rows 377 -> 355 us.  With FP4 operands a round is
-// 13 us and the second pipeline start (3 us) eats what 128-row tiles would save behind whole rounds (50.6 -> 52.4 us), so
-// there they are used only when they hold all rows.  A block has at most one tile of a chosen small shape; forced to take
+// as a full one, however empty it is; a round of 192-row tiles lasts 0.85 of it, 128-row tiles 0.6, 64-row tiles 0.4 (BF16,
+// K = 2048: 50, 43, 30 and 22 us).  Measured, BF16 gate/up: 13 162 rows 171 -> 149 us, 36 183 rows 377 -> 355 us; with the
+// 192-row tiles 3 548 rows 64.3 -> 58.0 us, FP4 20.6 -> 18.5 us.  With FP4 operands a round is 13 us and the second pipeline
+// start (3 us) eats what 192- or 128-row tiles would save behind whole rounds (50.6 -> 52.4 us), so there they are used only
+// when they hold all rows.  A block has at most one tile of a chosen small shape; forced to take
 // several, 64 x 128 tiles need at least four K-steps: their producer runs up to five steps ahead, and a tile's gather entries
 // are fetched one tile ahead.
 template <bool FP4, bool GATEUP, bool GATHER>
@@ -797,24 +798,31 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, uint8_t* smem) {
     if (p.tile_mode == 0) {
         const int mine = tiles_of<256>(lo, hi), cum = wave_inclusive_scan(mine);       // row tiles of the experts up to this lane's
         const int m_tiles = __builtin_amdgcn_readlane(cum, 63);
-        const int rounds = m_tiles * nt / slots;           // whole rounds of 256-row tiles
-        const int m_keep = rounds * slots / nt;            // row tiles that fill them
-        const int before = cum - mine;
-        const unsigned long long holds = __ballot(before <= m_keep && m_keep < cum);
-        const int c = holds == 0 ? 0x7FFFFFFF : __builtin_amdgcn_readlane(lo + (m_keep - before) * 256, __ffsll((long long)holds) - 1);
-        const int n128 = wave_sum(tiles_of<128>(max(lo, c), hi)), n64 = wave_sum(tiles_of<64>(max(lo, c), hi));
+        int c = 0;                                         // first row behind the whole rounds of 256-row tiles
+        if (m_tiles * nt >= slots) {
+            const int m_keep = m_tiles * nt / slots * slots / nt;      // row tiles that fill those rounds
+            const int before = cum - mine;
+            const unsigned long long holds = __ballot(before <= m_keep && m_keep < cum);
+            c = holds == 0 ? 0x7FFFFFFF : __builtin_amdgcn_readlane(lo + (m_keep - before) * 256, __ffsll((long long)holds) - 1);
+        }
+        const int tail = max(lo, c);
         const int nt64 = GATEUP ? p.n_out / 32 : p.n_out / 64, nt128 = nt64 / 2;      // column tiles of 64 and 128 weight rows
-        if (!FP4 && n64 * nt64 <= slots) { cut = c; rest = 3; }        // (FP4 weights are a quarter of the bytes)
-        else if (n64 * nt128 <= slots) { cut = c; rest = 0; }
-        else if (n64 * nt <= slots) { cut = c; rest = 1; }
-        else if (n128 * nt <= slots && (!FP4 || rounds == 0)) { cut = c; rest = 2; }
+        const int n64 = wave_sum(tiles_of<64>(tail, hi));
+        rest = 4;
+        if (n64 * nt <= slots) rest = !FP4 && n64 * nt64 <= slots ? 5 : n64 * nt128 <= slots ? 0 : 1;      // (FP4 weights are a quarter of the bytes)
+        else if (!FP4 || c == 0) {
+            if (wave_sum(tiles_of<128>(tail, hi)) * nt <= slots) rest = 2;
+            else if (wave_sum(tiles_of<192>(tail, hi)) * nt <= slots) rest = 3;
+        }
+        cut = rest == 4 ? 0x7FFFFFFF : c;
     } else if (p.tile_mode != 4) {
         cut = 0;
         rest = p.tile_mode != 5 ? p.tile_mode : p.K >= (FP4 ? 1024 : 256) ? 0 : 1;
     }
     if (cut > 0) tile_phase<FP4, GATEUP, GATHER, 4, 256>(p, smem, min(lo, cut), min(hi, cut), nt_out);
     if (cut < 0x7FFFFFFF) {
-        if (rest == 2) tile_phase<FP4, GATEUP, GATHER, 2, 256>(p, smem, max(lo, cut), max(hi, cut), nt_out);
+        if (rest == 3) tile_phase<FP4, GATEUP, GATHER, 3, 256>(p, smem, max(lo, cut), max(hi, cut), nt_out);
+        else if (rest == 2) tile_phase<FP4, GATEUP, GATHER, 2, 256>(p, smem, max(lo, cut), max(hi, cut), nt_out);
         else if (rest == 1) tile_phase<FP4, GATEUP, GATHER, 1, 256>(p, smem, max(lo, cut), max(hi, cut), nt_out);
         else if (rest == 0) tile_phase<FP4, GATEUP, GATHER, 1, 128>(p, smem, max(lo, cut), max(hi, cut), nt_out);
         else if constexpr (!FP4) tile_phase<FP4, GATEUP, GATHER, 1, 64>(p, smem, max(lo, cut), max(hi, cut), nt_out);
@@ -845,7 +853,7 @@ static unsigned tile_grid(const GemmParams& p, bool gate_up, long long max_rows,
     return (unsigned)(total_max < slots ? 8 * ((total_max + 7) / 8) : slots);
 }
 constexpr size_t max_size(size_t a, size_t b) { return a > b ? a : b; }
-constexpr size_t kTileLds = max_size(TileGeo<4, 256>::LDS_BYTES, max_size(TileGeo<2, 256>::LDS_BYTES, max_size(TileGeo<1, 128>::LDS_BYTES, TileGeo<1, 64>::LDS_BYTES)));
+constexpr size_t kTileLds = max_size(TileGeo<4, 256>::LDS_BYTES, max_size(max_size(TileGeo<3, 256>::LDS_BYTES, TileGeo<2, 256>::LDS_BYTES), max_size(TileGeo<1, 128>::LDS_BYTES, TileGeo<1, 64>::LDS_BYTES)));
 static_assert(TileGeo<1, 256>::LDS_BYTES <= kTileLds && kTileLds <= 160 * 1024, "LDS");
 
 template <typename K>
@@ -879,8 +887,8 @@ static int launch_tile_either(GemmParams b, GemmParams f, const PrecisionSource&
     return REALB_OK;
 }
 
-// Block tile choices (selector g_tile): 0 = the direct-to-LDS kernel above with the shapes it picks, 16 / 4 / 1 / 5 = with
-// 256- / 128- / 64-row tiles / 64 x 128 tiles only; the register-staged kernel with 64-byte K-steps as 2 = 256x128, 4 waves, two blocks per CU, or 8 = 256x256, 8 waves of 128x64, one block per CU.
+// Block tile choices (selector g_tile): 0 = the direct-to-LDS kernel above with the shapes it picks, 16 / 3 / 4 / 1 / 5 = with
+// 256- / 192- / 128- / 64-row tiles / 64 x 128 tiles only; the register-staged kernel with 64-byte K-steps as 2 = 256x128, 4 waves, two blocks per CU, or 8 = 256x256, 8 waves of 128x64, one block per CU.
 template <bool FP4, bool GATEUP, int WN, int WGN, int MINB>
 static int launch_gemm_geo(GemmParams p, long long max_rows, const Ctx* c, hipStream_t s) {
     using G = Geo<WN, WGN>;
@@ -906,13 +914,13 @@ static int launch_gemm_geo(GemmParams p, long long max_rows, const Ctx* c, hipSt
     return REALB_OK;
 }
 
-static std::atomic<int> g_tile{0};    // 0 = automatic; 2, 8 or 16 forces a kernel (set through realb_set_gemm_tile)
+static std::atomic<int> g_tile{0};    // 0 = automatic; another value forces a kernel (set through realb_set_gemm_tile)
 
 template <bool FP4, bool GATEUP>
 static int launch_gemm(const GemmParams& p, long long max_rows, const Ctx* c, hipStream_t s) {
     const int forced = g_tile.load(std::memory_order_relaxed);
     if (forced == 0 || forced == 16) return launch_tile<FP4, GATEUP, false>(p, max_rows, c, s, forced == 0 ? 0 : 4);
-    if (forced == 4 || forced == 1 || forced == 5) return launch_tile<FP4, GATEUP, false>(p, max_rows, c, s, forced == 4 ? 2 : forced);
+    if (forced == 3 || forced == 4 || forced == 1 || forced == 5) return launch_tile<FP4, GATEUP, false>(p, max_rows, c, s, forced == 4 ? 2 : forced);
     if (forced == 8 && (GATEUP || p.n_out % 256 == 0)) return launch_gemm_geo<FP4, GATEUP, 2, 4, 1>(p, max_rows, c, s);
     return launch_gemm_geo<FP4, GATEUP, 2, 2, 2>(p, max_rows, c, s);
 }
@@ -958,7 +966,7 @@ int launch_layer_down(Ctx* c, const PrecisionSource& prec, const realb_layer_io*
 using namespace realb;
 
 extern "C" int realb_set_gemm_tile(int wn) {
-    REALB_REQUIRE(wn == 0 || wn == 1 || wn == 2 || wn == 4 || wn == 5 || wn == 8 || wn == 16, REALB_EINVAL, "tile selector must be 0, 1, 2, 4, 5, 8 or 16");
+    REALB_REQUIRE(wn == 0 || wn == 1 || wn == 2 || wn == 3 || wn == 4 || wn == 5 || wn == 8 || wn == 16, REALB_EINVAL, "tile selector must be 0, 1, 2, 3, 4, 5, 8 or 16");
     g_tile.store(wn, std::memory_order_relaxed);
     return REALB_OK;
 }

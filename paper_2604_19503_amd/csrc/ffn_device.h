@@ -39,8 +39,8 @@ struct GemmParams {
     int src_shift;
     unsigned long long* start_word;   // host-coherent, or NULL: the kernel's first block writes start_seq there
     int start_seq;
-    int tile_mode;           // direct-to-LDS kernel: 0 = tile shapes chosen on the device, 4 / 2 / 1 = 256- / 128- / 64-row tiles of
-                             //   256 weight rows only, 5 = 64 x 128 tiles only
+    int tile_mode;           // direct-to-LDS kernel: 0 = tile shapes chosen on the device, 4 / 3 / 2 / 1 = 64 times that many rows of
+                             //   256 weight rows, 5 = 64 x 128 tiles only
 };
 
 // Exact division of 0 <= a < 2^31 by a small constant k through one multiplication: with s = ceil(log2 k) and
