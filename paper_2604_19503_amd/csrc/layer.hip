@@ -48,13 +48,15 @@ static void add_tokens(const Ctx* c, const realb_layer_io* io, int threads, Side
                        io->rank * c->n_local, c->n_local, (unsigned)ceil_div(io->T, threads / 64)};
 }
 
-// Makes `s` wait for the pending cross-layer prefetch.  An event that has completed is not waited for: a wait costs the
-// stream microseconds even then, and by the time a call's statistics have arrived the previous call's prefetch has ended.
-static int join_prefetch(Ctx* c, hipStream_t s) {
+// Makes `s` wait for the pending cross-layer prefetch.  may_query: an event that has completed is not waited for -- a wait
+// costs the stream microseconds even then, and by the time a layer call's statistics have arrived the previous call's
+// prefetch has ended.  Only the layer call, which waits for the host anyway, may ask so: the rank call and
+// realb_prefetch_join can be recorded into a graph, where querying an event breaks the recording.
+static int join_prefetch(Ctx* c, hipStream_t s, bool may_query) {
     if (!c->prefetch_pending) return REALB_OK;
-    const hipError_t q = hipEventQuery(c->ev_prefetch);
+    const hipError_t q = may_query ? hipEventQuery(c->ev_prefetch) : hipErrorNotReady;
     if (q != hipSuccess) {
-        (void)hipGetLastError();                          // (not-ready is no error of this call)
+        if (may_query) (void)hipGetLastError();           // (not-ready is no error of this call)
         REALB_HIP(hipStreamWaitEvent(s, c->ev_prefetch, 0));
     }
     c->prefetch_pending = false;
@@ -123,7 +125,7 @@ static int rank_forward_steps(realb_ctx* ctx, realb_layer_io* io, int prec, void
     const bool encode_weights = fp4 && io->overlap != 2 && io->overlap != 4;
     const bool gather = gate_up_gather_supported(c, io->T, fp4);
     if (io->overlap == 4 || prefetch) {                   // weights encoded by the previous call's prefetch, or its buffers reused
-        rc = join_prefetch(c, s);
+        rc = join_prefetch(c, s, false);
         if (rc != REALB_OK) return rc;
     }
     // FP4: the encoding rides along with the index kernels -- W13 beside the counting, tokens and W2 beside the ranking
@@ -248,7 +250,7 @@ static int layer_forward_steps(realb_ctx* ctx, realb_layer_io* io, void* stream)
     // everything the previous call enqueued has run, so the prefetch that filled this call's weights has ended and the
     // buffers of the next one have no reader left -- neither needs an event on the caller's stream.
     rc = wait_for_statistics();
-    if (rc == REALB_OK) rc = join_prefetch(c, s);
+    if (rc == REALB_OK) rc = join_prefetch(c, s, true);
     if (rc != REALB_OK) return rc;
     PrecisionSource known = prec;
     known.fixed = io->prec_host[io->rank];
@@ -263,5 +265,5 @@ extern "C" int realb_layer_forward(realb_ctx* ctx, realb_layer_io* io, void* str
 extern "C" int realb_prefetch_join(realb_ctx* ctx, void* stream) {
     REALB_REQUIRE(ctx != nullptr, REALB_EINVAL, "ctx is NULL");
     Ctx* c = reinterpret_cast<Ctx*>(ctx);
-    return join_prefetch(c, as_stream(stream));
+    return join_prefetch(c, as_stream(stream), false);
 }

@@ -561,6 +561,55 @@ def test_cross_layer_prefetch_pipeline_is_bit_identical(R, reserve):
     ctx.close()
 
 
+@pytest.mark.parametrize("precs", [("FP4", "FP4"), ("BF16", "FP4")])
+def test_rank_call_pipeline_can_be_recorded_into_a_graph(R, precs):
+    """Two rank calls, the first of which encodes the second's weights on the side stream: recorded into one graph and
+    replayed, with other calls of the same context in between, they give what they give eagerly, bit for bit."""
+    from paper_2604_19503_amd.binding import default_config
+    cfg = W.scaled(W.CONFIGS["c2"], T=700, H=512, I=384)
+    rcfg = default_config(cfg.T, cfg.E, cfg.k, cfg.D, cfg.H, cfg.I)
+    ctx = R.Context(rcfg)
+    inp = W.gen_layer(cfg, 23)
+    x = R.bf16_from_bits(inp["x"])
+    lg = torch.from_numpy(inp["logits"]).cuda(); isv = torch.from_numpy(inp["is_vision"]).cuda()
+    ws = [tuple(R.bf16_from_bits(a) for a in W.gen_weights(cfg, 310 + l)) for l in range(2)]
+    bufs = [R.LayerBuffers(rcfg, cfg.T) for _ in range(2)]
+    pair = [R.WeightBuffers(rcfg), R.WeightBuffers(rcfg)]
+    ios = []
+    for l in range(2):
+        ctx.route_stats(lg, isv, bufs[l])
+        io = ctx.make_io(lg, isv, x, ws[l][0], ws[l][1], bufs[l], cfg.rank, overlap=0 if l == 0 else 4)
+        ctx.use_weight_buffers(io, pair[l])
+        if l == 0:
+            ctx.set_prefetch(io, ws[1][0], ws[1][1], pair[1], 8)
+        ios.append(io)
+
+    def both():
+        for l in range(2):
+            ctx.rank_forward(ios[l], getattr(R, precs[l]))
+
+    both()
+    _sync()
+    ref = [b.out.clone() for b in bufs]
+    graph = torch.cuda.CUDAGraph()
+    _say(f"graph of rank calls {precs}")
+    with torch.cuda.graph(graph):
+        both()
+    for _ in range(3):
+        for b in bufs:
+            b.out.fill_(float("nan"))
+        for wb in pair:
+            wb.w13_q.fill_(0xEE)
+        graph.replay()
+        _sync()
+        for l in range(2):
+            assert torch.equal(bufs[l].out.view(torch.int16), ref[l].view(torch.int16)), l
+        both()                                            # the context still works eagerly
+        _sync()
+        assert torch.equal(bufs[1].out.view(torch.int16), ref[1].view(torch.int16))
+    ctx.close()
+
+
 def test_stage_timing_reports_the_stages_of_the_last_call(R, case):
     """realb_stage_timing / realb_stage_ms: seven non-negative stage times whose sum is of the order of the call's
     wall time, in both call forms; an error while timing is off; outputs unchanged by the timing events."""
