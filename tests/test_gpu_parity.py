@@ -129,6 +129,45 @@ def test_route_stats_expert_counts_and_ties(R, E, k, D):
     ctx.close()
 
 
+@pytest.mark.parametrize("T", [1, 15, 16, 17, 63, 65, 4096, 4097, 16385])
+@pytest.mark.parametrize("E,k,D", [(64, 6, 8), (24, 3, 2)])
+def test_layer_routing_at_the_edges_of_its_blocks(R, E, k, D, T):
+    """The layer call's routing and index kernels share the tokens out to blocks of 16 or more by the size of the batch:
+    selection, statistics and row tables at the sizes where that changes or leaves a remainder."""
+    from paper_2604_19503_amd.binding import default_config
+    rng = np.random.default_rng(T * 10 + k)
+    logits = rng.standard_normal((T, E)).astype(np.float32)
+    logits[::3] = np.round(logits[::3] * 2) / 2                   # many exact ties
+    isv_np = (rng.random(T) < 0.6).astype(np.uint8)
+    rcfg = default_config(T, E, k, D, 128, 128)
+    ctx = R.Context(rcfg)
+    n_local = E // D
+    x = torch.zeros((T, 128), dtype=torch.bfloat16, device="cuda")
+    w13 = torch.zeros((n_local, 256, 128), dtype=torch.bfloat16, device="cuda")
+    w2 = torch.zeros((n_local, 128, 128), dtype=torch.bfloat16, device="cuda")
+    ids, w = orouter.topk_route(logits, k)
+    cnt, vis, load, lvis = orouter.route_counts(ids, isv_np, E, D)
+    for rank in {0, D - 1}:
+        for force in (R.BF16, R.FP4):
+            _say(f"routing blocks E={E} T={T} rank={rank} force={force}")
+            b = R.LayerBuffers(rcfg, T)
+            io = ctx.make_io(torch.from_numpy(logits).cuda(), torch.from_numpy(isv_np).cuda(), x, w13, w2, b, rank, force=force, overlap=0)
+            b.row_to_assign.fill_(-7)
+            assert ctx.layer_forward(io) == force
+            _sync()
+            offs, r2a, a2r = operm.permute_indices(ids, rank, n_local)
+            assert same(b.topk_ids.cpu().numpy(), ids)
+            assert np.allclose(b.topk_w.cpu().numpy().astype(np.float64), w, rtol=GATE_W_RTOL, atol=1e-9)
+            assert same(b.expert_cnt.cpu().numpy(), cnt) and same(b.expert_vis.cpu().numpy(), vis)
+            assert same(b.rank_load.cpu().numpy(), load) and same(b.rank_vis.cpu().numpy(), lvis)
+            assert io.ib_global == load.max() * D / (T * k)
+            assert same(b.expert_offsets.cpu().numpy(), offs)
+            assert same(b.row_to_assign.cpu().numpy()[:len(r2a)], r2a)
+            assert bool((b.row_to_assign[len(r2a):] == -7).all())
+            assert same(b.assign_to_row.cpu().numpy().reshape(-1), np.asarray(a2r).reshape(-1))
+    ctx.close()
+
+
 def test_select_precision_from_device_stats(R, case):
     c, b = case.cfg, case.buf
     case.ctx.route_stats(case.logits, case.is_vision, b)
