@@ -65,6 +65,7 @@ int permute_indices(Ctx* c, const int32_t* topk_ids, int T, int rank, long long 
                     int32_t* row_to_assign, int32_t* assign_to_row, const SideJobs& beside_count, const SideJobs& beside_rank, hipStream_t s);
 int route_topk_only(Ctx* c, const float* logits, const uint8_t* is_vision, int T, int32_t* topk_ids, float* topk_w, const SideJobs& jobs,
                     int* per_block, int32_t** rank_part, hipStream_t s);
+bool route_small(Ctx* c, const realb_layer_io* io, int stats_seq, hipStream_t s);
 int route_and_index(Ctx* c, const realb_layer_io* io, int stats_seq, const SideJobs& beside_topk, const SideJobs& beside_finish, hipStream_t s);
 int permute_gather(Ctx* c, const void* x, const int32_t* assign_to_row, int T, int prec, void* x_perm, uint8_t* x_q,
                    uint8_t* x_s, hipStream_t s);

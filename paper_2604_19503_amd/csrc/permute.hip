@@ -375,6 +375,10 @@ int route_and_index(Ctx* c, const realb_layer_io* io, int stats_seq, const SideJ
     REALB_REQUIRE(io->expert_cnt && io->expert_vis && io->rank_load && io->rank_vis, REALB_EINVAL, "NULL argument");
     const int rc = check_permute(c, io->topk_ids, io->T, io->rank, io->max_rows, io->expert_offsets, io->row_to_assign, io->assign_to_row);
     if (rc != REALB_OK) return rc;
+    if (beside_topk.blocks() + beside_finish.blocks() == 0 && route_small(c, io, stats_seq, s)) {
+        REALB_HIP(hipGetLastError());
+        return REALB_OK;
+    }
     FinishArgs p{};
     int32_t* rank_part = nullptr;
     const int n_part = route_topk_only(c, io->logits, io->is_vision, io->T, io->topk_ids, io->topk_w, beside_topk, &p.per_block, &rank_part, s);

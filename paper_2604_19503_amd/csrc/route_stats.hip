@@ -136,22 +136,18 @@ __device__ __forceinline__ int row_min_i(int v) {
 // row holds the EPL = E/16 consecutive experts j*EPL .. j*EPL+EPL-1.  A selection round is the lane's
 // best, the row maximum, and the row minimum of the expert index among the lanes that hold that
 // maximum (lowest index wins ties) -- DPP only, no scalar round trips, the four rows in lock step.
-template <int EPL>
-__global__ void __launch_bounds__(1024, 2) topk_hist_rows_kernel(const float* __restrict__ logits, const uint8_t* __restrict__ is_vision,
-                                                                 int T, int E, int k, int32_t* __restrict__ topk_ids,
-                                                                 float* __restrict__ topk_w, int32_t* __restrict__ hist_part,
-                                                        int n_front, int per_block, int D, int32_t* __restrict__ rank_part, const SideJobs jobs) {
-    if ((int)blockIdx.x >= n_front) return run_side_jobs<kTopkThreads, false>(jobs, blockIdx.x - n_front);
-    extern __shared__ int32_t hist[];                 // [2*E]: counts, vision counts
-    for (int i = threadIdx.x; i < 2 * E; i += blockDim.x) hist[i] = 0;
-    __syncthreads();
+// The block's tokens are t_lo .. t_end-1.  hist (LDS, zeroed): 2*E counters; KEEP: the expert ids also go to kept (LDS).
+template <int EPL, bool KEEP>
+__device__ __forceinline__ void topk_rows(const float* __restrict__ logits, const uint8_t* __restrict__ is_vision, int t_lo, int t_end,
+                                          int E, int k, int32_t* __restrict__ topk_ids, float* __restrict__ topk_w, int32_t* hist,
+                                          int32_t* kept) {
     const int lane = threadIdx.x & 63;
     const int j = lane & 15, r = lane >> 4;
     const int wave = threadIdx.x >> 6;
     const int waves_per_block = blockDim.x >> 6;
     const float NEG = -INFINITY;
-    const int stride = waves_per_block * 4, t_end = min(T, ((int)blockIdx.x + 1) * per_block);
-    int t = blockIdx.x * per_block + wave * 4 + r;
+    const int stride = waves_per_block * 4;
+    int t = t_lo + wave * 4 + r;
     float nx[EPL];
     int nx_vision = 0;
     auto fetch = [&](int tok) __attribute__((always_inline)) {
@@ -191,14 +187,87 @@ __global__ void __launch_bounds__(1024, 2) topk_hist_rows_kernel(const float* __
         const float sum = row_sum(e);
         if (live && j < k) {
             topk_ids[(size_t)t * k + j] = my_id;
+            if (KEEP) kept[(t - t_lo) * k + j] = my_id;
             topk_w[(size_t)t * k + j] = e / sum;
             atomicAdd(&hist[my_id], 1);
             if (vision) atomicAdd(&hist[E + my_id], 1);
         }
     }
+}
+
+template <int EPL>
+__global__ void __launch_bounds__(1024, 2) topk_hist_rows_kernel(const float* __restrict__ logits, const uint8_t* __restrict__ is_vision,
+                                                                 int T, int E, int k, int32_t* __restrict__ topk_ids,
+                                                                 float* __restrict__ topk_w, int32_t* __restrict__ hist_part,
+                                                        int n_front, int per_block, int D, int32_t* __restrict__ rank_part, const SideJobs jobs) {
+    if ((int)blockIdx.x >= n_front) return run_side_jobs<kTopkThreads, false>(jobs, blockIdx.x - n_front);
+    extern __shared__ int32_t hist[];                 // [2*E]: counts, vision counts
+    for (int i = threadIdx.x; i < 2 * E; i += blockDim.x) hist[i] = 0;
+    __syncthreads();
+    topk_rows<EPL, false>(logits, is_vision, blockIdx.x * per_block, min(T, ((int)blockIdx.x + 1) * per_block), E, k, topk_ids, topk_w,
+                          hist, nullptr);
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * E; i += blockDim.x) hist_part[(size_t)blockIdx.x * 2 * E + i] = hist[i];
     store_rank_part(hist, E, D, rank_part);
+}
+
+// Routing and row indices of a decode batch in one launch of one block: with at most 64 tokens every wave has one set of four
+// tokens and at most 64 assignments, the histogram is whole in LDS, and nothing has to pass from block to block.  Bound by
+// latency: a second kernel costs as much as the work in either.
+constexpr int kSmallTokens = 64;
+struct RouteSmallArgs {
+    const float* logits;
+    const uint8_t* is_vision;
+    int T, E, k, D, lo, n_local;
+    int32_t* topk_ids;
+    float* topk_w;
+    int32_t *expert_cnt, *expert_vis, *rank_load, *rank_vis;
+    unsigned long long* stats_words;
+    int stats_seq;
+    int32_t *expert_offsets, *row_to_assign, *assign_to_row;
+};
+template <int EPL>
+__global__ void __launch_bounds__(1024) route_small_kernel(const RouteSmallArgs p) {
+    __shared__ int32_t hist[2 * 128], ids[kSmallTokens * 16], wcnt[kSmallTokens / 4][64];
+    for (int i = threadIdx.x; i < 2 * p.E; i += blockDim.x) hist[i] = 0;
+    __syncthreads();
+    topk_rows<EPL, true>(p.logits, p.is_vision, 0, p.T, p.E, p.k, p.topk_ids, p.topk_w, hist, ids);
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * p.D; i += blockDim.x) {     // rank loads, then vision loads (E = D * n_local)
+        int sum = 0;
+        for (int e = 0; e < p.n_local; ++e) sum += hist[i * p.n_local + e];
+        *(i < p.D ? p.rank_load + i : p.rank_vis + (i - p.D)) = sum;
+        __hip_atomic_store(p.stats_words + i, (unsigned long long)(uint32_t)p.stats_seq << 32 | (uint32_t)sum, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    for (int i = threadIdx.x; i < 2 * p.E; i += blockDim.x) *(i < p.E ? p.expert_cnt + i : p.expert_vis + (i - p.E)) = hist[i];
+    // rank of each assignment: position in its wave, assignments of the waves before, experts before
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int a = wave * 64 + lane, A = p.T * p.k;                // (k <= 16: the waves' 4 tokens cover all assignments)
+    const int le = a < A ? ids[a] - p.lo : -1;
+    const bool mine = le >= 0 && le < p.n_local;
+    const unsigned long long lt_mask = (1ull << lane) - 1ull;
+    int cnt = 0, in_wave = 0;
+    for (int e = 0; e < p.n_local; ++e) {
+        const unsigned long long m = __ballot(le == e);
+        if (lane == e) cnt = __popcll(m);
+        if (le == e) in_wave = __popcll(m & lt_mask);
+    }
+    wcnt[wave][lane] = cnt;
+    __syncthreads();
+    const int tot = lane < p.n_local ? hist[p.lo + lane] : 0;
+    const int incl = wave_inclusive_scan(tot);
+    if (wave == 0) {
+        if (lane < p.n_local) p.expert_offsets[lane] = incl - tot;
+        if (lane == p.n_local - 1) p.expert_offsets[p.n_local] = incl;
+    }
+    int base = incl - tot;
+    for (int w = 0; w < wave; ++w) base += wcnt[w][lane];
+    const int row = __shfl(base, mine ? le : 0) + in_wave;
+    if (a < A) {
+        p.assign_to_row[a] = mine ? row : -1;
+        if (mine) p.row_to_assign[row] = a;
+    }
 }
 
 __global__ void __launch_bounds__(1024) hist_reduce_kernel(const int32_t* __restrict__ hist_part, int n_part, int E, int D,
@@ -263,6 +332,30 @@ static int launch_route_stats(int num_cus, int max_blocks, int32_t* hist_part, c
                        expert_cnt, expert_vis, rank_load, rank_vis);
     REALB_HIP(hipGetLastError());
     return REALB_OK;
+}
+
+// Routing and row indices of a layer call in one launch, for batches that one block handles; false: nothing was launched.
+// E is a multiple of 16 up to 128 (four tokens per wave), T at most 64; beyond, one block would take its tokens in turns and the
+// two launches win.  Whole BF16 layers, two launches -> one: 1 / 8 / 64 tokens of 64 experts 32.5 / 42.8 / 46.4 -> 30.6 / 40.6 /
+// 45.4 us, 16 / 64 tokens of 128 experts 47.6 / 50.9 -> 45.2 / 50.2 us.
+bool route_small(Ctx* c, const realb_layer_io* io, int stats_seq, hipStream_t s) {
+    const int E = c->cfg.E, T = io->T;
+    if (T <= 0 || T > kSmallTokens || E > 128 || E % 16 != 0) return false;
+    const RouteSmallArgs p{io->logits, io->is_vision, T, E, c->cfg.k, c->cfg.D, io->rank * c->n_local, c->n_local, io->topk_ids, io->topk_w,
+                           io->expert_cnt, io->expert_vis, io->rank_load, io->rank_vis, c->stats_words, stats_seq,
+                           io->expert_offsets, io->row_to_assign, io->assign_to_row};
+    const dim3 threads(64 * ceil_div(T, 4));
+    switch (E / 16) {
+        case 1: hipLaunchKernelGGL(route_small_kernel<1>, dim3(1), threads, 0, s, p); break;
+        case 2: hipLaunchKernelGGL(route_small_kernel<2>, dim3(1), threads, 0, s, p); break;
+        case 3: hipLaunchKernelGGL(route_small_kernel<3>, dim3(1), threads, 0, s, p); break;
+        case 4: hipLaunchKernelGGL(route_small_kernel<4>, dim3(1), threads, 0, s, p); break;
+        case 5: hipLaunchKernelGGL(route_small_kernel<5>, dim3(1), threads, 0, s, p); break;
+        case 6: hipLaunchKernelGGL(route_small_kernel<6>, dim3(1), threads, 0, s, p); break;
+        case 7: hipLaunchKernelGGL(route_small_kernel<7>, dim3(1), threads, 0, s, p); break;
+        default: hipLaunchKernelGGL(route_small_kernel<8>, dim3(1), threads, 0, s, p); break;
+    }
+    return true;
 }
 
 // Routing for the layer call: only the top-k + histogram kernel; what follows it is route_finish_kernel (permute.hip).  The
