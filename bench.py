@@ -711,7 +711,7 @@ def main():
     gu_ms, dn_ms = layer_stages["gate_up"], layer_stages["down"]
     gu_rate = 4.0 * rows * H * I / (gu_ms * 1e-3) / 1e12
     dn_rate = 2.0 * rows * H * I / (dn_ms * 1e-3) / 1e12
-    kernel = f"ffn_gemm256_kernel<{str(fp4).lower()}, true, true>"
+    kernel = f"ffn_tile_kernel<{str(fp4).lower()}, true, true>"
     roofline = {"kernel": kernel, "what": "gate/up grouped GEMM + SwiGLU as launched by realb_layer_forward (activation rows fetched through row_to_assign)",
                 "bound": "mfma", "achieved": gu_rate, "peak": peak, "unit": "TFLOP/s", "frac": gu_rate / peak, "traffic": None, "ms": gu_ms}
     traffic_file = os.path.join(ROOT, "profiles", "traffic.json")      # HBM bytes per launch from the committed counter runs, keyed by kernel

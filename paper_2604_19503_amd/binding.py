@@ -15,7 +15,7 @@ EXPORTS = [
     "realb_default_config", "realb_create", "realb_destroy", "realb_last_error", "realb_get_M", "realb_set_M",
     "realb_route_stats", "realb_select_precision", "realb_select_precision_host", "realb_quantize_experts_fp4",
     "realb_quantize_rows_fp4", "realb_permute", "realb_grouped_moe_ffn", "realb_grouped_moe_ffn_gate_up",
-    "realb_grouped_moe_ffn_down", "realb_set_gemm_tile", "realb_combine", "realb_layer_forward", "realb_rank_forward",
+    "realb_grouped_moe_ffn_down", "realb_set_gemm_tile", "realb_set_gemm_tile_shape", "realb_combine", "realb_layer_forward", "realb_rank_forward",
     "realb_quantize_rows_nvfp4", "realb_amax_bf16", "realb_route_stats_static",
     "realb_workspace_bytes", "realb_scale_offset", "realb_scale_index_map", "realb_prefetch_join", "realb_stage_timing", "realb_stage_ms",
 ]
@@ -75,6 +75,7 @@ def load_library() -> C.CDLL:
     lib.realb_scale_index_map.argtypes = [C.c_longlong, C.c_int, C.c_void_p]
     lib.realb_create.argtypes = [C.POINTER(Config), C.POINTER(C.c_void_p)]
     lib.realb_destroy.argtypes = [C.c_void_p]
+    lib.realb_set_gemm_tile_shape.argtypes = [C.c_void_p, C.c_int]
     vp = C.c_void_p
     lib.realb_route_stats.argtypes = [vp, vp, vp, C.c_int, vp, vp, vp, vp, vp, vp, vp]
     lib.realb_route_stats_static.argtypes = [vp, vp, C.c_int, C.c_int, C.c_int, C.c_int, vp, vp, vp, vp, vp, vp, vp]
@@ -350,6 +351,9 @@ class Context:
         """Points a layer call's FP4 weight buffers at wbuf (instead of the LayerBuffers' own)."""
         io.w13_q, io.w13_s, io.w2_q, io.w2_s = (t.data_ptr() for t in (wbuf.w13_q, wbuf.w13_s, wbuf.w2_q, wbuf.w2_s))
         io._keep_w = wbuf
+
+    def set_gemm_tile_shape(self, shape: int):
+        _check(self.lib.realb_set_gemm_tile_shape(self._h, int(shape)))
 
     STAGES = ("route_stats", "permute_indices", "decision_and_encode", "gather", "gate_up", "down", "combine")
 

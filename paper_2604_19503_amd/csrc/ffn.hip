@@ -887,8 +887,9 @@ static int launch_tile_either(GemmParams b, GemmParams f, const PrecisionSource&
     return REALB_OK;
 }
 
-// Block tile choices (selector g_tile): 0 = the direct-to-LDS kernel above with the shapes it picks, 16 / 3 / 4 / 1 / 5 = with
-// 256- / 192- / 128- / 64-row tiles / 64 x 128 tiles only; the register-staged kernel with 64-byte K-steps as 2 = 256x128, 4 waves, two blocks per CU, or 8 = 256x256, 8 waves of 128x64, one block per CU.
+// Block tile choices (selector g_tile): 0 = the direct-to-LDS kernel above with the shapes it picks (or with the one that
+// the context names, see realb_set_gemm_tile_shape), 16 = with 256-row tiles only; the register-staged kernel with 64-byte K-steps as 2 = 256x128, 4 waves,
+// two blocks per CU, or 8 = 256x256, 8 waves of 128x64, one block per CU.
 template <bool FP4, bool GATEUP, int WN, int WGN, int MINB>
 static int launch_gemm_geo(GemmParams p, long long max_rows, const Ctx* c, hipStream_t s) {
     using G = Geo<WN, WGN>;
@@ -919,8 +920,8 @@ static std::atomic<int> g_tile{0};    // 0 = automatic; another value forces a k
 template <bool FP4, bool GATEUP>
 static int launch_gemm(const GemmParams& p, long long max_rows, const Ctx* c, hipStream_t s) {
     const int forced = g_tile.load(std::memory_order_relaxed);
-    if (forced == 0 || forced == 16) return launch_tile<FP4, GATEUP, false>(p, max_rows, c, s, forced == 0 ? 0 : 4);
-    if (forced == 3 || forced == 4 || forced == 1 || forced == 5) return launch_tile<FP4, GATEUP, false>(p, max_rows, c, s, forced == 4 ? 2 : forced);
+    if (forced == 0 || forced == 16)
+        return launch_tile<FP4, GATEUP, false>(p, max_rows, c, s, forced == 16 ? 4 : c->gemm_shape);
     if (forced == 8 && (GATEUP || p.n_out % 256 == 0)) return launch_gemm_geo<FP4, GATEUP, 2, 4, 1>(p, max_rows, c, s);
     return launch_gemm_geo<FP4, GATEUP, 2, 2, 2>(p, max_rows, c, s);
 }
@@ -966,8 +967,15 @@ int launch_layer_down(Ctx* c, const PrecisionSource& prec, const realb_layer_io*
 using namespace realb;
 
 extern "C" int realb_set_gemm_tile(int wn) {
-    REALB_REQUIRE(wn == 0 || wn == 1 || wn == 2 || wn == 3 || wn == 4 || wn == 5 || wn == 8 || wn == 16, REALB_EINVAL, "tile selector must be 0, 1, 2, 3, 4, 5, 8 or 16");
+    REALB_REQUIRE(wn == 0 || wn == 2 || wn == 8 || wn == 16, REALB_EINVAL, "tile selector must be 0, 2, 8 or 16");
     g_tile.store(wn, std::memory_order_relaxed);
+    return REALB_OK;
+}
+
+extern "C" int realb_set_gemm_tile_shape(realb_ctx* ctx, int shape) {
+    REALB_REQUIRE(ctx != nullptr, REALB_EINVAL, "ctx is NULL");
+    REALB_REQUIRE(shape == 0 || shape == 1 || shape == 2 || shape == 3 || shape == 5, REALB_EINVAL, "tile shape must be 0, 1, 2, 3 or 5");
+    reinterpret_cast<Ctx*>(ctx)->gemm_shape = shape;
     return REALB_OK;
 }
 

@@ -164,3 +164,10 @@ def test_gemm_tile_selector_accepts_only_its_values():
     for v in (2, 8, 16, 0):
         assert lib.realb_set_gemm_tile(v) == 0
     assert lib.realb_set_gemm_tile(3) == -1
+
+
+def test_gemm_tile_selector_refuses_the_shape_values():
+    lib = R.load_library()
+    for v in (-1, 1, 3, 4, 5, 32):
+        assert lib.realb_set_gemm_tile(v) == -1
+    assert lib.realb_set_gemm_tile_shape(None, 1) == -1

@@ -391,21 +391,23 @@ def test_tile_shapes_give_the_same_rows(R, H, I, segments):
     ctx.quantize_experts_fp4(w13, w2, b)
     for prec in (R.BF16, R.FP4):
         ref = None
-        for tile in (2, 0, 16, 3, 4, 1, 5):
-            _say(f"tile shapes H={H} I={I} prec={prec} tile={tile}")
+        for tile, shape in ((2, 0), (0, 0), (16, 0), (0, 3), (0, 2), (0, 1), (0, 5)):
+            _say(f"tile shapes H={H} I={I} prec={prec} tile={tile} shape={shape}")
             b.y_rows.fill_(float("nan"))
             try:
                 set_gemm_tile(tile)
+                ctx.set_gemm_tile_shape(shape)
                 ctx.grouped_moe_ffn(prec, w13, w2, b)
                 _sync()
             finally:
                 set_gemm_tile(0)
+                ctx.set_gemm_tile_shape(0)
             got = b.y_rows.view(torch.int16).clone()
             if ref is None:
                 ref = got
                 assert bool(torch.isfinite(b.y_rows[:rows].float()).all()) and bool(torch.isnan(b.y_rows[rows:].float()).all())
-            if tile != 0:
-                assert torch.equal(got, ref), tile
+            if tile != 0 or shape != 0:
+                assert torch.equal(got, ref), (tile, shape)
             elif rows:
                 a, r = got[:rows].view(torch.bfloat16).float(), ref[:rows].view(torch.bfloat16).float()
                 assert float((a - r).norm() / r.norm()) <= 5e-4 and bool(torch.isnan(b.y_rows[rows:].float()).all())
