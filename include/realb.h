@@ -217,13 +217,13 @@ int realb_grouped_moe_ffn_down(realb_ctx* ctx, int prec, const int32_t* expert_o
  * shapes picked on the device from the expert segments), 16 = persistent 256x256 tiles fed by
  * direct-to-LDS loads, 2 = register-staged 256x128 tiles with two blocks per CU, 8 = register-staged
  * 256x256 tiles with one block per CU (where the output width is a multiple of its tile, else 2).
- * Process-wide; outputs are bit-identical for every choice but 0, which may sum the K-steps of some
- * shapes in another order (FP32 rounding).  REALB_EINVAL for any other value. */
+ * Process-wide; outputs are bit-identical for every choice (the accumulation order along K does not
+ * change).  REALB_EINVAL for any other value. */
 int realb_set_gemm_tile(int wn);
 
 /* Tuning hook for this context's step-by-step GEMM entry points where the selector above is 0: 0 = shapes picked on the
  * device (default), 1 / 2 / 3 = 64x256, 128x256 or 192x256 tiles only, 5 = 64x128 tiles only (needs four K-steps, else
- * 64x256).  The layer and rank calls always pick.  Outputs of all fixed shapes are
+ * 64x256).  The layer and rank calls always pick.  Outputs of all shapes are
  * bit-identical.  REALB_EINVAL for any other value. */
 int realb_set_gemm_tile_shape(realb_ctx* ctx, int shape);
 

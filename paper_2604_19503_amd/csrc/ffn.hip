@@ -317,8 +317,8 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 // Measured, BF16, weights from HBM, gate/up + down us: 24 tokens (61 rows) 49.9 + 27.8 -> 19.6 + 11.6 (138 MB: 4.4 TB/s);
 // 192 tokens 50.9 + 28.2 -> 22.5 + 13.2; 1 token 19 + 14 with 64 x 256 tiles -> 13.3 + 10.2; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.  A split of the contraction over the
 // waves of a block with operands straight in registers (no LDS) measured 34 + 18 at 24 tokens and was dropped.
-// The accumulation order along K is the same for every shape and that of the other kernel, so results are bit-identical --
-// except where a shape that the kernel chooses itself starts at another K-step (see first_step).
+// The accumulation order along K is the same for every shape and that of the other kernel, so results are bit-identical: a
+// row's result does not depend on the batch it is in.
 constexpr int KB = 128;                    // bytes of each operand row per K-step
 // Geometry of a block tile: 64*MT activation rows x TW weight rows, 8 waves.  TW = 256: a 2 x 4 grid of waves of 32*MT x 64
 // each.  TW = 128 and 64 (MT = 1 only): waves 0..3 (0..1) are that grid's first two columns (first column), the others only
@@ -428,21 +428,6 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     const uint8_t* b_tile = nullptr;
 
     TileInfo ti = decode(tile);
-    // The K-step a tile starts at (it then wraps around).  Normally 0, the order every kernel shares.  Chosen shapes rotate it
-    //   - FP4 down with streamed output: by column tile, so that the blocks that work on the column tiles of one row tile at the same time ask for
-    //     different parts of its rows and find the others' in L2, instead of all waiting for the same lines of a tensor that
-    //     large outputs have pushed out to HBM (65536 tokens: 350 -> 293 us; where the output stays in the caches there is nothing
-    //     to gain, and 36 183 rows lost 0.5 us);
-    //   - BF16 with narrow tiles: by column tile and expert, because a block reads 128-byte columns of its weight rows and
-    //     with rows of 4 KB all blocks in step hit the same HBM channels (4.1-4.7 TB/s streaming so, 6.0 TB/s rotated; 24
-    //     tokens: layer 45.9 -> 44.5 us).
-    // Only the order of the FP32 sums changes.
-    constexpr bool ROTATE = FP4 ? !GATEUP : TW < 256;
-    const bool rotate = ROTATE && p.tile_mode == 0 && (!FP4 || nt_out);
-    auto first_step = [&](const TileInfo& t) __attribute__((always_inline)) {
-        if (!rotate) return 0;
-        return (int)((unsigned)((t.n0 >> (FP4 ? 8 : 7)) * (FP4 ? 5 : 1) + t.e) % (unsigned)nks);
-    };
     // GATHER: the row_to_assign entries of a tile's rows are brought into LDS one tile ahead (a wave fetches the
     // entries of its own rows with one direct-to-LDS transfer and later reads back only what it fetched), so
     // that switching tiles never waits for global memory: a register load at the switch would stall the producer
@@ -511,17 +496,14 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
     // ---- producer position: the K-step it fetches next (pk of tile ptile).  Past the block's last tile
     //      it keeps refetching that tile's steps, which nobody reads.
-    int ptile = tile, pk = first_step(ti), pn = 0;        // pk: K-step, pn: how many of the tile's have gone out
+    int ptile = tile, pk = 0;
     auto advance = [&]() __attribute__((always_inline)) {
-        if (++pk == nks) pk = 0;
-        if (++pn == nks) {
-            pn = 0;
+        if (++pk == nks) {
+            pk = 0;
             if (ptile + nslots < tile_hi) {
                 ptile += nslots;
                 if constexpr (GATHER) tokbuf ^= 1;                     // fetched while the previous tile was being produced
-                const TileInfo t = decode(ptile);
-                setup_src(t);
-                pk = first_step(t);
+                setup_src(decode(ptile));
                 if constexpr (GATHER) {
                     if (ptile + nslots < tile_hi) fetch_tokens(decode(ptile + nslots), tokbuf ^ 1);
                 }
@@ -576,7 +558,6 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    int kc = first_step(ti);                              // K-step being multiplied
     int cur_row0 = ti.row0, cur_rows = ti.seg_hi - ti.row0, cur_n0 = ti.n0;
 
     // Ends a tile: epilogue, accumulators back to zero, the block's next tile; false if there is none.
@@ -595,7 +576,6 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         ti = decode(tile);
         cur_row0 = ti.row0; cur_rows = ti.seg_hi - ti.row0; cur_n0 = ti.n0;
         ks = 0;
-        kc = first_step(ti);
         return true;
     };
 
@@ -624,7 +604,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         read_step(0, 0);
         auto step = [&](int set) __attribute__((always_inline)) {
             const bool last = ks == nks - 1;
-            const bool full = !(tail_half && kc == nks - 1);
+            const bool full = !(tail_half && last);
             // the next step has landed, this wave's reads of the current stage are done: its transfers may be replaced
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 2) * OPS) : "memory");
             left = stg;
@@ -653,7 +633,6 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
                 __builtin_amdgcn_sched_barrier(0);
             }
             ++ks;
-            if (++kc == nks) kc = 0;
             return !last || finish_tile();
         };
         while (step(0) && step(1)) {}
@@ -715,7 +694,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
     while (true) {
         const bool last = ks == nks - 1;
-        const bool full = !(tail_half && kc == nks - 1);           // all four K-slices present
+        const bool full = !(tail_half && last);                    // all four K-slices present
         const uint8_t* st = smem + stg * G::STAGE;
 
         // MFMAs of slice s out of fragment slot s&1.  PRODUCE 1: after each row tile's MFMAs one weight
@@ -768,7 +747,6 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         take_scales();
 
         ++ks;
-        if (++kc == nks) kc = 0;
         if (last && !finish_tile()) break;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no transfer may still be writing this block's LDS when it ends
