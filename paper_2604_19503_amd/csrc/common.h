@@ -39,6 +39,7 @@ struct Ctx {
     hipEvent_t ev_fork;    // orders a rank call's prefetch behind the work before its GEMMs
     hipEvent_t ev_prefetch;   // end of the last cross-layer prefetch on the side stream
     bool prefetch_pending;    // ev_prefetch has been recorded and not yet been waited for by a caller's stream
+    unsigned prefetches;      // prefetches issued so far
     int gemm_shape;           // tile shape of the step-by-step GEMMs, GemmParams::tile_mode (realb_set_gemm_tile_shape)
     int gemm_reserve;         // compute units the grouped GEMMs' persistent grids leave free (set around a prefetching call)
     // optional per-stage timing of the layer calls (realb_stage_timing): events recorded on the caller's stream

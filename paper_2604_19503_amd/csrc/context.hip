@@ -174,7 +174,7 @@ int realb_create(const realb_config* cfg, realb_ctx** out) {
     c->cfg = *cfg;
     c->n_local = cfg->E / cfg->D;
     c->M = cfg->M_init;
-    c->wave_cnt = nullptr; c->group_cnt = nullptr; c->hist_part = nullptr; c->stats_host = nullptr; c->stats_words = nullptr; c->side = nullptr; c->ev_fork = nullptr; c->stats_seq = 0; c->start_seq = 0; c->start_word = nullptr; c->ev_prefetch = nullptr; c->prefetch_pending = false; c->gemm_reserve = 0; c->gemm_shape = 0; c->stage_timing = false; c->stage_valid = false;
+    c->wave_cnt = nullptr; c->group_cnt = nullptr; c->hist_part = nullptr; c->stats_host = nullptr; c->stats_words = nullptr; c->side = nullptr; c->ev_fork = nullptr; c->stats_seq = 0; c->start_seq = 0; c->start_word = nullptr; c->ev_prefetch = nullptr; c->prefetch_pending = false; c->prefetches = 0; c->gemm_reserve = 0; c->gemm_shape = 0; c->stage_timing = false; c->stage_valid = false;
     for (auto& ev : c->stage_ev) ev = nullptr;
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&c->num_cus, hipDeviceAttributeMultiprocessorCount, c->device);

@@ -68,6 +68,7 @@ static int join_prefetch(Ctx* c, hipStream_t s, bool may_query) {
 static int issue_prefetch(Ctx* c, const realb_layer_io* io) {
     const int rc = launch_quantize_flat(io->next_w13, (long long)c->n_local * 2 * c->cfg.I, c->cfg.H, io->next_w13_q, io->next_w13_s,
                                         io->next_w2, (long long)c->n_local * c->cfg.H, c->cfg.I, io->next_w2_q, io->next_w2_s, c->side);
+    ++c->prefetches;
     REALB_HIP(hipEventRecord(c->ev_prefetch, c->side));
     c->prefetch_pending = true;
     return rc;
@@ -179,18 +180,22 @@ static int rank_forward_steps(realb_ctx* ctx, realb_layer_io* io, int prec, void
     return REALB_OK;
 }
 
-// If a step fails while a prefetch is in flight on the side stream, the caller's stream is still made to wait for it, so
-// that the caller may free or reuse the buffers after its stream has drained, whatever the call returned.
-static int joined_on_error(Ctx* c, int rc, void* stream) {
-    if (rc != REALB_OK && c && c->prefetch_pending) {
-        (void)hipStreamWaitEvent(as_stream(stream), c->ev_prefetch, 0);
+// Runs the steps of a call; if one of them fails after the call has issued its prefetch, the caller's stream is still made to
+// wait for it, so that the caller may free or reuse the buffers after its stream has drained, whatever the call returned.  An
+// earlier call's prefetch is left to the call that will consume it: that may be on another stream than a call that is refused.
+template <typename F>
+static int joined_on_error(realb_ctx* ctx, void* stream, const F& steps) {
+    Ctx* c = reinterpret_cast<Ctx*>(ctx);
+    const unsigned issued_before = c ? c->prefetches : 0;
+    const int rc = steps();
+    if (rc != REALB_OK && c && c->prefetches != issued_before && c->prefetch_pending &&
+        hipStreamWaitEvent(as_stream(stream), c->ev_prefetch, 0) == hipSuccess)
         c->prefetch_pending = false;
-    }
     return rc;
 }
 
 extern "C" int realb_rank_forward(realb_ctx* ctx, realb_layer_io* io, int prec, void* stream) {
-    return joined_on_error(reinterpret_cast<Ctx*>(ctx), rank_forward_steps(ctx, io, prec, stream, false), stream);
+    return joined_on_error(ctx, stream, [&] { return rank_forward_steps(ctx, io, prec, stream, false); });
 }
 
 static int layer_forward_steps(realb_ctx* ctx, realb_layer_io* io, void* stream) {
@@ -259,7 +264,7 @@ static int layer_forward_steps(realb_ctx* ctx, realb_layer_io* io, void* stream)
 
 extern "C" int realb_layer_forward(realb_ctx* ctx, realb_layer_io* io, void* stream) {
     REALB_REQUIRE(ctx && io, REALB_EINVAL, "NULL argument");
-    return joined_on_error(reinterpret_cast<Ctx*>(ctx), layer_forward_steps(ctx, io, stream), stream);
+    return joined_on_error(ctx, stream, [&] { return layer_forward_steps(ctx, io, stream); });
 }
 
 extern "C" int realb_prefetch_join(realb_ctx* ctx, void* stream) {

@@ -1,0 +1,145 @@
+"""CPU tests of what the library's host side enqueues and in which order: the library runs in a child process against
+stand-ins for the HIP runtime (hip_calls.c) that write its launches, event records and event waits down and run no kernel.
+A layer call's statistics never arrive there, so it ends in an error after its launches; rank calls run to their end."""
+import ctypes as C
+import json
+import os
+import re
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+EINVAL = -1
+A, B = 0xA0000, 0xB0000                                  # two caller's streams
+
+
+# ------------------------------------------------------------------------------------------ the child process
+class Host:
+    """The library behind the stand-ins; every tensor is an address that nobody reads."""
+
+    def __init__(self, stub, T=512, E=64, k=6, D=8, H=256, I=128):
+        self.stub = C.CDLL(stub, mode=C.RTLD_GLOBAL)
+        self.stub.calls_log.restype = C.c_char_p
+        self.lib = C.CDLL(os.path.join(ROOT, "paper_2604_19503_amd", "librealb.so"))
+        sys.path.insert(0, ROOT)
+        from paper_2604_19503_amd import binding
+        self.b = binding
+        vp = C.c_void_p
+        self.lib.realb_layer_forward.argtypes = [vp, vp, vp]
+        self.lib.realb_rank_forward.argtypes = [vp, vp, C.c_int, vp]
+        self.lib.realb_prefetch_join.argtypes = [vp, vp]
+        self.lib.realb_combine.argtypes = [vp, vp, vp, vp, C.c_int, vp, vp]
+        self.cfg = binding.default_config(T, E, k, D, H, I)
+        self.ctx = vp()
+        assert self.lib.realb_create(C.byref(self.cfg), C.byref(self.ctx)) == 0
+        self.addr = 0x10000000
+
+    def new(self):
+        self.addr += 0x100000
+        return self.addr
+
+    def io(self, overlap, force=-1, fp4=True, prefetch=False, T=None):
+        io = self.b.LayerIO()
+        for name, kind in io._fields_:
+            if kind is C.c_void_p and not name.startswith("next_"):
+                setattr(io, name, self.new())
+        if not fp4:
+            io.w13_q = io.w13_s = io.w2_q = io.w2_s = None
+        if prefetch:
+            for name in ("next_w13", "next_w2", "next_w13_q", "next_w13_s", "next_w2_q", "next_w2_s"):
+                setattr(io, name, self.new())
+        io.T = self.cfg.T_max if T is None else T
+        io.rank, io.force, io.overlap = 0, force, overlap
+        io.max_rows = io.T * min(self.cfg.k, self.cfg.E // self.cfg.D)
+        return io
+
+    def calls(self):
+        """(return value, calls) of the last step: launches as ("launch", kernel, threads, stream), events as (what, event, stream)."""
+        out = []
+        for line in self.stub.calls_log().decode().splitlines():
+            m = re.match(r"launch (\S+) grid (\d+) block (\d+) stream (\S+)", line)
+            if m:
+                out.append(["launch", m[1], int(m[2]) * int(m[3]), _num(m[4])])
+            else:
+                m = re.match(r"(record|wait) event (\S+) stream (\S+)", line)
+                out.append([m[1], _num(m[2]), _num(m[3])])
+        self.stub.calls_clear()
+        return out
+
+    def layer(self, io, stream):
+        return self.lib.realb_layer_forward(self.ctx, C.byref(io), stream), self.calls()
+
+    def rank(self, io, prec, stream):
+        return self.lib.realb_rank_forward(self.ctx, C.byref(io), prec, stream), self.calls()
+
+    def pending_prefetch(self, stream):
+        """A rank call that leaves a prefetch pending; returns the event that marks its end."""
+        io = self.io(0, prefetch=True)
+        rc, calls = self.rank(io, 1, stream)
+        assert rc == 0
+        return [c for c in calls if c[0] == "record"][-1][1]
+
+
+def _num(text):
+    return 0 if text == "(nil)" else int(text, 16)
+
+
+def refused_call(stub):
+    """A refused call enqueues nothing and leaves a pending prefetch to the call that will consume it."""
+    h = Host(stub)
+    out = []
+    for how in ("layer", "rank", "force"):
+        ev = h.pending_prefetch(A)
+        bad = h.io(4, force=7 if how == "force" else 1)
+        if how != "force":
+            bad.max_rows = 1
+        rc, calls = h.rank(bad, 1, B) if how == "rank" else h.layer(bad, B)
+        rc2, used = h.rank(h.io(4), 1, A)
+        first = next(i for i, c in enumerate(used) if c[0] == "launch")
+        out.append([rc, calls, rc2, ["wait", ev, A] in used[:first]])
+    return out
+
+
+def call_that_fails_behind_its_prefetch(stub):
+    """Its own stream waits for the prefetch, so that the caller may free the buffers; nobody has to wait again."""
+    h = Host(stub)
+    h.stub.calls_fail(b"combine_kernel")
+    rc, calls = h.rank(h.io(0, prefetch=True), 1, A)
+    h.stub.calls_fail(b"")
+    ev = [c for c in calls if c[0] == "record"][-1][1]
+    rc2, used = h.rank(h.io(4), 1, A)
+    return [rc, calls[-1] == ["wait", ev, A], rc2, [c for c in used if c[0] != "launch"]]
+
+
+# ------------------------------------------------------------------------------------------ the tests
+@pytest.fixture(scope="session")
+def stub(tmp_path_factory):
+    path = str(tmp_path_factory.mktemp("hip_calls") / "libhip_calls.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-o", path, os.path.join(ROOT, "tests", "hip_calls.c")], check=True)
+    return path
+
+
+def _run(stub, what, *args):
+    res = subprocess.run([sys.executable, os.path.abspath(__file__), stub, what, json.dumps(args)], capture_output=True, text=True, timeout=300)
+    assert res.returncode == 0, res.stderr[-2000:]
+    return json.loads(res.stdout.splitlines()[-1])
+
+
+def test_refused_call_leaves_a_pending_prefetch_alone(stub):
+    """The refused call is on another stream than the pipeline's: were the prefetch marked as waited for there, the consuming
+    call would read half-encoded weights."""
+    for rc, enqueued, rc2, waits in _run(stub, "refused_call"):
+        assert rc == EINVAL and enqueued == []
+        assert rc2 == 0 and waits
+
+
+def test_call_that_fails_behind_its_prefetch_waits_for_it(stub):
+    rc, waited, rc2, events = _run(stub, "call_that_fails_behind_its_prefetch")
+    assert rc < 0 and waited
+    assert rc2 == 0 and events == []
+
+
+if __name__ == "__main__":
+    print(json.dumps(globals()[sys.argv[2]](sys.argv[1], *json.loads(sys.argv[3]))))
