@@ -63,6 +63,17 @@ static int join_prefetch(Ctx* c, hipStream_t s, bool may_query) {
     return REALB_OK;
 }
 
+// A call that encodes its own weights comes behind a pending prefetch, which may be writing the same buffers.  The prefetch
+// stays pending: the call that consumes it may be on another stream.  (In a stream that is being recorded into a graph an event
+// from outside cannot be waited for; what a graph's replays find in flight is for the caller to join.)
+static int order_behind_prefetch(Ctx* c, hipStream_t s) {
+    if (!c->prefetch_pending) return REALB_OK;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    REALB_HIP(hipStreamIsCapturing(s, &capture));
+    if (capture == hipStreamCaptureStatusNone) REALB_HIP(hipStreamWaitEvent(s, c->ev_prefetch, 0));
+    return REALB_OK;
+}
+
 // The next layer's weights, on the side stream.  The caller has made sure that the buffers' readers (the previous call's
 // GEMMs) are done or waited for.
 static int issue_prefetch(Ctx* c, const realb_layer_io* io) {
@@ -127,6 +138,9 @@ static int rank_forward_steps(realb_ctx* ctx, realb_layer_io* io, int prec, void
     const bool gather = gate_up_gather_supported(c, io->T, fp4);
     if (io->overlap == 4 || prefetch) {                   // weights encoded by the previous call's prefetch, or its buffers reused
         rc = join_prefetch(c, s, false);
+        if (rc != REALB_OK) return rc;
+    } else if (encode_weights) {
+        rc = order_behind_prefetch(c, s);
         if (rc != REALB_OK) return rc;
     }
     // FP4: the encoding rides along with the index kernels -- W13 beside the counting, tokens and W2 beside the ranking
@@ -224,6 +238,8 @@ static int layer_forward_steps(realb_ctx* ctx, realb_layer_io* io, void* stream)
         beside_finish.when = prec;
         add_tokens(c, io, kSideThreads, &beside_finish);
         if (io->overlap != 2 && io->overlap != 4) {
+            rc = order_behind_prefetch(c, s);
+            if (rc != REALB_OK) return rc;
             if (prec.fixed == REALB_FP4 || io->overlap == 3) rc = add_w13(c, io, kTopkThreads, &beside_topk);
             else rc = add_w13(c, io, kSideThreads, &beside_finish);
             if (rc == REALB_OK) rc = add_w2(c, io, kSideThreads, &beside_finish);

@@ -19,7 +19,7 @@ A, B = 0xA0000, 0xB0000                                  # two caller's streams
 class Host:
     """The library behind the stand-ins; every tensor is an address that nobody reads."""
 
-    def __init__(self, stub, T=512, E=64, k=6, D=8, H=256, I=128):
+    def __init__(self, stub, T=4096, E=64, k=6, D=8, H=256, I=128):
         self.stub = C.CDLL(stub, mode=C.RTLD_GLOBAL)
         self.stub.calls_log.restype = C.c_char_p
         self.lib = C.CDLL(os.path.join(ROOT, "paper_2604_19503_amd", "librealb.so"))
@@ -113,6 +113,27 @@ def call_that_fails_behind_its_prefetch(stub):
     return [rc, calls[-1] == ["wait", ev, A], rc2, [c for c in used if c[0] != "launch"]]
 
 
+def encoding_behind_a_prefetch(stub):
+    """Calls that encode their weights themselves while a prefetch is pending: (placement, precision call, waits for the prefetch
+    before its first launch, the consuming call on another stream still waits); then the same under capture."""
+    h = Host(stub)
+    out = []
+    for overlap in (0, 1, 3):
+        for how in ("layer", "open", "rank"):
+            for again in (False, True):                  # again: the call issues a prefetch of its own
+                ev = h.pending_prefetch(A)
+                io = h.io(overlap, force=-1 if how == "open" else 1, prefetch=again, T=4096)
+                _, calls = h.rank(io, 1, A) if how == "rank" else h.layer(io, A)
+                first = next(i for i, c in enumerate(calls) if c[0] == "launch")
+                _, used = h.rank(h.io(4), 1, B)
+                first_used = next(i for i, c in enumerate(used) if c[0] == "launch")
+                out.append([overlap, how, again, ["wait", ev, A] in calls[:first], ["wait", ev, B] in used[:first_used]])
+    ev = h.pending_prefetch(A)
+    h.stub.calls_set_capturing(1)
+    rc, calls = h.rank(h.io(1), 1, B)
+    return out, [rc, [c for c in calls if c[0] != "launch"]]
+
+
 # ------------------------------------------------------------------------------------------ the tests
 @pytest.fixture(scope="session")
 def stub(tmp_path_factory):
@@ -139,6 +160,18 @@ def test_call_that_fails_behind_its_prefetch_waits_for_it(stub):
     rc, waited, rc2, events = _run(stub, "call_that_fails_behind_its_prefetch")
     assert rc < 0 and waited
     assert rc2 == 0 and events == []
+
+
+def test_call_that_encodes_its_weights_waits_for_a_pending_prefetch(stub):
+    """The prefetch may be writing the very buffers that the call encodes into.  Only the call that consumes it (or issues the
+    next one) takes it off the list; an encoding call recorded into a graph, where an event from outside cannot be waited
+    for, is recorded as before."""
+    eager, (rc, captured) = _run(stub, "encoding_behind_a_prefetch")
+    for overlap, how, again, waits, still_pending in eager:
+        assert waits, (overlap, how, again)
+        # (a layer call ends in an error here before it gets to its own prefetch; a rank call has replaced the pending one)
+        assert still_pending or again, (overlap, how, again)
+    assert rc == 0 and captured == []
 
 
 if __name__ == "__main__":
