@@ -223,6 +223,8 @@ static int layer_forward_steps(realb_ctx* ctx, realb_layer_io* io, void* stream)
     REALB_REQUIRE(io->expert_cnt && io->expert_vis && io->rank_load && io->rank_vis, REALB_EINVAL, "NULL argument");
     REALB_REQUIRE(io->T == 0 || (io->logits && io->is_vision), REALB_EINVAL, "NULL argument");
     if (io->force == REALB_FP4) REALB_REQUIRE(fp4_buffers(io), REALB_EINVAL, "NULL FP4 buffer");
+    if (io->overlap == 3 && io->force != REALB_BF16)
+        REALB_REQUIRE(io->w13_q && io->w13_s && io->w2_q && io->w2_s, REALB_EINVAL, "NULL FP4 weight buffer");
     const PrecisionSource prec = precision_source(c, io->T, io->force, io->rank, io->rank_load, io->rank_vis);
     const bool can_fp4 = prec.fixed != REALB_BF16, can_bf16 = prec.fixed != REALB_FP4;
     const bool prefetch = io->next_w13 != nullptr;

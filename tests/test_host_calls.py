@@ -134,6 +134,17 @@ def encoding_behind_a_prefetch(stub):
     return out, [rc, [c for c in calls if c[0] != "launch"]]
 
 
+def speculation_without_buffers(stub):
+    h = Host(stub)
+    out = []
+    for T in (64, 4096):                                 # gate closed: the decision will be BF16; open
+        rc, calls = h.layer(h.io(3, force=-1, fp4=False, T=T), A)
+        out.append([rc, calls])
+    forced = h.layer(h.io(3, force=0, fp4=False), A)     # forced BF16: nothing is speculated on
+    plain = h.layer(h.io(1, force=-1, fp4=False), A)
+    return out, [len([c for c in calls if c[0] == "launch"]) for _, calls in (forced, plain)]
+
+
 # ------------------------------------------------------------------------------------------ the tests
 @pytest.fixture(scope="session")
 def stub(tmp_path_factory):
@@ -172,6 +183,13 @@ def test_call_that_encodes_its_weights_waits_for_a_pending_prefetch(stub):
         # (a layer call ends in an error here before it gets to its own prefetch; a rank call has replaced the pending one)
         assert still_pending or again, (overlap, how, again)
     assert rc == 0 and captured == []
+
+
+def test_speculative_encoding_needs_its_buffers(stub):
+    """Without the FP4 weight buffers a speculative call is refused before anything is enqueued, whatever the decision would be."""
+    refused, launches = _run(stub, "speculation_without_buffers")
+    assert refused == [[EINVAL, []], [EINVAL, []]]
+    assert all(n > 0 for n in launches)
 
 
 if __name__ == "__main__":
