@@ -76,11 +76,17 @@ __global__ void __launch_bounds__(256) combine_kernel(const u32x4c_t* __restrict
     else out[(size_t)t * chunks + c] = o;
 }
 
+// (a launch has fewer than 2^32 threads; pieces of 2^22 waves take half a millisecond and more, so another launch is nothing)
 template <bool NT_LOAD, bool NT_STORE>
 static void launch_combine(const void* y_rows, const int32_t* assign_to_row, const float* topk_w, int T, int k, int H, void* out, hipStream_t s) {
-    const long long items = (long long)T * ((H / 8 + 63) / 64);
-    hipLaunchKernelGGL((combine_kernel<NT_LOAD, NT_STORE>), dim3((unsigned)((items + 3) / 4)), dim3(256), 0, s, (const u32x4c_t*)y_rows,
-                       assign_to_row, topk_w, T, k, H, (u32x4c_t*)out);
+    const int chunks = H / 8, panels = (chunks + 63) / 64, most = (1 << 22) / panels;
+    for (int t = 0; t < T; t += most) {
+        const int n = T - t < most ? T - t : most;
+        hipLaunchKernelGGL((combine_kernel<NT_LOAD, NT_STORE>), dim3((unsigned)ceil_div((long long)n * panels, 4)), dim3(256), 0, s,
+                           (const u32x4c_t*)y_rows, assign_to_row + (size_t)t * k, topk_w + (size_t)t * k, n, k, H,
+                           (u32x4c_t*)out + (size_t)t * chunks);
+        if (T - t <= most) break;                         // (t + most may not fit)
+    }
 }
 
 }  // namespace realb

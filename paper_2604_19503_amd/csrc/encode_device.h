@@ -137,18 +137,18 @@ struct TokenJob {
     unsigned blocks;
 };
 
+constexpr unsigned kTokenBlocksMax = 1u << 20;
 // Block `block` (NT threads): a wave takes one token, 2048 elements in one go.  One token per wave, not several in turn:
 // what hides the latency of the chain ids -> row -> store is the number of waves (16384 tokens, 75 MB: 35 -> 24 us for the
-// launch that carries them together with W2).
+// launch that carries them together with W2); beyond kTokenBlocksMax blocks (4M tokens and more) they take turns, so that a
+// launch stays below 2^32 threads.
 template <int NT>
 __device__ __forceinline__ void encode_tokens_block(const TokenJob& job, unsigned block) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int t = (int)block * (NT / 64) + wave;
-    {
-        if (t >= job.T) return;
+    for (int t = (int)block * (NT / 64) + wave; t < job.T; t += (int)job.blocks * (NT / 64)) {
         const int e = lane < job.k ? job.topk_ids[(size_t)t * job.k + lane] - job.lo : -1;
-        if (__ballot(e >= 0 && e < job.n_local) == 0ull) return;                   // no local expert: nobody reads this row
+        if (__ballot(e >= 0 && e < job.n_local) == 0ull) continue;                 // no local expert: nobody reads this row
         const u32x4_t* src = job.x + (size_t)t * job.chunks;
         for (int c0 = 0; c0 < job.chunks; c0 += 256) {
             u32x4_t v[4];

@@ -44,8 +44,9 @@ static int add_w2(const Ctx* c, const realb_layer_io* io, int threads, SideJobs*
     return add_quant_tensor(&jobs->w, io->w2, (long long)c->n_local * c->cfg.H, c->cfg.I, io->w2_q, io->w2_s, threads);
 }
 static void add_tokens(const Ctx* c, const realb_layer_io* io, int threads, SideJobs* jobs) {
+    const unsigned blocks = (unsigned)ceil_div(io->T, threads / 64);
     jobs->x = TokenJob{(const u32x4_t*)io->x, io->topk_ids, (uint32_t*)io->x_q, io->x_s, io->T, c->cfg.k, c->cfg.H / 8,
-                       io->rank * c->n_local, c->n_local, (unsigned)ceil_div(io->T, threads / 64)};
+                       io->rank * c->n_local, c->n_local, blocks < kTokenBlocksMax ? blocks : kTokenBlocksMax};
 }
 
 // Makes `s` wait for the pending cross-layer prefetch.  may_query: an event that has completed is not waited for -- a wait

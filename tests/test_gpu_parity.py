@@ -844,6 +844,35 @@ def test_edge_sixty_four_local_experts_some_empty(R):
     ctx.close()
 
 
+def test_batches_beyond_one_launch_of_the_token_encoder_and_of_combine(R):
+    """4 M tokens and a few: the encoder's waves take a second token each, combine goes out in two launches."""
+    from paper_2604_19503_amd.binding import default_config
+    T, H = (1 << 22) + 101, 128
+    rcfg = default_config(T, 4, 1, 2, H, 128)
+    ctx = R.Context(rcfg)
+    b = R.LayerBuffers(rcfg, T)
+    gen = torch.Generator(device="cuda"); gen.manual_seed(3)
+    x = torch.randn((T, H), generator=gen, device="cuda").to(torch.bfloat16)
+    w13 = (torch.randn((2, 256, H), generator=gen, device="cuda") * 0.1).to(torch.bfloat16)
+    w2 = (torch.randn((2, H, 128), generator=gen, device="cuda") * 0.1).to(torch.bfloat16)
+    lg = torch.randn((T, 4), generator=gen, device="cuda")
+    _say("4 M tokens")
+    b.x_q.fill_(0x77); b.out.fill_(float("nan"))
+    io = ctx.make_io(lg, torch.zeros(T, dtype=torch.uint8, device="cuda"), x, w13, w2, b, 0, force=R.FP4, overlap=0)
+    assert ctx.layer_forward(io) == R.FP4
+    _sync()
+    local = (b.topk_ids[:, 0] < 2)
+    xq, xs = R.quantize_rows_fp4(x)
+    assert torch.equal(b.x_q[:T][local], xq[local]) and bool((b.x_q[:T][~local] == 0x77).all())
+    # scales: the dword of (row, the only K-step) is at index row
+    assert torch.equal(b.x_s.view(-1).view(torch.int32)[:T][local], xs.view(-1).view(torch.int32)[:T][local])
+    rows = b.assign_to_row.view(-1).long()
+    assert bool(((rows >= 0) == local).all()) and bool((b.topk_w == 1).all())
+    want = torch.where(local[:, None], b.y_rows[rows.clamp(min=0)].float() + 0.0, torch.zeros((), device="cuda")).to(torch.bfloat16)
+    assert torch.equal(b.out.view(torch.int16), want.view(torch.int16))
+    ctx.close()
+
+
 def test_capacity_and_argument_errors(R, case):
     b = case.buf
     big = torch.empty((case.cfg.T + 1, case.cfg.E), dtype=torch.float32, device="cuda")

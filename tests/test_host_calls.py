@@ -145,6 +145,16 @@ def speculation_without_buffers(stub):
     return out, [len([c for c in calls if c[0] == "launch"]) for _, calls in (forced, plain)]
 
 
+def largest_grids(stub, T, H, force):
+    """(return value, threads of the largest launch) of a rank call (force) or of combine alone (None)."""
+    h = Host(stub, T=T, E=2, k=1, D=2, H=H)
+    if force is None:
+        rc, calls = h.lib.realb_combine(h.ctx, h.new(), h.new(), h.new(), T, h.new(), A), h.calls()
+    else:
+        rc, calls = h.rank(h.io(0), force, A)
+    return rc, max(c[2] for c in calls if c[0] == "launch")
+
+
 # ------------------------------------------------------------------------------------------ the tests
 @pytest.fixture(scope="session")
 def stub(tmp_path_factory):
@@ -190,6 +200,17 @@ def test_speculative_encoding_needs_its_buffers(stub):
     refused, launches = _run(stub, "speculation_without_buffers")
     assert refused == [[EINVAL, []], [EINVAL, []]]
     assert all(n > 0 for n in launches)
+
+
+@pytest.mark.parametrize("T,H,force", [
+    ((1 << 22) + 3, 8192, None),                         # combine: 16 panels per token
+    ((1 << 26) + 5, 128, 0),                             # rows that the gate/up GEMM cannot fetch itself
+    ((1 << 26) - 1, 128, 1),                             # FP4, tokens encoded beside the ranking kernel
+])
+def test_no_launch_passes_the_runtimes_grid_limit(stub, T, H, force):
+    """Fewer than 2^32 threads in a launch, at sizes that a context is created for."""
+    rc, threads = _run(stub, "largest_grids", T, H, force)
+    assert rc == 0 and threads < 1 << 32
 
 
 if __name__ == "__main__":
