@@ -844,6 +844,36 @@ def test_edge_sixty_four_local_experts_some_empty(R):
     ctx.close()
 
 
+@pytest.mark.parametrize("H,T", [(640, 31000), (640, 31500), (2048, 9700), (2048, 9800)])
+def test_combine_on_both_sides_of_its_streaming_rule(R, H, T):
+    """Outputs just below and just above 38 MiB; H = 640 leaves the second panel of 512 columns partly empty.  The FP32 sums
+    differ from the float64 ones by 2^-22 of their terms at most (three roundings), which can move an element across one BF16
+    rounding boundary: one step, 2^-7 of its value."""
+    from paper_2604_19503_amd.binding import default_config
+    k, rows = 3, 4000
+    rcfg = default_config(T, 8, k, 1, H, 128)
+    ctx = R.Context(rcfg)
+    b = R.LayerBuffers(rcfg, T)
+    gen = torch.Generator(device="cuda"); gen.manual_seed(T)
+    b.y_rows[:rows] = torch.randn((rows, H), generator=gen, device="cuda").to(torch.bfloat16)
+    b.topk_w.copy_(torch.rand((T, k), generator=gen, device="cuda"))
+    a2r = torch.randint(-rows, rows, (T, k), generator=gen, device="cuda").clamp(min=-1).to(torch.int32)   # half of them not local
+    b.assign_to_row.copy_(a2r.view(-1))
+    b.out.fill_(float("nan"))
+    _say(f"combine H={H} T={T}")
+    ctx.combine(b)
+    _sync()
+    y, idx = b.y_rows[:rows].double(), a2r.long().clamp(min=0)
+    want, terms = torch.zeros((T, H), dtype=torch.float64, device="cuda"), torch.zeros((T, H), dtype=torch.float64, device="cuda")
+    for j in range(k):
+        term = y[idx[:, j]] * (b.topk_w[:, j].double() * (a2r[:, j] >= 0))[:, None]
+        want += term; terms += term.abs()
+    diff = (b.out.double() - want).abs()
+    assert bool((diff <= 2.0 ** -7 * want.abs() + 2.0 ** -22 * terms).all())
+    assert not bool(b.out[(a2r < 0).all(1)].any())
+    ctx.close()
+
+
 def test_batches_beyond_one_launch_of_the_token_encoder_and_of_combine(R):
     """4 M tokens and a few: the encoder's waves take a second token each, combine goes out in two launches."""
     from paper_2604_19503_amd.binding import default_config
