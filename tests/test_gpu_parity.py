@@ -134,6 +134,22 @@ def test_route_stats_expert_counts_and_ties(R, E, k, D):
 def test_layer_routing_at_the_edges_of_its_blocks(R, E, k, D, T):
     """The layer call's routing and index kernels share the tokens out to blocks of 16 or more by the size of the batch:
     selection, statistics and row tables at the sizes where that changes or leaves a remainder."""
+    _check_layer_routing(R, E, k, D, T)
+
+
+@pytest.mark.parametrize("T", [3, 64])
+@pytest.mark.parametrize("E,k,D", [(16, 2, 2), (32, 16, 1), (48, 4, 3), (64, 16, 1), (80, 8, 5), (96, 6, 4), (112, 16, 7), (128, 8, 8), (128, 16, 2)])
+def test_layer_routing_of_a_decode_batch(R, E, k, D, T):
+    """Every instantiation of the one-launch routing kernel, with its largest batch, k = 16 and up to 64 local experts."""
+    _check_layer_routing(R, E, k, D, T)
+
+
+def test_layer_routing_with_more_assignments_per_block_than_registers_hold(R):
+    """2304 assignments per routing block: the index kernel reads them again instead of keeping them."""
+    _check_layer_routing(R, 64, 16, 64, 33000)
+
+
+def _check_layer_routing(R, E, k, D, T):
     from paper_2604_19503_amd.binding import default_config
     rng = np.random.default_rng(T * 10 + k)
     logits = rng.standard_normal((T, E)).astype(np.float32)
@@ -640,6 +656,67 @@ def test_cross_layer_prefetch_pipeline_is_bit_identical(R, reserve):
     with pytest.raises(R.RealbError):
         ctx.layer_forward(io)
     _sync()
+    ctx.close()
+
+
+@pytest.mark.parametrize("rank,reached", [(0, 1), (5, 0)])
+def test_prefetch_pipeline_with_an_open_decision(R, rank, reached):
+    """Layer calls that leave the precision to the policy and prefetch the next layer's weights: outputs and encoded weights
+    are those of plain calls forced to the precision that the policy chooses (hot rank FP4, cold rank BF16), bit for bit."""
+    from paper_2604_19503_amd.binding import default_config
+    cfg = W.scaled(W.CONFIGS["c2"], T=2500, H=256, I=384)
+    rcfg = default_config(cfg.T, cfg.E, cfg.k, cfg.D, cfg.H, cfg.I)
+    ctx = R.Context(rcfg)
+    inp = W.gen_layer(cfg, 51)
+    x = R.bf16_from_bits(inp["x"])
+    lg = torch.from_numpy(inp["logits"]).cuda(); isv = torch.from_numpy(inp["is_vision"]).cuda()
+    ids, _ = orouter.topk_route(inp["logits"], cfg.k)
+    _, _, load, vis = orouter.route_counts(ids, inp["is_vision"], cfg.E, cfg.D)
+    L = 3
+    ws = [tuple(R.bf16_from_bits(a) for a in W.gen_weights(cfg, 320 + l)) for l in range(L)]
+    b = R.LayerBuffers(rcfg, cfg.T)
+    ref = []
+    for l in range(L):
+        ctx.layer_forward(ctx.make_io(lg, isv, x, *ws[l], b, rank, force=reached, overlap=0))
+        ctx.quantize_experts_fp4(*ws[l], b)
+        _sync()
+        ref.append([t.clone() for t in (b.out, b.w13_q, b.w13_s, b.w2_q, b.w2_s)])
+    pair = [R.WeightBuffers(rcfg), R.WeightBuffers(rcfg)]
+    ctx.M = M = 0.9
+    _say(f"open prefetch pipeline rank={rank}")
+    for l in range(L):
+        io = ctx.make_io(lg, isv, x, *ws[l], b, rank, overlap=0 if l == 0 else 4)
+        cur, nxt = pair[l & 1], pair[(l + 1) & 1]
+        ctx.use_weight_buffers(io, cur)
+        if l + 1 < L:
+            for t in (nxt.w13_q, nxt.w13_s, nxt.w2_q, nxt.w2_s):
+                t.fill_(0xEE)
+            ctx.set_prefetch(io, *ws[l + 1], nxt, 0)
+        b.out.fill_(float("nan"))
+        want = opol.select_precision(load, vis, cfg.T, cfg.k, M)
+        assert ctx.layer_forward(io) == want[0][rank] == reached
+        M = want[2]
+        assert io.M_after == M == ctx.M
+        out = b.out.clone()
+        ctx.prefetch_join()                              # (the next call finds nothing pending; overlap = 4 is still right)
+        _sync()
+        assert torch.equal(out.view(torch.int16), ref[l][0].view(torch.int16)), l
+        if l + 1 < L:
+            for got, r in zip((nxt.w13_q, nxt.w13_s, nxt.w2_q, nxt.w2_s), ref[l + 1][1:]):
+                assert torch.equal(got, r), l
+    # the same without a join or a synchronisation in between
+    outs = []
+    for l in range(L):
+        io = ctx.make_io(lg, isv, x, *ws[l], b, rank, overlap=0 if l == 0 else 4)
+        ctx.use_weight_buffers(io, pair[l & 1])
+        if l + 1 < L:
+            ctx.set_prefetch(io, *ws[l + 1], pair[(l + 1) & 1], 8)
+        ctx.M = 0.9
+        assert ctx.layer_forward(io) == reached
+        outs.append(b.out.clone())
+    _sync()
+    for l in range(L):
+        assert torch.equal(outs[l].view(torch.int16), ref[l][0].view(torch.int16)), l
     ctx.close()
 
 
