@@ -223,8 +223,8 @@ int realb_set_gemm_tile(int wn);
 
 /* Tuning hook for this context's step-by-step GEMM entry points where the selector above is 0: 0 = shapes picked on the
  * device (default), 1 / 2 / 3 = 64x256, 128x256 or 192x256 tiles only, 5 = 64x128 tiles only (needs four K-steps, else
- * 64x256).  The layer and rank calls always pick.  Outputs of all shapes are
- * bit-identical.  REALB_EINVAL for any other value. */
+ * 64x256).  The layer and rank calls pick for themselves, except where they go through a permuted copy of the rows (token
+ * matrices of 4 GiB and more).  Outputs of all shapes are bit-identical.  REALB_EINVAL for any other value. */
 int realb_set_gemm_tile_shape(realb_ctx* ctx, int shape);
 
 /* Unpermute + weighted combine (local part of the result combination):
@@ -245,7 +245,8 @@ typedef struct {
                                                        else from the one that knows the decision; 0 and 1 no longer differ),
                                                    2 = skipped (w13_q .. w2_s already hold this layer's encoded weights),
                                                    3 = speculative (realb_layer_forward only): like 1, but W13's goes beside the
-                                                       routing kernel, ahead of the decision, and is unused if that is BF16,
+                                                       routing kernel, ahead of the decision, and is unused if that is BF16 (the FP4
+                                                       weight buffers are then required unless BF16 is forced),
                                                    4 = prefetched: w13_q .. w2_s are being filled by the previous call's
                                                        cross-layer prefetch (see next_w13 below); the GEMMs wait for it */
     long long max_rows;
@@ -253,7 +254,9 @@ typedef struct {
        receive their FP4 encoding.  The encoder for them is issued on the context's side stream once this layer's
        gate/up GEMM has started and runs beside this layer's two GEMMs, which leave `reserve_cus` compute units
        free for it (their persistent grids shrink by that many blocks).  The next call then passes those buffers as
-       w13_q .. w2_s with overlap = 4.  The buffers must differ from this call's w13_q .. w2_s. */
+       w13_q .. w2_s with overlap = 4.  The buffers must differ from this call's w13_q .. w2_s.  A call that encodes its own
+       weights while a prefetch is in flight waits for it first (not while it is being recorded into a graph); a refused call
+       leaves it to the call that will consume it. */
     const void* next_w13; const void* next_w2;
     uint8_t* next_w13_q; uint8_t* next_w13_s; uint8_t* next_w2_q; uint8_t* next_w2_s;
     int reserve_cus;

@@ -708,7 +708,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         auto slice = [&](int s, int produce, bool multiply, int next) __attribute__((always_inline)) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) {
-                if (multiply && multiplies) {
+                if (multiply) {
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
                         if (s & 1) mma<FP4, 2>(acc[mt][t], fb[s & 1][t], fa[s & 1][mt], sb[t][s >> 1], sa[mt][s >> 1]);
@@ -716,7 +716,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
                     }
                 }
                 __builtin_amdgcn_sched_barrier(0);
-                if (next >= 0 && multiplies) {
+                if (next >= 0) {
                     if (next < 4) read_frags_part(mt, next, next & 1, st);
                     else { read_scales_part(mt, stg); read_frags_part(mt, 0, 0, smem + stg * G::STAGE); }
                 }
