@@ -66,12 +66,21 @@ static int join_prefetch(Ctx* c, hipStream_t s, bool may_query) {
 
 // A call that encodes its own weights comes behind a pending prefetch, which may be writing the same buffers.  The prefetch
 // stays pending: the call that consumes it may be on another stream.  (In a stream that is being recorded into a graph an event
-// from outside cannot be waited for; what a graph's replays find in flight is for the caller to join.)
-static int order_behind_prefetch(Ctx* c, hipStream_t s) {
+// from outside cannot be waited for; what a graph's replays find in flight is for the caller to join.)  may_query, as above: a
+// prefetch that has ended is pending no more -- else every call after a pipeline that nobody continued would wait for it again.
+static int order_behind_prefetch(Ctx* c, hipStream_t s, bool may_query) {
     if (!c->prefetch_pending) return REALB_OK;
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     REALB_HIP(hipStreamIsCapturing(s, &capture));
-    if (capture == hipStreamCaptureStatusNone) REALB_HIP(hipStreamWaitEvent(s, c->ev_prefetch, 0));
+    if (capture != hipStreamCaptureStatusNone) return REALB_OK;
+    if (may_query) {
+        if (hipEventQuery(c->ev_prefetch) == hipSuccess) {
+            c->prefetch_pending = false;
+            return REALB_OK;
+        }
+        (void)hipGetLastError();                          // (not-ready is no error of this call)
+    }
+    REALB_HIP(hipStreamWaitEvent(s, c->ev_prefetch, 0));
     return REALB_OK;
 }
 
@@ -141,7 +150,7 @@ static int rank_forward_steps(realb_ctx* ctx, realb_layer_io* io, int prec, void
         rc = join_prefetch(c, s, false);
         if (rc != REALB_OK) return rc;
     } else if (encode_weights) {
-        rc = order_behind_prefetch(c, s);
+        rc = order_behind_prefetch(c, s, false);
         if (rc != REALB_OK) return rc;
     }
     // FP4: the encoding rides along with the index kernels -- W13 beside the counting, tokens and W2 beside the ranking
@@ -241,7 +250,7 @@ static int layer_forward_steps(realb_ctx* ctx, realb_layer_io* io, void* stream)
         beside_finish.when = prec;
         add_tokens(c, io, kSideThreads, &beside_finish);
         if (io->overlap != 2 && io->overlap != 4) {
-            rc = order_behind_prefetch(c, s);
+            rc = order_behind_prefetch(c, s, true);
             if (rc != REALB_OK) return rc;
             if (prec.fixed == REALB_FP4 || io->overlap == 3) rc = add_w13(c, io, kTopkThreads, &beside_topk);
             else rc = add_w13(c, io, kSideThreads, &beside_finish);

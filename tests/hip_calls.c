@@ -13,7 +13,7 @@ enum { kNotReady = 600 };
 static char* log_text;
 static size_t log_len, log_cap;
 static intptr_t next_handle = 0x1000;
-static int last_error, capturing;
+static int last_error, capturing, events_done;
 static char failing[128];
 
 static void record(const char* line) {
@@ -29,6 +29,7 @@ static void record(const char* line) {
 const char* calls_log(void) { return log_text ? log_text : ""; }
 void calls_clear(void) { log_len = 0; if (log_text) log_text[0] = 0; }
 void calls_set_capturing(int on) { capturing = on; }
+void calls_set_events_done(int on) { events_done = on; }
 /* launches of kernels whose name holds this text fail ("": none) */
 void calls_fail(const char* kernel) { snprintf(failing, sizeof failing, "%s", kernel); }
 
@@ -65,7 +66,7 @@ int hipLaunchKernel(const void* f, dim3_t grid, dim3_t block, void** args, size_
 int hipEventRecord(void* e, void* s) { char l[96]; snprintf(l, sizeof l, "record event %p stream %p", e, s); record(l); return 0; }
 int hipStreamWaitEvent(void* s, void* e, unsigned f) { char l[96]; (void)f; snprintf(l, sizeof l, "wait event %p stream %p", e, s); record(l); return 0; }
 int hipStreamIsCapturing(void* s, int* status) { (void)s; *status = capturing; return 0; }
-int hipEventQuery(void* e) { (void)e; return kNotReady; }
+int hipEventQuery(void* e) { (void)e; return events_done ? 0 : kNotReady; }
 int hipStreamQuery(void* s) { (void)s; return 0; }
 int hipEventSynchronize(void* e) { (void)e; return 0; }
 int hipEventElapsedTime(float* ms, void* a, void* b) { (void)a; (void)b; *ms = 0; return 0; }

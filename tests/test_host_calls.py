@@ -134,6 +134,16 @@ def encoding_behind_a_prefetch(stub):
     return out, [rc, [c for c in calls if c[0] != "launch"]]
 
 
+def encoding_behind_an_ended_prefetch(stub):
+    """The event waits of two layer calls that encode their own weights and of a consuming rank call on another stream, once
+    the prefetch of a pipeline that nobody continued has ended."""
+    h = Host(stub)
+    h.pending_prefetch(A)
+    h.stub.calls_set_events_done(1)
+    calls = [h.layer(h.io(1, force=1), A)[1], h.layer(h.io(3, force=1), A)[1], h.rank(h.io(4), 1, B)[1]]
+    return [[e for e in c if e[0] == "wait"] for c in calls]
+
+
 def speculation_without_buffers(stub):
     h = Host(stub)
     out = []
@@ -193,6 +203,11 @@ def test_call_that_encodes_its_weights_waits_for_a_pending_prefetch(stub):
         # (a layer call ends in an error here before it gets to its own prefetch; a rank call has replaced the pending one)
         assert still_pending or again, (overlap, how, again)
     assert rc == 0 and captured == []
+
+
+def test_an_ended_prefetch_is_waited_for_no_more(stub):
+    """A wait costs the stream microseconds also for an event that has completed."""
+    assert _run(stub, "encoding_behind_an_ended_prefetch") == [[], [], []]
 
 
 def test_speculative_encoding_needs_its_buffers(stub):
