@@ -70,11 +70,12 @@ __global__ void __launch_bounds__(1024, 2) topk_hist_kernel(const float* __restr
     const float NEG = -INFINITY;
     // The wave's next token is fetched while the current one is being ranked (one load latency per
     // wave instead of one per token).
-    const int stride = waves_per_block, t_end = min(T, ((int)blockIdx.x + 1) * per_block);
-    int t = blockIdx.x * per_block + wave;
+    // (token indices are unsigned: a block's whole share, and the token after next, may lie beyond 2^31)
+    const unsigned stride = waves_per_block, t_end = min((unsigned)T, (blockIdx.x + 1) * (unsigned)per_block);
+    unsigned t = blockIdx.x * (unsigned)per_block + wave;
     float nx[EPL];
     int nx_vision = 0;
-    auto fetch = [&](int tok) __attribute__((always_inline)) {
+    auto fetch = [&](unsigned tok) __attribute__((always_inline)) {
         if (tok < t_end) {
             const float* row = logits + (size_t)tok * E + lane * EPL;
 #pragma unroll
@@ -138,7 +139,7 @@ __device__ __forceinline__ int row_min_i(int v) {
 // maximum (lowest index wins ties) -- DPP only, no scalar round trips, the four rows in lock step.
 // The block's tokens are t_lo .. t_end-1.  hist (LDS, zeroed): 2*E counters; KEEP: the expert ids also go to kept (LDS).
 template <int EPL, bool KEEP>
-__device__ __forceinline__ void topk_rows(const float* __restrict__ logits, const uint8_t* __restrict__ is_vision, int t_lo, int t_end,
+__device__ __forceinline__ void topk_rows(const float* __restrict__ logits, const uint8_t* __restrict__ is_vision, unsigned t_lo, unsigned t_end,
                                           int E, int k, int32_t* __restrict__ topk_ids, float* __restrict__ topk_w, int32_t* hist,
                                           int32_t* kept) {
     const int lane = threadIdx.x & 63;
@@ -146,11 +147,11 @@ __device__ __forceinline__ void topk_rows(const float* __restrict__ logits, cons
     const int wave = threadIdx.x >> 6;
     const int waves_per_block = blockDim.x >> 6;
     const float NEG = -INFINITY;
-    const int stride = waves_per_block * 4;
-    int t = t_lo + wave * 4 + r;
+    const unsigned stride = waves_per_block * 4;
+    unsigned t = t_lo + wave * 4 + r;
     float nx[EPL];
     int nx_vision = 0;
-    auto fetch = [&](int tok) __attribute__((always_inline)) {
+    auto fetch = [&](unsigned tok) __attribute__((always_inline)) {
         if (tok < t_end) {
             const float* row = logits + (size_t)tok * E + j * EPL;
 #pragma unroll
@@ -159,7 +160,7 @@ __device__ __forceinline__ void topk_rows(const float* __restrict__ logits, cons
         }
     };
     fetch(t);
-    for (int t0 = t - r; t0 < t_end; t0 += stride, t += stride) {  // uniform trip count: rows past the end idle but take part in the DPP steps
+    for (unsigned t0 = t - r; t0 < t_end; t0 += stride, t += stride) {  // uniform trip count: rows past the end idle but take part in the DPP steps
         float v[EPL];
 #pragma unroll
         for (int q = 0; q < EPL; ++q) v[q] = nx[q];
@@ -204,7 +205,7 @@ __global__ void __launch_bounds__(1024, 2) topk_hist_rows_kernel(const float* __
     extern __shared__ int32_t hist[];                 // [2*E]: counts, vision counts
     for (int i = threadIdx.x; i < 2 * E; i += blockDim.x) hist[i] = 0;
     __syncthreads();
-    topk_rows<EPL, false>(logits, is_vision, blockIdx.x * per_block, min(T, ((int)blockIdx.x + 1) * per_block), E, k, topk_ids, topk_w,
+    topk_rows<EPL, false>(logits, is_vision, blockIdx.x * (unsigned)per_block, min((unsigned)T, (blockIdx.x + 1) * (unsigned)per_block), E, k, topk_ids, topk_w,
                           hist, nullptr);
     __syncthreads();
     for (int i = threadIdx.x; i < 2 * E; i += blockDim.x) hist_part[(size_t)blockIdx.x * 2 * E + i] = hist[i];

@@ -45,6 +45,25 @@ def test_static_scratch_route_stats_matches_the_context_call(E, k, D):
     ctx.close()
 
 
+def test_route_stats_of_the_largest_batch():
+    """T = 2^31 - 1 tokens (one expert, so that the tensors fit): the last block's whole share of tokens ends beyond the
+    largest 32-bit integer, and every token is routed and counted all the same."""
+    from types import SimpleNamespace
+    import paper_2604_19503_amd as R
+    T = 2 ** 31 - 1
+    print(f"[no-alloc] T={T}", flush=True)
+    lg = torch.zeros((T, 1), dtype=torch.float32, device="cuda")
+    iv = torch.zeros(T, dtype=torch.uint8, device="cuda")
+    iv[-1000:] = 1
+    one = lambda: torch.full((1,), -3, dtype=torch.int32, device="cuda")
+    b = SimpleNamespace(topk_ids=torch.full((T, 1), -3, dtype=torch.int32, device="cuda"), topk_w=torch.zeros((T, 1), dtype=torch.float32, device="cuda"),
+                        expert_cnt=one(), expert_vis=one(), rank_load=one(), rank_vis=one())
+    R.route_stats_static(lg, iv, 1, 1, 1, b)
+    torch.cuda.synchronize()
+    assert int(b.expert_cnt[0]) == int(b.rank_load[0]) == T and int(b.expert_vis[0]) == int(b.rank_vis[0]) == 1000
+    assert not b.topk_ids.any() and bool((b.topk_w == 1.0).all())
+
+
 def test_static_scratch_route_stats_rejects_sizes_beyond_its_array():
     import paper_2604_19503_amd as R
     from paper_2604_19503_amd.binding import default_config
