@@ -18,8 +18,8 @@ N(0, 0.02), because only timing is taken):
                   iterations with the vision skew redrawn, AIMD state carried: max-over-ranks
                   layer time, all-BF16 versus the policy's mixed-precision plan.
   --workload c5   48 layers with distinct BF16 weight sets on a Qwen3-VL-shaped rank, 65536
-                  tokens: per-layer time with the weight encoding on the side stream, on the
-                  main stream, and skipped (weights encoded beforehand) -> exposed encoding time.
+                  tokens: per-layer time with each placement of the weight encoding and with the
+                  encoding skipped (weights encoded beforehand) -> exposed encoding time.
   --workload gate-sweep [--shape c2|c3]
                   the measured rank's layer time with FP4 forced (weight encoding included) and with BF16
                   forced, for batch sizes T = 64 .. 65536 (prefixes of one seeded batch): the smallest T from
@@ -50,8 +50,23 @@ if ROOT not in sys.path:
 PEAK_TFLOPS = {"fp4": 10100.0, "bf16": 2500.0}     # MI355X dense MFMA peaks
 PEAK_HBM_GBS = 8000.0
 PREROLL_MS = 150.0                                  # untimed steps before the timed region, beyond --warmup
-ENCODE_MODES = ("prefetch", "speculative", "side", "main")
-MODE_ID = {"speculative": 3, "side": 1, "main": 0}
+ENCODE_MODES = ("prefetch", "speculative", "after", "separate")
+
+
+def single_layer_step(ctx, lg, isv, x, w13, w2, buf, rank, force, mode):
+    """A function that runs one whole rank-layer step with the weight encoding placed by `mode` (see --encode-mode; with BF16
+    forced there is nothing to place, and "speculative" is the plain layer call)."""
+    io = ctx.make_io(lg, isv, x, w13, w2, buf, rank, force=force, overlap={"speculative": 3, "after": 1, "separate": 2}[mode])
+
+    def after():
+        ctx.route_stats(lg, isv, buf)
+        prec, _, _ = ctx.select_precision(buf, io.T, force)
+        ctx.rank_forward(io, int(prec[rank]))
+
+    def separate():
+        ctx.quantize_experts_fp4(w13, w2, buf)
+        ctx.layer_forward(io)
+    return {"speculative": lambda: ctx.layer_forward(io), "after": after, "separate": separate}[mode]
 
 
 class LayerRun:
@@ -82,8 +97,7 @@ class LayerRun:
         R, ctx = self.R, self.ctx
         force = R.FP4 if fp4 else R.BF16
         if not (fp4 and mode == "prefetch"):
-            io = ctx.make_io(self.lg, self.isv, self.x, self.w13, self.w2, self.buf, self.cfg.rank, force=force, overlap=MODE_ID[mode])
-            return lambda: ctx.layer_forward(io)
+            return single_layer_step(ctx, self.lg, self.isv, self.x, self.w13, self.w2, self.buf, self.cfg.rank, force, mode)
         if self._pair is None:
             import workloads as W
             wB = tuple(R.bf16_from_bits(a) for a in W.gen_weights(self.cfg, 1))
@@ -153,11 +167,11 @@ def parse():
     ap.add_argument("--precision", default="fp4", choices=["fp4", "bf16"])
     ap.add_argument("--no-cpu-baseline", action="store_true")
     ap.add_argument("--encode-mode", default="speculative", choices=list(ENCODE_MODES),
-                    help="where the FP4 weight encoding runs: speculative (default) = side stream ahead of the decision, beside the routing and "
-                         "index kernels; prefetch = layer pipeline, each step encodes the next layer's weights on the side stream beside "
-                         "its own GEMMs; main = caller's "
-                         "stream after the decision; side = side stream after the decision (under the permutation).  The step is timed "
-                         "in all of them, in rotated order, and reported under extra")
+                    help="where the FP4 weight encoding runs: speculative (default) = one layer call, W13's encoding beside its routing "
+                         "kernel, tokens and W2 beside its index kernel; prefetch = layer pipeline, each step encodes the next layer's "
+                         "weights on the side stream beside its own GEMMs; after = routing and decision as calls of their own, then the "
+                         "rank call, which encodes beside its permutation kernels; separate = the encoder in a launch of its own in "
+                         "front of a layer call.  The step is timed in all of them, in rotated order, and reported under extra")
     ap.add_argument("--reserve-cus", type=int, default=0, help="compute units the GEMMs leave to the encoder in prefetch mode")
     ap.add_argument("--only-headline", action="store_true",
                     help="time the headline placement only (profiling runs: every launch of a kernel then belongs to the same placement)")
@@ -294,8 +308,8 @@ def run_c4(args):
 
 
 def run_c5(args):
-    """Overlap stress: how much of the on-the-fly weight transformation stays exposed when it
-    runs on the side stream under the permutation (the paper hides it under dispatch)."""
+    """Overlap stress: how much of the on-the-fly weight transformation stays exposed in each of its
+    placements (the paper hides it under dispatch)."""
     import numpy as np
     import torch
     import workloads as W
@@ -311,12 +325,12 @@ def run_c5(args):
     isv = torch.from_numpy(isv_np).cuda()
     lg = torch.from_numpy(W.gen_logits(cfg, 0, isv_np)).cuda()
     weights = [_device_weights(torch, cfg.n_local, cfg.H, cfg.I, 200 + l) for l in range(layers)]
-    ios = {mode: [ctx.make_io(lg, isv, x, w13, w2, buf, cfg.rank, force=R.FP4, overlap=mode) for (w13, w2) in weights]
-           for mode in (0, 1, 3)}
+    steps = {mode: [single_layer_step(ctx, lg, isv, x, w13, w2, buf, cfg.rank, R.FP4, mode) for (w13, w2) in weights]
+             for mode in ("speculative", "after", "separate")}
 
     def sweep(mode):
         for l in range(layers):
-            ctx.layer_forward(ios[mode][l])
+            steps[mode][l]()
 
     def timed(mode):
         sweep(mode)
@@ -339,15 +353,15 @@ def run_c5(args):
             nw = weights[(l + 1) % layers]
             ctx.set_prefetch(io, nw[0], nw[1], pair[(l + 1) & 1], reserve)
             pios.append(io)
-        ios[("prefetch", reserve)] = pios
+        steps[("prefetch", reserve)] = [lambda io=io: ctx.layer_forward(io) for io in pios]
         ctx.quantize_experts_fp4(weights[0][0], weights[0][1], pair[0])
         ms_prefetch[reserve] = timed(("prefetch", reserve))
         ctx.prefetch_join()
         torch.cuda.synchronize()
     best_reserve = min(ms_prefetch, key=ms_prefetch.get)
-    ms_overlap = timed(1)
-    ms_seq = timed(0)
-    ms_spec = timed(3)
+    ms_after = timed("after")
+    ms_separate = timed("separate")
+    ms_spec = timed("speculative")
     # weights encoded beforehand: one layer's buffers reused (the GEMMs read the same bytes each time)
     io2 = ctx.make_io(lg, isv, x, weights[0][0], weights[0][1], buf, cfg.rank, force=R.FP4, overlap=0)
     ctx.layer_forward(io2)
@@ -373,10 +387,11 @@ def run_c5(args):
                                      "85% vision, 48 distinct BF16 weight sets"},
               "extra": {"rows_on_rank": rows, "layer_ms_prefetch_by_reserved_cus": {str(k_): round(v, 5) for k_, v in ms_prefetch.items()},
                         "reserved_cus": best_reserve, "exposed_encoding_ms_prefetch": ms_pf - ms_noquant,
-                        "layer_ms_overlap": ms_overlap, "layer_ms_sequential": ms_seq,
-                        "layer_ms_weights_pre_encoded": ms_noquant, "exposed_encoding_ms_overlap": ms_overlap - ms_noquant,
-                        "exposed_encoding_ms_sequential": ms_seq - ms_noquant, "layer_ms_speculative": ms_spec,
-                        "exposed_encoding_ms_speculative": ms_spec - ms_noquant, "encoder_alone_ms": qms,
+                        "layer_ms_weights_pre_encoded": ms_noquant,
+                        "layer_ms_speculative": ms_spec, "exposed_encoding_ms_speculative": ms_spec - ms_noquant,
+                        "layer_ms_after_decision": ms_after, "exposed_encoding_ms_after_decision": ms_after - ms_noquant,
+                        "layer_ms_separate": ms_separate, "exposed_encoding_ms_separate": ms_separate - ms_noquant,
+                        "encoder_alone_ms": qms,
                         "encoder_alone_gbs": n_w * 2.53125 / (qms * 1e-3) / 1e9,
                         "paper_context": "paper: hiding the transformation is worth 3% end to end (ReaLB vs ReaLB-seq)"}}
     if args.detail:
@@ -411,23 +426,22 @@ def run_gate_sweep(args):
     for T in (64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384, 32768, 65536):
         x, isv, lg = x_all[:T], isv_all[:T], lg_all[:T]
         ms = {}
-        for name, force, mode in (("bf16", R.BF16, 3), ("fp4", R.FP4, 3), ("fp4_side", R.FP4, 1)):
-            io = ctx.make_io(lg, isv, x, w13, w2, buf, cfg.rank, force=force, overlap=mode)
-            io.T = T
+        for name, force, mode in (("bf16", R.BF16, "speculative"), ("fp4", R.FP4, "speculative"), ("fp4_after", R.FP4, "after")):
+            step = single_layer_step(ctx, lg, isv, x, w13, w2, buf, cfg.rank, force, mode)
             for _ in range(3):
-                ctx.layer_forward(io)
+                step()
             torch.cuda.synchronize()
             t0 = time.perf_counter()
             for _ in range(steps):
-                ctx.layer_forward(io)
+                step()
             torch.cuda.synchronize()
             ms[name] = (time.perf_counter() - t0) * 1e3 / steps
         rows = int(buf.expert_offsets[-1].item())
         rows_out.append({"T": T, "rows_on_rank": rows, "ms_bf16": round(ms["bf16"], 5), "ms_fp4": round(ms["fp4"], 5),
-                         "ms_fp4_encode_after_decision": round(ms["fp4_side"], 5),
+                         "ms_fp4_encode_after_decision": round(ms["fp4_after"], 5),
                          "fp4_speedup": round(ms["bf16"] / ms["fp4"], 3),
-                         "fp4_speedup_encode_after_decision": round(ms["bf16"] / ms["fp4_side"], 3)})
-    gamma_side = None
+                         "fp4_speedup_encode_after_decision": round(ms["bf16"] / ms["fp4_after"], 3)})
+    gamma_after = None
     for r in reversed(rows_out):                      # smallest T from which FP4 stays faster
         if r["fp4_speedup"] > 1.0:
             gamma = r["T"]
@@ -435,7 +449,7 @@ def run_gate_sweep(args):
             break
     for r in reversed(rows_out):
         if r["fp4_speedup_encode_after_decision"] > 1.0:
-            gamma_side = r["T"]
+            gamma_after = r["T"]
         else:
             break
     result = {"metric": "LB gate on MI355X: smallest batch size T from which the FP4 layer (weight encoding included) stays faster than BF16",
@@ -443,7 +457,7 @@ def run_gate_sweep(args):
               "higher_is_better": False, "scaling": "weak", "vs_baseline": None, "dtype": "bf16 vs fp4", "data": "synthetic",
               "config": {"workload": f"gate-sweep on the {args.shape} layer shape ({cfg.E} experts top-{cfg.k}, {cfg.n_local} local, "
                                      f"H={cfg.H} I={cfg.I}), hot rank, prefixes of one seeded 65536-token batch"},
-              "extra": {"gate_with_encoding_after_the_decision": gamma_side, "sweep": rows_out, "paper_context": "paper: Gamma = 2048 tokens (256 per rank x 8 ranks) on RTX 5090"}}
+              "extra": {"gate_with_encoding_after_the_decision": gamma_after, "sweep": rows_out, "paper_context": "paper: Gamma = 2048 tokens (256 per rank x 8 ranks) on RTX 5090"}}
     if args.detail:
         with open(args.detail, "w") as f:
             json.dump({"result": result}, f, indent=1)
@@ -636,7 +650,7 @@ def main():
     cfg = W.CONFIGS[args.workload]
     fp4 = args.precision == "fp4"
     lr = LayerRun(args.workload, args, torch, W, R, default_config)
-    mode = args.encode_mode if fp4 else "main"
+    mode = args.encode_mode if fp4 else "speculative"
 
     # ---- warm-up: the driver's W steps, then a fixed, declared pre-roll (the clocks need about 100 ms of load to settle)
     step = lr.stepper(fp4, mode)
@@ -718,6 +732,8 @@ def main():
     if os.path.exists(traffic_file):
         with open(traffic_file) as f:
             roofline["traffic"] = json.load(f).get(f"{args.workload}_{args.precision}:{kernel}")
+    if roofline["traffic"] is None:
+        roofline["traffic_note"] = f"no counter run of {args.workload}_{args.precision}:{kernel} in profiles/traffic.json"
     if args.calibrate_copy:
         src = torch.ones(128 << 20, dtype=torch.int32, device="cuda")
         dst = torch.empty_like(src)
@@ -745,11 +761,11 @@ def main():
         extra["reserve_cus"] = lr.reserve
     # ---- the other half of the metric ("BF16 vs FP4") and the Qwen-shaped layer, briefly, in the same run
     if not args.no_compare and args.workload == "c2":
-        other = lr.brief(not fp4, "main" if fp4 else args.encode_mode)
+        other = lr.brief(not fp4, "speculative" if fp4 else args.encode_mode)
         extra["same_layer_" + ("bf16" if fp4 else "fp4")] = other
         extra["fp4_speedup_over_bf16"] = (other["layer_ms"] / ms_step) if fp4 else (ms_step / other["layer_ms"])
         lr3 = LayerRun("c3", args, torch, W, R, default_config)
-        extra["c3"] = {"fp4": lr3.brief(True, args.encode_mode), "bf16": lr3.brief(False, "main")}
+        extra["c3"] = {"fp4": lr3.brief(True, args.encode_mode), "bf16": lr3.brief(False, "speculative")}
         extra["c3"]["fp4_speedup_over_bf16"] = extra["c3"]["bf16"]["layer_ms"] / extra["c3"]["fp4"]["layer_ms"]
         lr3.close()
     result = {
@@ -759,8 +775,8 @@ def main():
         "dtype": "fp4 (MXFP4 E2M1 + E8M0/32, fp32 accumulate)" if fp4 else "bf16",
         "data": "synthetic",
         "config": {"workload": f"{args.workload}: {cfg.E} experts top-{cfg.k}, {cfg.n_local} local, H={H} I={I}, "
-                               f"T={T} tokens, {int(cfg.vision_frac * 100)}% vision, precision {args.precision} forced, "
-                               f"weight encoding mode {mode}"},
+                               f"T={T} tokens, {int(cfg.vision_frac * 100)}% vision, precision {args.precision} forced"
+                               + (f", weight encoding mode {mode}" if fp4 else "")},
         "roofline": roofline,
         "extra": extra,
     }
