@@ -148,7 +148,7 @@ int realb_select_precision_host(const realb_config* cfg, const int32_t* rank_loa
  * MXFP4, blocks of 32 along the contraction dimension.  Weights are only read.
  *   w13  bf16 [n_local, 2I, H]  rows [0,I) gate, [I,2I) up     -> w13_q u8 [n_local,2I,H/2], w13_s u8 [n_local,2I,H/32]
  *   w2   bf16 [n_local, H, I]                                   -> w2_q  u8 [n_local,H,I/2],  w2_s  u8 [n_local,H,I/32]
- * Meant to be issued on a side stream so that it overlaps realb_permute. */
+ * For callers that place the encoding themselves: the layer and rank calls encode in their own launches (see overlap). */
 int realb_quantize_experts_fp4(realb_ctx* ctx, const void* w13, const void* w2, int n_local,
                                uint8_t* w13_q, uint8_t* w13_s, uint8_t* w2_q, uint8_t* w2_s, void* stream);
 

@@ -314,9 +314,11 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 //     step's transfers (s_waitcnt vmcnt(n), n > 0), leaving those of the step behind it in flight;
 //   - 64 x 128 and (BF16) 64 x 64 tiles double the number of blocks once or twice and have six or nine stages (five or
 //     eight steps in flight); four or two waves multiply, eight move data.
-// Measured, BF16, weights from HBM, gate/up + down us: 24 tokens (61 rows) 49.9 + 27.8 -> 19.6 + 11.6 (138 MB: 4.4 TB/s);
-// 192 tokens 50.9 + 28.2 -> 22.5 + 13.2; 1 token 19 + 14 with 64 x 256 tiles -> 13.3 + 10.2; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.  A split of the contraction over the
-// waves of a block with operands straight in registers (no LDS) measured 34 + 18 at 24 tokens and was dropped.
+// Measured, BF16, weights from HBM, gate/up + down us, 256-row tiles -> these: 24 tokens (61 rows) 49.9 + 27.8 -> 19.6 + 11.6;
+// 192 tokens 50.9 + 28.2 -> 22.5 + 13.2; 1 token 19 + 14 with 64 x 256 tiles -> 13.3 + 10.2; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.
+// With four sets of weights in turn, under the profiler: 1 token 14.0 + 10.1, 24 tokens 23.9 + 12.3 (170 MB read, 4.7 TB/s),
+// 1000 tokens 38.3 + 26.1.  A split of the contraction over the waves of a block with operands straight in registers (no LDS)
+// measured 34 + 18 at 24 tokens and was dropped.
 // The accumulation order along K is the same for every shape and that of the other kernel, so results are bit-identical: a
 // row's result does not depend on the batch it is in.
 constexpr int KB = 128;                    // bytes of each operand row per K-step

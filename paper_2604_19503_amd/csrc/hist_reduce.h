@@ -1,5 +1,5 @@
 // Reduction of the routing kernel's per-block partial histograms (one block per EP rank), shared by the stand-alone
-// reduce kernel and by the layer call's fused reduce + count launch.
+// reduce kernel and by the layer call's route_finish_kernel.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>

@@ -11,7 +11,7 @@ namespace realb {
 
 constexpr int kIters = kPermChunk / 64;   // 64 assignments per wave iteration
 // Chunks (= waves) per block of the count and rank kernels: kPermGroup (4) for long batches, 16 for short ones.  These
-// latency-bound kernels run beside the HBM-bound encoders of the side stream.  Measured, whole layer steps: with more than
+// latency-bound kernels run beside HBM-bound encoders.  Measured with those on a side stream, whole layer steps: with more than
 // about 500 chunks (32k and 64k tokens) 4-wave blocks are 1 % faster -- a small block finds room on a busy CU sooner --,
 // with fewer (16k tokens: 384 chunks, 24 blocks of 16 waves) the large blocks are, by as much in the prefetched form of
 // the call.  The workspace is sized for the small groups.

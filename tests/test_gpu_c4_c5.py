@@ -134,7 +134,7 @@ def test_config5_three_weight_sets_and_pre_encoded_call():
     sample = np.unique(np.concatenate([np.array(edge, dtype=np.int64), rng.integers(0, Rr, 4096 - len(edge))]))
     seg_of = np.searchsorted(off, sample, side="right") - 1
     for layer in (0, 23, 47):
-        _say(f"c5: layer {layer}: weights, layer_forward (encoder on the side stream)")
+        _say(f"c5: layer {layer}: weights, layer_forward")
         w13b, w2b = W.gen_weights(cfg, layer)
         w13, w2 = R.bf16_from_bits(w13b), R.bf16_from_bits(w2b)
         buf.y_rows.fill_(float("nan"))

@@ -479,7 +479,7 @@ def test_layer_forward_matches_step_calls_and_is_deterministic(R, case, force):
     _run_path(R, case, force)
     ref = {n: getattr(b, n).clone() for n in ("out", "y_rows", "topk_ids", "assign_to_row", "expert_offsets")}
     Rr = int(ref["expert_offsets"][-1])
-    for overlap in (True, False, 3, True):          # side stream, main stream, speculative (before routing)
+    for overlap in (True, False, 3, True):          # in the call's launches (1 and 0 are the same), W13 ahead of the decision
         io = case.ctx.make_io(case.logits, case.is_vision, case.x, case.w13, case.w2, b, case.rank, force=force, overlap=overlap)
         b.out.zero_()
         prec = case.ctx.layer_forward(io)
@@ -991,7 +991,7 @@ def test_capacity_and_argument_errors(R, case):
     small.max_rows = 1
     with pytest.raises(R.RealbError):
         case.ctx.permute(case.x, small, 0, R.BF16)
-    # the layer calls refuse bad arguments before anything reaches the side stream, in every encoder placement,
+    # the layer calls refuse bad arguments before anything is enqueued, in every encoder placement,
     # and the context stays usable
     for overlap in (3, 1, 0):
         io = case.ctx.make_io(case.logits, case.is_vision, case.x, case.w13, case.w2, b, case.rank, force=R.FP4, overlap=overlap)
