@@ -551,6 +551,38 @@ def test_layer_call_decides_on_the_device_as_the_host_does(R, shape, T, rank, re
     ctx.close()
 
 
+@pytest.mark.parametrize("aimd,update_first", [(1, 1), (1, 0), (0, 1)])
+def test_device_decision_under_the_other_threshold_rules(R, aimd, update_first):
+    """The M that the device decides with -- updated before the decision, after it, or never -- where that makes the
+    difference: the hot rank's vision share lies between M / 2 and M of a congested layer, so only the first rule takes FP4."""
+    from paper_2604_19503_amd.binding import default_config
+    cfg = W.scaled(W.CONFIGS["c2"], T=2049, H=256, I=128)
+    rcfg = default_config(cfg.T, cfg.E, cfg.k, cfg.D, cfg.H, cfg.I)
+    rcfg.aimd_enabled, rcfg.update_first = aimd, update_first
+    ctx = R.Context(rcfg)
+    inp = W.gen_layer(cfg, 51)
+    x, w13, w2 = (R.bf16_from_bits(inp[n]) for n in ("x", "w13", "w2"))
+    lg = torch.from_numpy(inp["logits"]).cuda(); isv = torch.from_numpy(inp["is_vision"]).cuda()
+    ids, _ = orouter.topk_route(inp["logits"], cfg.k)
+    _, _, load, vis = orouter.route_counts(ids, inp["is_vision"], cfg.E, cfg.D)
+    M = float(1.05 * vis[0] / load[0])
+    want = opol.select_precision(load, vis, cfg.T, cfg.k, M, opol.PolicyConfig(aimd_enabled=bool(aimd), update_first=bool(update_first)))
+    assert want[0][0] == (1 if aimd and update_first else 0)
+    b = R.LayerBuffers(rcfg, cfg.T)
+    _say(f"device decision, aimd={aimd} update_first={update_first}")
+    ctx.M = M
+    io = ctx.make_io(lg, isv, x, w13, w2, b, 0)
+    prec = ctx.layer_forward(io)
+    _sync()
+    assert list(io.prec_host[:cfg.D]) == list(want[0]) and io.M_after == want[2] == ctx.M
+    got = b.out.clone()
+    b.out.fill_(float("nan"))
+    ctx.layer_forward(ctx.make_io(lg, isv, x, w13, w2, b, 0, force=prec))
+    _sync()
+    assert torch.equal(got.view(torch.int16), b.out.view(torch.int16))
+    ctx.close()
+
+
 @pytest.mark.parametrize("T", [1, 5, 63, 257, 1000])
 def test_fused_gather_layer_equals_step_calls_for_odd_batch_sizes(R, T):
     """realb_layer_forward fuses the permutation's gather into the gate/up GEMM (rows fetched through
