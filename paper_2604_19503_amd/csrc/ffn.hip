@@ -156,8 +156,12 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
     int sa_off[4], sb_off[WN];
     uint32_t sa_nx[4], sb_nx[WN];                         // scale words of the next K-step
     TileInfo ti = decode_tile(p, tile, COLS);
+    const KStart kstart = k_start<FP4, GATEUP>((nks + 1) >> 1);
+    int kp = 0;                                           // the K-step (64 bytes) that the next loads fetch
+    auto next_k = [&]() { kp = kp + 1 == nks ? 0 : kp + 1; };
 
     auto prefetch_tile = [&](const TileInfo& t) {
+        kp = 2 * kstart.of(t.e, t.n0);
 #pragma unroll
         for (int j = 0; j < G::JA; ++j) {
             const int gr = min(t.row0 + (tid >> 2) + (NT / 4) * j, t.seg_hi - 1);
@@ -169,23 +173,24 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
             b_src[j] = p.W + ((size_t)t.e * p.w_rows + w_tile_row<GATEUP, G::GC>(br, t.n0, I_up)) * rowbytes + part * 16;
         }
 #pragma unroll
-        for (int j = 0; j < G::JA; ++j) ga[j] = *reinterpret_cast<const u32x4_t*>(a_src[j]);
+        for (int j = 0; j < G::JA; ++j) ga[j] = *reinterpret_cast<const u32x4_t*>(a_src[j] + (size_t)kp * KSTEP_BYTES);
 #pragma unroll
-        for (int j = 0; j < G::JB; ++j) gb[j] = *reinterpret_cast<const u32x4_t*>(b_src[j]);
+        for (int j = 0; j < G::JB; ++j) gb[j] = *reinterpret_cast<const u32x4_t*>(b_src[j] + (size_t)kp * KSTEP_BYTES);
         if constexpr (FP4) {
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) {
                 const int row = min(t.row0 + wm * 128 + mt * 32 + li, t.seg_hi - 1);
                 sa_off[mt] = ((row >> 5) * kd) * 32 + (row & 31);
-                sa_nx[mt] = As32[sa_off[mt]];
+                sa_nx[mt] = As32[sa_off[mt] + kp * 32];
             }
 #pragma unroll
             for (int c = 0; c < WN; ++c) {
                 const int wrow = t.e * p.w_rows + w_tile_row<GATEUP, G::GC>(b_rows[c] + w_row_of_lane(li), t.n0, I_up);
                 sb_off[c] = ((wrow >> 5) * kd) * 32 + (wrow & 31);
-                sb_nx[c] = Ws32[sb_off[c]];
+                sb_nx[c] = Ws32[sb_off[c] + kp * 32];
             }
         }
+        next_k();
     };
     prefetch_tile(ti);
 
@@ -197,9 +202,9 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
         for (int j = 0; j < G::JB; ++j) *reinterpret_cast<u32x4_t*>(smem + b_dst[j]) = gb[j];
         if (nks > 1) {
 #pragma unroll
-            for (int j = 0; j < G::JA; ++j) ga[j] = *reinterpret_cast<const u32x4_t*>(a_src[j] + KSTEP_BYTES);
+            for (int j = 0; j < G::JA; ++j) ga[j] = *reinterpret_cast<const u32x4_t*>(a_src[j] + (size_t)kp * KSTEP_BYTES);
 #pragma unroll
-            for (int j = 0; j < G::JB; ++j) gb[j] = *reinterpret_cast<const u32x4_t*>(b_src[j] + KSTEP_BYTES);
+            for (int j = 0; j < G::JB; ++j) gb[j] = *reinterpret_cast<const u32x4_t*>(b_src[j] + (size_t)kp * KSTEP_BYTES);
         }
         __syncthreads();
 
@@ -225,11 +230,12 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
                 for (int t = 0; t < WN; ++t) sb[t] = (int)(sb_nx[t] >> sshift);
                 if (ks + 1 < nks) {
 #pragma unroll
-                    for (int mt = 0; mt < 4; ++mt) sa_nx[mt] = As32[sa_off[mt] + (ks + 1) * 32];
+                    for (int mt = 0; mt < 4; ++mt) sa_nx[mt] = As32[sa_off[mt] + kp * 32];
 #pragma unroll
-                    for (int t = 0; t < WN; ++t) sb_nx[t] = Ws32[sb_off[t] + (ks + 1) * 32];
+                    for (int t = 0; t < WN; ++t) sb_nx[t] = Ws32[sb_off[t] + kp * 32];
                 }
             }
+            next_k();
             u32x4_t fa0[4], fb0[WN], fa1[4], fb1[WN];
 #pragma unroll
             for (int mt = 0; mt < 4; ++mt) fa0[mt] = *reinterpret_cast<const u32x4_t*>(st + a_frag + mt * 512);
@@ -258,9 +264,9 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
             __builtin_amdgcn_sched_barrier(0);
             if (ks + 2 < nks) {
 #pragma unroll
-                for (int j = 0; j < G::JA; ++j) ga[j] = *reinterpret_cast<const u32x4_t*>(a_src[j] + (size_t)(ks + 2) * KSTEP_BYTES);
+                for (int j = 0; j < G::JA; ++j) ga[j] = *reinterpret_cast<const u32x4_t*>(a_src[j] + (size_t)kp * KSTEP_BYTES);
 #pragma unroll
-                for (int j = 0; j < G::JB; ++j) gb[j] = *reinterpret_cast<const u32x4_t*>(b_src[j] + (size_t)(ks + 2) * KSTEP_BYTES);
+                for (int j = 0; j < G::JB; ++j) gb[j] = *reinterpret_cast<const u32x4_t*>(b_src[j] + (size_t)kp * KSTEP_BYTES);
             }
             __syncthreads();
         }
@@ -498,14 +504,18 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
     // ---- producer position: the K-step it fetches next (pk of tile ptile).  Past the block's last tile
     //      it keeps refetching that tile's steps, which nobody reads.
-    int ptile = tile, pk = 0;
+    const KStart kstart = k_start<FP4, GATEUP>(nks);
+    int ptile = tile, pn = 0, pk = kstart.of(ti.e, ti.n0);      // pn: K-steps of the tile issued before this one
     auto advance = [&]() __attribute__((always_inline)) {
-        if (++pk == nks) {
-            pk = 0;
+        pk = pk + 1 == nks ? 0 : pk + 1;
+        if (++pn == nks) {
+            pn = 0;
             if (ptile + nslots < tile_hi) {
                 ptile += nslots;
                 if constexpr (GATHER) tokbuf ^= 1;                     // fetched while the previous tile was being produced
-                setup_src(decode(ptile));
+                const TileInfo next = decode(ptile);
+                setup_src(next);
+                pk = kstart.of(next.e, next.n0);
                 if constexpr (GATHER) {
                     if (ptile + nslots < tile_hi) fetch_tokens(decode(ptile + nslots), tokbuf ^ 1);
                 }
@@ -552,7 +562,8 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     //   - the producer starts on the step AFTER the next one: its activation rows go out between the
     //     MFMAs of the fourth slice, its weight rows and scales between those of the next step's first
     //     slice, so every transfer has a whole step to land before the barrier that publishes it.
-    int stg = 0, left = G::NS - 1, ks = 0;                // stage of the current step, stage of the step before it
+    int stg = 0, left = G::NS - 1;                        // stage of the current step, stage of the step before it
+    int ks = 0, ck = kstart.of(ti.e, ti.n0);                    // steps of the tile multiplied so far, K-step being multiplied
     v16f_t acc[MT][2];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -578,6 +589,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         ti = decode(tile);
         cur_row0 = ti.row0; cur_rows = ti.seg_hi - ti.row0; cur_n0 = ti.n0;
         ks = 0;
+        ck = kstart.of(ti.e, ti.n0);
         return true;
     };
 
@@ -606,7 +618,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         read_step(0, 0);
         auto step = [&](int set) __attribute__((always_inline)) {
             const bool last = ks == nks - 1;
-            const bool full = !(tail_half && last);
+            const bool full = !(tail_half && ck == nks - 1);
             // the next step has landed, this wave's reads of the current stage are done: its transfers may be replaced
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 2) * OPS) : "memory");
             left = stg;
@@ -635,6 +647,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
                 __builtin_amdgcn_sched_barrier(0);
             }
             ++ks;
+            ck = ck + 1 == nks ? 0 : ck + 1;
             return !last || finish_tile();
         };
         while (step(0) && step(1)) {}
@@ -696,7 +709,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
     while (true) {
         const bool last = ks == nks - 1;
-        const bool full = !(tail_half && last);                    // all four K-slices present
+        const bool full = !(tail_half && ck == nks - 1);           // all four K-slices present
         const uint8_t* st = smem + stg * G::STAGE;
 
         // MFMAs of slice s out of fragment slot s&1.  PRODUCE 1: after each row tile's MFMAs one weight
@@ -749,6 +762,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         take_scales();
 
         ++ks;
+        ck = ck + 1 == nks ? 0 : ck + 1;
         if (last && !finish_tile()) break;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no transfer may still be writing this block's LDS when it ends
