@@ -13,6 +13,7 @@ constexpr int kPermChunk = 256;    // assignments ranked by one wave in permute
 // Smallest group of chunks that one block of the permutation's count and rank kernels handles (the workspace holds one
 // per-expert sum per group).
 constexpr int kPermGroup = 4;
+constexpr int kPermThreads = 64 * kPermGroup;      // block size of those kernels
 constexpr int kTopkThreads = 1024;     // block size of the routing kernel
 constexpr int kRouteBlocksMax = 512;   // most blocks the routing kernel is launched with (two per CU on 256 CUs)
 
@@ -60,7 +61,6 @@ PrecisionSource precision_source(const Ctx* c, int T, int force, int rank, const
 int launch_layer_gate_up(Ctx* c, const PrecisionSource& prec, const realb_layer_io* io, bool announce, hipStream_t s);
 int launch_layer_down(Ctx* c, const PrecisionSource& prec, const realb_layer_io* io, hipStream_t s);
 int next_stats_seq(Ctx* c);      // sequence number of the next set of statistics words
-int perm_block_threads(int T, int k);
 // Waits until the gate/up GEMM that was launched with start_seq has started.
 int wait_for_gemm_start(Ctx* c, hipStream_t s);
 int permute_indices(Ctx* c, const int32_t* topk_ids, int T, int rank, long long max_rows, int32_t* expert_offsets,
@@ -107,6 +107,21 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
     return v;
 }
 __device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_inclusive_scan(v), 63); }
+
+// 64 assignments, a lane each; v: the assignment's local expert, anything outside [0, n_local) if it has none.  own: the lanes
+// whose expert is this lane's (if this lane has one); of_lane: the lanes whose expert has this lane's number (lanes below
+// n_local).  A ballot per bit of the expert's number instead of one per expert: 3 to 6 instead of 8 to 64.
+struct SameExpert { unsigned long long own, of_lane; };
+__device__ __forceinline__ SameExpert same_expert(int v, int n_local, int lane) {
+    const unsigned long long any = __ballot((unsigned)v < (unsigned)n_local);
+    SameExpert s{any, any};
+    for (int b = 0; (1 << b) < n_local; ++b) {
+        const unsigned long long set = __ballot((v >> b) & 1);
+        s.own &= (v >> b) & 1 ? set : ~set;
+        s.of_lane &= (lane >> b) & 1 ? set : ~set;
+    }
+    return s;
+}
 
 inline hipStream_t as_stream(void* s) { return reinterpret_cast<hipStream_t>(s); }
 inline int ceil_div(long long a, long long b) { return (int)((a + b - 1) / b); }

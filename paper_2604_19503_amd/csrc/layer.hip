@@ -154,17 +154,17 @@ static int rank_forward_steps(realb_ctx* ctx, realb_layer_io* io, int prec, void
         if (rc != REALB_OK) return rc;
     }
     // FP4: the encoding rides along with the index kernels -- W13 beside the counting, tokens and W2 beside the ranking
-    const int threads = indices_done ? kSideThreads : perm_block_threads(io->T, c->cfg.k);
+    static_assert(kPermThreads == kSideThreads, "the side jobs of either launch");
     PrecisionSource known{};
     known.fixed = prec;
     SideJobs first{}, second{};
     first.when = second.when = known;
     if (encode_weights) {
-        rc = add_w13(c, io, threads, &first);
-        if (rc == REALB_OK) rc = add_w2(c, io, threads, &second);
+        rc = add_w13(c, io, kSideThreads, &first);
+        if (rc == REALB_OK) rc = add_w2(c, io, kSideThreads, &second);
         if (rc != REALB_OK) return rc;
     }
-    if (fp4 && gather) add_tokens(c, io, threads, &second);
+    if (fp4 && gather) add_tokens(c, io, kSideThreads, &second);
     if (!indices_done) {
         stage_mark(c, s, 0);
         stage_mark(c, s, 1);

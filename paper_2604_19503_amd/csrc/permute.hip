@@ -5,18 +5,14 @@
 // "Overhead-Aware Pipeline Orchestration"); the weight encoder overlaps it.
 #include "encode_device.h"
 #include "hist_reduce.h"
-#include <type_traits>
 
 namespace realb {
 
 constexpr int kIters = kPermChunk / 64;   // 64 assignments per wave iteration
-// Chunks (= waves) per block of the count and rank kernels: kPermGroup (4) for long batches, 16 for short ones.  These
-// latency-bound kernels run beside HBM-bound encoders.  Measured with those on a side stream, whole layer steps: with more than
-// about 500 chunks (32k and 64k tokens) 4-wave blocks are 1 % faster -- a small block finds room on a busy CU sooner --,
-// with fewer (16k tokens: 384 chunks, 24 blocks of 16 waves) the large blocks are, by as much in the prefetched form of
-// the call.  The workspace is sized for the small groups.
-constexpr int kGroupLong = kPermGroup, kGroupShort = 16;
-static int perm_group(int n_chunks) { return n_chunks > 512 ? kGroupLong : kGroupShort; }
+// Chunks (= waves) per block of the count and rank kernels.  They are bound by latency, and a wave's chain of instructions
+// takes the longer the more waves share its SIMD: blocks of 4 waves, one per SIMD.  8192 tokens, 65 536 assignments, 16 local
+// experts: ranking 10.4 us with blocks of 16 waves, 7.5 us with 4; with a ballot per bit of the expert's number (same_expert)
+// 6.0 us; counting 6.6 -> 4.1 us.
 
 // The local expert (or -1) of each of the 4 x 64 assignments a = t*k + j of a wave's chunk.
 __device__ __forceinline__ void load_chunk(int (&le)[kIters], const int32_t* __restrict__ topk_ids, int chunk, int n_chunks, int A,
@@ -28,16 +24,15 @@ __device__ __forceinline__ void load_chunk(int (&le)[kIters], const int32_t* __r
     }
 }
 
-// Phase 1 (a block = one group of G chunks, one wave per chunk): each wave counts, per local expert, the
+// Phase 1 (a block = one group of kPermGroup chunks, one wave per chunk): each wave counts, per local expert, the
 // assignments of its chunk of kPermChunk consecutive flat indices (lane e holds expert e's count); the block adds
 // them up per expert.  wave_cnt is expert-major [n_local, n_chunks], group_cnt [n_local, n_groups].
 // gsum: 64 ints of LDS.
-template <int G>
 __device__ __forceinline__ void perm_count_body(int* gsum, int group, const int32_t* __restrict__ topk_ids, int A, int lo, int n_local,
                                                 int n_chunks, int n_groups, int32_t* __restrict__ wave_cnt,
                                                 int32_t* __restrict__ group_cnt) {
     const int lane = threadIdx.x & 63;
-    const int chunk = group * G + (threadIdx.x >> 6);
+    const int chunk = group * kPermGroup + (threadIdx.x >> 6);
     int le[kIters];
     load_chunk(le, topk_ids, chunk, n_chunks, A, lo, lane);
     if (threadIdx.x < 64) gsum[threadIdx.x] = 0;
@@ -45,10 +40,7 @@ __device__ __forceinline__ void perm_count_body(int* gsum, int group, const int3
     int cnt = 0;
 #pragma unroll
     for (int i = 0; i < kIters; ++i)
-        for (int e = 0; e < n_local; ++e) {
-            const unsigned long long m = __ballot(le[i] == e);
-            if (lane == e) cnt += __popcll(m);
-        }
+        cnt += __popcll(same_expert(le[i], n_local, lane).of_lane);
     if (chunk < n_chunks && lane < n_local) {
         wave_cnt[(size_t)lane * n_chunks + chunk] = cnt;
         atomicAdd(&gsum[lane], cnt);
@@ -57,13 +49,12 @@ __device__ __forceinline__ void perm_count_body(int* gsum, int group, const int3
     if ((int)threadIdx.x < n_local) group_cnt[(size_t)threadIdx.x * n_groups + group] = gsum[threadIdx.x];
 }
 
-template <int G>
-__global__ void __launch_bounds__(64 * G) perm_count_kernel(const int32_t* __restrict__ topk_ids, int A, int lo, int n_local,
+__global__ void __launch_bounds__(kPermThreads) perm_count_kernel(const int32_t* __restrict__ topk_ids, int A, int lo, int n_local,
                                                             int n_chunks, int n_groups, int32_t* __restrict__ wave_cnt,
                                                             int32_t* __restrict__ group_cnt, const SideJobs jobs) {
     __shared__ int gsum[64];
-    if ((int)blockIdx.x >= n_groups) return run_side_jobs<64 * G>(jobs, blockIdx.x - n_groups);
-    perm_count_body<G>(gsum, blockIdx.x, topk_ids, A, lo, n_local, n_chunks, n_groups, wave_cnt, group_cnt);
+    if ((int)blockIdx.x >= n_groups) return run_side_jobs<kPermThreads>(jobs, blockIdx.x - n_groups);
+    perm_count_body(gsum, blockIdx.x, topk_ids, A, lo, n_local, n_chunks, n_groups, wave_cnt, group_cnt);
 }
 
 // Phase 2 (same blocks): every block first works out, from the group sums, each expert's total (whose exclusive scan
@@ -71,8 +62,7 @@ __global__ void __launch_bounds__(64 * G) perm_count_kernel(const int32_t* __res
 // adds up expert w's column of group_cnt, 64 groups per step -- so no separate scan kernel sits between the two
 // phases.  Then each wave walks its chunk again and gives every local assignment its row:
 // expert_offsets[e] + (assignments of e in earlier groups) + (in earlier chunks of the group) + (rank inside the chunk).
-template <int G>
-__global__ void __launch_bounds__(64 * G) perm_rank_kernel(const int32_t* __restrict__ topk_ids, int A, int lo, int n_local,
+__global__ void __launch_bounds__(kPermThreads) perm_rank_kernel(const int32_t* __restrict__ topk_ids, int A, int lo, int n_local,
                                                                  int n_chunks, int n_groups, const int32_t* __restrict__ wave_cnt,
                                                                  const int32_t* __restrict__ group_cnt,
                                                                  int32_t* __restrict__ expert_offsets,
@@ -81,21 +71,21 @@ __global__ void __launch_bounds__(64 * G) perm_rank_kernel(const int32_t* __rest
     __shared__ int before[64], total[64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int group = blockIdx.x, n_front = max(n_groups, 1);
-    if (group >= n_front) return run_side_jobs<64 * G>(jobs, blockIdx.x - n_front);
-    const int chunk = group * G + wave;
+    if (group >= n_front) return run_side_jobs<kPermThreads>(jobs, blockIdx.x - n_front);
+    const int chunk = group * kPermGroup + wave;
     int le[kIters];
     load_chunk(le, topk_ids, chunk, n_chunks, A, lo, lane);
     // this lane's expert: its assignments in the earlier chunks of this group
     int within = 0;
     if (lane < n_local) {
-        int v[G];
+        int v[kPermGroup];
 #pragma unroll
-        for (int q = 0; q < G; ++q)                          // (q < wave: chunk group*G + q exists whenever this wave's chunk does)
-            v[q] = (q < wave && group * G + q < n_chunks) ? wave_cnt[(size_t)lane * n_chunks + group * G + q] : 0;
+        for (int q = 0; q < kPermGroup; ++q)                          // (q < wave: chunk group*G + q exists whenever this wave's chunk does)
+            v[q] = (q < wave && group * kPermGroup + q < n_chunks) ? wave_cnt[(size_t)lane * n_chunks + group * kPermGroup + q] : 0;
 #pragma unroll
-        for (int q = 0; q < G; ++q) within += v[q];
+        for (int q = 0; q < kPermGroup; ++q) within += v[q];
     }
-    for (int e = wave; e < n_local; e += G) {
+    for (int e = wave; e < n_local; e += kPermGroup) {
         int b = 0, t = 0;
         for (int q = lane; q < n_groups; q += 64) {
             const int v = group_cnt[(size_t)e * n_groups + q];
@@ -119,13 +109,11 @@ __global__ void __launch_bounds__(64 * G) perm_rank_kernel(const int32_t* __rest
 #pragma unroll
     for (int i = 0; i < kIters; ++i) {
         const int a = chunk * kPermChunk + i * 64 + lane;
-        int row = -1;
-        for (int e = 0; e < n_local; ++e) {
-            const unsigned long long m = __ballot(le[i] == e);
-            const int base = __builtin_amdgcn_readlane(running, e);
-            if (le[i] == e) row = base + __popcll(m & lt_mask);
-            if (lane == e) running += __popcll(m);
-        }
+        const SameExpert same = same_expert(le[i], n_local, lane);
+        const bool local = (unsigned)le[i] < (unsigned)n_local;
+        const int base = __shfl(running, local ? le[i] : 0);
+        const int row = local ? base + __popcll(same.own & lt_mask) : -1;
+        running += __popcll(same.of_lane);
         if (a < A) {
             assign_to_row[a] = row;
             if (row >= 0) row_to_assign[row] = a;
@@ -139,7 +127,7 @@ __global__ void __launch_bounds__(64 * G) perm_rank_kernel(const int32_t* __rest
 // D + b ranks the assignments of routing block b (expert_offsets and its own base from the partial histograms of all blocks
 // and of the blocks before it); the blocks behind those run the side jobs, whose precision they evaluate from the per-rank
 // partial counts, since the reduced ones are being written beside them.
-// Bound by latency: two dependent memory round trips and n_local ballots per 64 assignments, twice.
+// Bound by latency: two dependent memory round trips, and a few ballots per 64 assignments, twice.
 constexpr int kFinishThreads = 256, kFinishWaves = kFinishThreads / 64, kFinishRegs = 8;
 struct FinishArgs {
     const int32_t* hist_part;
@@ -208,10 +196,7 @@ __global__ void __launch_bounds__(kFinishThreads) route_finish_kernel(const Fini
 #pragma unroll
             for (int r = 0; r < kFinishRegs; ++r) v = r == i ? le[r] : v;
         } else v = local_expert(i);
-        for (int e = 0; e < n_local; ++e) {
-            const unsigned long long m = __ballot(v == e);
-            if (lane == e) cnt += __popcll(m);
-        }
+        cnt += __popcll(same_expert(v, n_local, lane).of_lane);
     }
     wcnt[wave][lane] = cnt;
     __syncthreads();
@@ -230,13 +215,11 @@ __global__ void __launch_bounds__(kFinishThreads) route_finish_kernel(const Fini
 #pragma unroll
             for (int r = 0; r < kFinishRegs; ++r) v = r == i ? le[r] : v;
         } else v = local_expert(i);
-        int row = -1;
-        for (int e = 0; e < n_local; ++e) {
-            const unsigned long long m = __ballot(v == e);
-            const int base = __builtin_amdgcn_readlane(running, e);
-            if (v == e) row = base + __popcll(m & lt_mask);
-            if (lane == e) running += __popcll(m);
-        }
+        const SameExpert same = same_expert(v, n_local, lane);
+        const bool local = (unsigned)v < (unsigned)n_local;
+        const int base = __shfl(running, local ? v : 0);
+        const int row = local ? base + __popcll(same.own & lt_mask) : -1;
+        running += __popcll(same.of_lane);
         const int q = w_lo + i * 64 + lane;
         if (q < n) {
             p.assign_to_row[a_lo + q] = row;
@@ -329,7 +312,7 @@ using namespace realb;
 
 namespace realb {
 
-int perm_block_threads(int T, int k) { return 64 * perm_group(ceil_div((long long)T * k, kPermChunk)); }
+
 
 static int check_permute(const Ctx* c, const int32_t* topk_ids, int T, int rank, long long max_rows, const int32_t* expert_offsets,
                          const int32_t* row_to_assign, const int32_t* assign_to_row) {
@@ -343,7 +326,7 @@ static int check_permute(const Ctx* c, const int32_t* topk_ids, int T, int rank,
     return REALB_OK;
 }
 
-// The index half of realb_permute (count / rank); the side jobs' blocks have perm_block_threads(T, k) threads.
+// The index half of realb_permute (count / rank); the side jobs' blocks have kPermThreads threads.
 int permute_indices(Ctx* c, const int32_t* topk_ids, int T, int rank, long long max_rows, int32_t* expert_offsets,
                     int32_t* row_to_assign, int32_t* assign_to_row, const SideJobs& beside_count, const SideJobs& beside_rank, hipStream_t s) {
     const int rc = check_permute(c, topk_ids, T, rank, max_rows, expert_offsets, row_to_assign, assign_to_row);
@@ -351,19 +334,13 @@ int permute_indices(Ctx* c, const int32_t* topk_ids, int T, int rank, long long 
     const int n_local = c->n_local, lo = rank * n_local;
     const long long A = (long long)T * c->cfg.k;
     const int n_chunks = ceil_div(A, kPermChunk);
-    const int G = perm_group(n_chunks);
-    const int n_groups = ceil_div(n_chunks, G);
-    auto launch = [&](auto g) {
-        constexpr int GG = decltype(g)::value;
-        if (n_groups + beside_count.blocks() > 0)
-            hipLaunchKernelGGL(perm_count_kernel<GG>, dim3(n_groups + beside_count.blocks()), dim3(64 * GG), 0, s, topk_ids, (int)A, lo, n_local,
-                               n_chunks, n_groups, c->wave_cnt, c->group_cnt, beside_count);
-        hipLaunchKernelGGL(perm_rank_kernel<GG>, dim3((n_groups > 0 ? n_groups : 1) + beside_rank.blocks()), dim3(64 * GG), 0, s, topk_ids,
-                           (int)A, lo, n_local, n_chunks, n_groups, c->wave_cnt, c->group_cnt, expert_offsets, row_to_assign,
-                           assign_to_row, beside_rank);
-    };
-    if (G == kGroupLong) launch(std::integral_constant<int, kGroupLong>{});
-    else launch(std::integral_constant<int, kGroupShort>{});
+    const int n_groups = ceil_div(n_chunks, kPermGroup);
+    if (n_groups + beside_count.blocks() > 0)
+        hipLaunchKernelGGL(perm_count_kernel, dim3(n_groups + beside_count.blocks()), dim3(kPermThreads), 0, s, topk_ids, (int)A, lo, n_local,
+                           n_chunks, n_groups, c->wave_cnt, c->group_cnt, beside_count);
+    hipLaunchKernelGGL(perm_rank_kernel, dim3((n_groups > 0 ? n_groups : 1) + beside_rank.blocks()), dim3(kPermThreads), 0, s, topk_ids,
+                       (int)A, lo, n_local, n_chunks, n_groups, c->wave_cnt, c->group_cnt, expert_offsets, row_to_assign,
+                       assign_to_row, beside_rank);
     REALB_HIP(hipGetLastError());
     return REALB_OK;
 }

@@ -248,13 +248,9 @@ __global__ void __launch_bounds__(1024) route_small_kernel(const RouteSmallArgs 
     const int le = a < A ? ids[a] - p.lo : -1;
     const bool mine = le >= 0 && le < p.n_local;
     const unsigned long long lt_mask = (1ull << lane) - 1ull;
-    int cnt = 0, in_wave = 0;
-    for (int e = 0; e < p.n_local; ++e) {
-        const unsigned long long m = __ballot(le == e);
-        if (lane == e) cnt = __popcll(m);
-        if (le == e) in_wave = __popcll(m & lt_mask);
-    }
-    wcnt[wave][lane] = cnt;
+    const SameExpert same = same_expert(le, p.n_local, lane);
+    const int in_wave = __popcll(same.own & lt_mask);
+    wcnt[wave][lane] = __popcll(same.of_lane);
     __syncthreads();
     const int tot = lane < p.n_local ? hist[p.lo + lane] : 0;
     const int incl = wave_inclusive_scan(tot);
