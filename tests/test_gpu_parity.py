@@ -270,6 +270,39 @@ def test_permute_bit_exact(R, case, prec):
         assert same(R.scales_to_canonical(b.x_s, Rr, c.H), o["xs"])
 
 
+@pytest.mark.parametrize("n_local,D,T", [(1, 3, 1), (2, 1, 64), (3, 5, 65), (5, 3, 257), (16, 8, 999), (33, 2, 300), (64, 1, 40), (64, 8, 1025)])
+def test_row_indices_for_every_number_of_local_experts(R, n_local, D, T):
+    """The rows of an expert are found through one ballot per bit of its number: numbers of local experts on both sides of the
+    powers of two, first and last rank, partly filled waves, against the oracle; by realb_permute and by the layer call."""
+    from paper_2604_19503_amd.binding import default_config
+    from oracle import permute as operm
+    E = n_local * D
+    k, H, I = min(E, 3), 128, 128
+    rcfg = default_config(T, E, k, D, H, I)
+    ctx, b = R.Context(rcfg), R.LayerBuffers(rcfg, T)
+    gen = torch.Generator(device="cuda"); gen.manual_seed(n_local * 100 + T)
+    rnd = lambda *shape: torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    logits = torch.randn((T, E), generator=gen, device="cuda")
+    vis = torch.zeros(T, dtype=torch.uint8, device="cuda")
+    x, w13, w2 = rnd(T, H), rnd(n_local, 2 * I, H), rnd(n_local, H, I)
+    for rank in (0, D - 1):
+        _say(f"row indices n_local={n_local} D={D} T={T} rank={rank}")
+        for layer in (False, True):
+            for t in (b.row_to_assign, b.assign_to_row, b.expert_offsets):
+                t.fill_(-7)
+            if layer:
+                ctx.layer_forward(ctx.make_io(logits, vis, x, w13, w2, b, rank, force=R.BF16))
+            else:
+                ctx.route_stats(logits, vis, b)
+                ctx.permute(x, b, rank, R.BF16)
+            _sync()
+            off, r2a, a2r = operm.permute_indices(b.topk_ids.cpu().numpy()[:T], rank, n_local)
+            assert same(b.expert_offsets.cpu().numpy(), off)
+            assert same(b.row_to_assign.cpu().numpy()[:off[-1]], r2a) and (b.row_to_assign.cpu().numpy()[off[-1]:] == -7).all()
+            assert same(b.assign_to_row.cpu().numpy()[:T * k], a2r)
+    ctx.close()
+
+
 # ---------------------------------------------------------------------------- FFN + combine
 def _run_path(R, case, prec):
     b = case.buf
