@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
     int sa_off[4], sb_off[WN];
     uint32_t sa_nx[4], sb_nx[WN];                         // scale words of the next K-step
     TileInfo ti = decode_tile(p, tile, COLS);
-    const KStart kstart = k_start<FP4, GATEUP>((nks + 1) >> 1);
+    const KStart kstart = k_start<FP4, GATEUP>((uint32_t)rowbytes);
     int kp = 0;                                           // the K-step (64 bytes) that the next loads fetch
     auto next_k = [&]() { kp = kp + 1 == nks ? 0 : kp + 1; };
 
@@ -504,7 +504,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
     // ---- producer position: the K-step it fetches next (pk of tile ptile).  Past the block's last tile
     //      it keeps refetching that tile's steps, which nobody reads.
-    const KStart kstart = k_start<FP4, GATEUP>(nks);
+    const KStart kstart = k_start<FP4, GATEUP>(rowbytes);
     int ptile = tile, pn = 0, pk = kstart.of(ti.e, ti.n0);      // pn: K-steps of the tile issued before this one
     auto advance = [&]() __attribute__((always_inline)) {
         pk = pk + 1 == nks ? 0 : pk + 1;

@@ -91,13 +91,15 @@ __device__ __forceinline__ int w_row_of_lane(int li) { return (((li >> 2) & 1) <
 
 // K-step (128 bytes of every operand row) at which the sum of an output column starts; from there it runs to the row's end and
 // on from the row's front.  Blocks that work side by side start together; with one K order for all of them they would ask for
-// the same part of every row at the same time, and as row pitches are multiples of large powers of two, of few L2 and HBM
+// the same part of every row at the same time, and where row pitches are multiples of large powers of two, of few L2 and HBM
 // channels.  The start depends on the output column (and, BF16, the expert) alone: a row's result does not depend on the batch
 // it is in, nor on the tile shape.  Neighbouring columns start one step apart and no more, because they read the same
 // activation rows, which have to be found in L2 (starts spread over the whole row: BF16 ranks of 9 807 and 36 183 rows 1-3 %
 // slower).  Experts share nothing, so there the starts may lie anywhere (golden-section steps), which helps where every block
-// has one tile.  Kernel times before -> after: FP4 down, 249 000 rows, K = 768 359 -> 297 us; BF16 gate/up of 24 tokens 22.9 ->
-// 20.0 us (22.9 -> 21.5 with starts by column alone), of 192 tokens 27.1 -> 24.2 us; FP4 by expert too: 1 % slower.
+// has one tile and the pitch is a multiple of 1 KB; with other pitches (H = 1152, I = 640: 2304 and 1280 bytes) rows fall on
+// all channels by themselves, and 5003 tokens were 1 % slower so.  FP4, by expert too: 1 % slower.
+// Kernel times before -> after: FP4 down, 249 000 rows, K = 768 359 -> 297 us; BF16 gate/up of 24 tokens 22.9 -> 20.0 us (21.5
+// with starts by column alone), of 192 tokens 27.1 -> 24.2 us.
 struct KStart {
     int nks, shift;                                       // K-steps of a row; output columns per wide tile, log2
     uint32_t by_expert;                                   // share of a row per expert, 0.16 fixed point
@@ -107,7 +109,9 @@ struct KStart {
     }
 };
 template <bool FP4, bool GATEUP>
-__device__ __forceinline__ KStart k_start(int nks) { return KStart{nks, GATEUP ? 7 : 8, FP4 ? 0u : 40503u}; }   // 0.618 * 2^16
+__device__ __forceinline__ KStart k_start(uint32_t rowbytes) {
+    return KStart{(int)((rowbytes + 127) >> 7), GATEUP ? 7 : 8, !FP4 && rowbytes % 1024 == 0 ? 40503u : 0u};      // 0.618 * 2^16
+}
 
 struct TileInfo {
     int e;        // local expert
