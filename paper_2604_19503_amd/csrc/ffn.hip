@@ -322,8 +322,8 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 //     eight steps in flight); four or two waves multiply, eight move data.
 // Measured, BF16, weights from HBM, gate/up + down us, 256-row tiles -> these: 24 tokens (61 rows) 49.9 + 27.8 -> 19.6 + 11.6;
 // 192 tokens 50.9 + 28.2 -> 22.5 + 13.2; 1 token 19 + 14 with 64 x 256 tiles -> 13.3 + 10.2; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.
-// With four sets of weights in turn, under the profiler: 1 token 14.0 + 10.1, 24 tokens 23.9 + 12.3 (170 MB read, 4.7 TB/s),
-// 1000 tokens 38.3 + 26.1.  A split of the contraction over the waves of a block with operands straight in registers (no LDS)
+// With several sets of weights in turn, under the profiler: 24 tokens 19.6 + 12.4 (before the K starts of KStart 22.9 + 12.2),
+// 192 tokens of the Qwen3-VL shape 23.6 + 16.2, 1000 tokens 36.5 + 25.5.  A split of the contraction over the waves of a block with operands straight in registers (no LDS)
 // measured 34 + 18 at 24 tokens and was dropped.
 // The accumulation order along K is the same for every shape and that of the other kernel, so results are bit-identical: a
 // row's result does not depend on the batch it is in.
