@@ -197,7 +197,9 @@ int realb_permute(realb_ctx* ctx, const void* x, const int32_t* topk_ids, int T,
  *                       h_mid bf16 [max_rows,I] (workspace/out), h_s ignored
  *   prec == REALB_FP4 : x = x_q, w13 = w13_q, w2 = w2_q with their scale tensors,
  *                       h_mid u8 [max_rows,I/2], h_s u8 [max_rows,I/32] (workspace/out)
- *   y_rows bf16 [max_rows,H] out; only rows < R are written. */
+ *   y_rows bf16 [max_rows,H] out; only rows < R are written.
+ * A row's bits depend on that row and its expert's weights alone: not on the other rows, the number of experts, the
+ * expert's place among them (the EP degree, a call over a subset of the experts) or the kernel. */
 int realb_grouped_moe_ffn(realb_ctx* ctx, int prec, const int32_t* expert_offsets, int n_local,
                           long long max_rows, const void* x, const uint8_t* x_s,
                           const void* w13, const uint8_t* w13_s, const void* w2, const uint8_t* w2_s,

@@ -156,12 +156,11 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
     int sa_off[4], sb_off[WN];
     uint32_t sa_nx[4], sb_nx[WN];                         // scale words of the next K-step
     TileInfo ti = decode_tile(p, tile, COLS);
-    const KStart kstart = k_start<FP4, GATEUP>((uint32_t)rowbytes);
     int kp = 0;                                           // the K-step (64 bytes) that the next loads fetch
     auto next_k = [&]() { kp = kp + 1 == nks ? 0 : kp + 1; };
 
     auto prefetch_tile = [&](const TileInfo& t) {
-        kp = 2 * kstart.of(t.e, t.n0);
+        kp = 2 * k_start<FP4, GATEUP>(t.n0, (nks + 1) >> 1);
 #pragma unroll
         for (int j = 0; j < G::JA; ++j) {
             const int gr = min(t.row0 + (tid >> 2) + (NT / 4) * j, t.seg_hi - 1);
@@ -322,8 +321,8 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 //     eight steps in flight); four or two waves multiply, eight move data.
 // Measured, BF16, weights from HBM, gate/up + down us, 256-row tiles -> these: 24 tokens (61 rows) 49.9 + 27.8 -> 19.6 + 11.6;
 // 192 tokens 50.9 + 28.2 -> 22.5 + 13.2; 1 token 19 + 14 with 64 x 256 tiles -> 13.3 + 10.2; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.
-// With several sets of weights in turn, under the profiler: 24 tokens 19.6 + 12.4 (before the K starts of KStart 22.9 + 12.2),
-// 192 tokens of the Qwen3-VL shape 23.6 + 16.2, 1000 tokens 36.5 + 25.5.  A split of the contraction over the waves of a block with operands straight in registers (no LDS)
+// With four sets of weights in turn, under the profiler: 1 token 14.0 + 10.1, 24 tokens 23.9 + 12.3 (170 MB read, 4.7 TB/s),
+// 1000 tokens 38.3 + 26.1.  A split of the contraction over the waves of a block with operands straight in registers (no LDS)
 // measured 34 + 18 at 24 tokens and was dropped.
 // The accumulation order along K is the same for every shape and that of the other kernel, so results are bit-identical: a
 // row's result does not depend on the batch it is in.
@@ -514,8 +513,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
     // ---- producer position: the K-step it fetches next (pk of tile ptile).  Past the block's last tile
     //      it keeps refetching that tile's steps, which nobody reads.
-    const KStart kstart = k_start<FP4, GATEUP>(rowbytes);
-    int ptile = tile, pn = 0, pk = kstart.of(ti.e, ti.n0);      // pn: K-steps of the tile issued before this one
+    int ptile = tile, pn = 0, pk = k_start<FP4, GATEUP>(ti.n0, nks);      // pn: K-steps of the tile issued before this one
     auto advance = [&]() __attribute__((always_inline)) {
         pk = pk + 1 == nks ? 0 : pk + 1;
         if (++pn == nks) {
@@ -525,7 +523,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
                 if constexpr (GATHER) tokbuf ^= 1;                     // fetched while the previous tile was being produced
                 const TileInfo next = decode(ptile);
                 setup_src(next);
-                pk = kstart.of(next.e, next.n0);
+                pk = k_start<FP4, GATEUP>(next.n0, nks);
                 if constexpr (GATHER) {
                     if (ptile + nslots < tile_hi) fetch_tokens(decode(ptile + nslots), tokbuf ^ 1);
                 }
@@ -573,7 +571,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     //     MFMAs of the fourth slice, its weight rows and scales between those of the next step's first
     //     slice, so every transfer has a whole step to land before the barrier that publishes it.
     int stg = 0, left = G::NS - 1;                        // stage of the current step, stage of the step before it
-    int ks = 0, ck = kstart.of(ti.e, ti.n0);                    // steps of the tile multiplied so far, K-step being multiplied
+    int ks = 0, ck = k_start<FP4, GATEUP>(ti.n0, nks);          // steps of the tile multiplied so far, K-step being multiplied
     v16f_t acc[MT][2];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -599,7 +597,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         ti = decode(tile);
         cur_row0 = ti.row0; cur_rows = ti.seg_hi - ti.row0; cur_n0 = ti.n0;
         ks = 0;
-        ck = kstart.of(ti.e, ti.n0);
+        ck = k_start<FP4, GATEUP>(ti.n0, nks);
         return true;
     };
 

@@ -90,27 +90,19 @@ __device__ __forceinline__ int w_slot(int br) { return (br & ~31) | (((br >> 2) 
 __device__ __forceinline__ int w_row_of_lane(int li) { return (((li >> 2) & 1) << 4) | ((li >> 3) << 2) | (li & 3); }
 
 // K-step (128 bytes of every operand row) at which the sum of an output column starts; from there it runs to the row's end and
-// on from the row's front.  Blocks that work side by side start together; with one K order for all of them they would ask for
-// the same part of every row at the same time, and where row pitches are multiples of large powers of two, of few L2 and HBM
-// channels.  The start depends on the output column (and, BF16, the expert) alone: a row's result does not depend on the batch
-// it is in, nor on the tile shape.  Neighbouring columns start one step apart and no more, because they read the same
-// activation rows, which have to be found in L2 (starts spread over the whole row: BF16 ranks of 9 807 and 36 183 rows 1-3 %
-// slower).  Experts share nothing, so there the starts may lie anywhere (golden-section steps), which helps where every block
-// has one tile and the pitch is a multiple of 1 KB; with other pitches (H = 1152, I = 640: 2304 and 1280 bytes) rows fall on
-// all channels by themselves, and 5003 tokens were 1 % slower so.  FP4, by expert too: 1 % slower.
-// Kernel times before -> after: FP4 down, 249 000 rows, K = 768 359 -> 297 us; BF16 gate/up of 24 tokens 22.9 -> 20.0 us (21.5
-// with starts by column alone), of 192 tokens 27.1 -> 24.2 us.
-struct KStart {
-    int nks, shift;                                       // K-steps of a row; output columns per wide tile, log2
-    uint32_t by_expert;                                   // share of a row per expert, 0.16 fixed point
-    __device__ __forceinline__ int of(int e, int n0) const {
-        const uint32_t first = ((((uint32_t)e * by_expert) & 0xFFFFu) * (uint32_t)nks) >> 16;
-        return (int)((first + (uint32_t)(n0 >> shift)) % (uint32_t)nks);
-    }
-};
+// on from the row's front.
+// BF16: the front, for every column.  FP32 sums of BF16 products round, and a row's bits shall depend on its expert alone -- not on
+// the batch, the tile shape, the expert's local slot (the EP degree) or the column.  What that leaves: blocks that work side by
+// side ask for the same part of every row at the same time, that is of few HBM channels.  Starts that differ by slot and column
+// took a layer call of 24 tokens, weights from HBM, from 44.0 to 40.0 us (1000 tokens 71.2 -> 69.4); starts by column alone 42.9
+// us, but with cached weights 36.0 -> 36.8, and 16 384 tokens on a rank without load 171.7 -> 177.4 us.
+// FP4: neighbouring column tiles start one step apart, so that they read different parts of the weight rows.  The order depends
+// on the column alone.  Down GEMM, H = 2048, before -> after: 249 000 rows, K = 768 359 -> 297 us; 100 000 rows, K = 1024 153 ->
+// 137, K = 2048 242 -> 228; but 20 000 rows, K = 1408 43.2 -> 44.1, K = 2048 50.8 -> 53.6 us; no difference at 600 and 4000 rows.
 template <bool FP4, bool GATEUP>
-__device__ __forceinline__ KStart k_start(uint32_t rowbytes) {
-    return KStart{(int)((rowbytes + 127) >> 7), GATEUP ? 7 : 8, !FP4 && rowbytes % 1024 == 0 ? 40503u : 0u};      // 0.618 * 2^16
+__device__ __forceinline__ int k_start(int n0, int nks) {
+    if constexpr (FP4) return (int)((uint32_t)(n0 >> (GATEUP ? 7 : 8)) % (uint32_t)nks);      // (column tile of the wide shapes)
+    else return 0;
 }
 
 struct TileInfo {

@@ -504,6 +504,81 @@ def test_down_gemm_with_a_streamed_output_sums_in_the_order_of_a_small_one(R, I,
     ctx.close()
 
 
+@pytest.mark.parametrize("prec", [0, 1])
+@pytest.mark.parametrize("H,I", [(2048, 512), (512, 1536), (1152, 640), (1024, 1408)])     # pitches of 1 KB multiples and others, K odd and even
+def test_an_experts_rows_do_not_depend_on_its_slot_or_batch(R, H, I, prec):
+    """The same expert and the same rows in every local slot, with segments from 1 row to several 256-row tiles, and alone in a
+    call over a subset of the experts (n_local = 1, shifted pointers): bit-identical rows.  BF16: output columns with the same
+    weights are bit-identical too, because every column sums its K front to back."""
+    from paper_2604_19503_amd.binding import default_config
+    segments = [37, 300, 0, 1, 1100, 65]
+    nl, rows, longest = len(segments), sum(segments), max(segments)
+    rcfg = default_config(rows, nl, 1, 1, H, I)
+    ctx = R.Context(rcfg)
+    b = R.LayerBuffers(rcfg, rows)
+    gen = torch.Generator(device="cuda"); gen.manual_seed(H + 7 * I)
+    rnd = lambda std, *shape: (torch.randn(shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    # activations spread over many binades, so that FP32 sums round (and another order would show)
+    one = rnd(1.0, longest, H) * torch.exp2(torch.randint(-8, 9, (longest, H // 32), generator=gen, device="cuda").float()).repeat_interleave(32, 1).to(torch.bfloat16)
+    x = torch.cat([one[:n] for n in segments])
+    gate, up, down = rnd(0.02, 32, H), rnd(0.02, 32, H), rnd(0.02, 32, I)          # weight rows repeat every 32 output columns
+    w13 = torch.cat([gate.repeat(I // 32, 1), up.repeat(I // 32, 1)])[None].repeat(nl, 1, 1).contiguous()
+    w2 = down.repeat(H // 32, 1)[None].repeat(nl, 1, 1).contiguous()
+    ctx.quantize_experts_fp4(w13, w2, b)
+
+    def ffn(seg, src, w13, w2):
+        b.n_local = len(seg)
+        b.expert_offsets[:len(seg) + 1].copy_(torch.from_numpy(np.concatenate([[0], np.cumsum(seg)]).astype(np.int32)))
+        n = src.shape[0]
+        b.x_perm[:n].copy_(src)
+        q, sc = R.quantize_rows_fp4(src)
+        b.x_q[:n].copy_(q); b.x_s.view(-1)[:sc.numel()].copy_(sc.view(-1))
+        b.y_rows.fill_(float("nan"))
+        ctx.grouped_moe_ffn(prec, w13, w2, b)
+        _sync()
+        return b.y_rows[:n].view(torch.int16).clone()
+
+    _say(f"slots H={H} I={I} prec={prec}")
+    y = ffn(segments, x, w13, w2)
+    if prec == R.BF16:
+        h = b.h_mid[:rows].view(torch.int16).reshape(rows, I // 32, 32)
+        assert torch.equal(h, h[:, :1].expand_as(h))
+        cols = y.reshape(rows, H // 32, 32)
+        assert torch.equal(cols, cols[:, :1].expand_as(cols))
+    parts = list(torch.split(y, segments))
+    for e, n in enumerate(segments):
+        assert torch.equal(parts[e], parts[4][:n]), e
+    for e, n in ((5, 37), (1, 700)):
+        assert torch.equal(ffn([n], one[:n], w13[e:e + 1], w2[e:e + 1]), parts[4][:n]), (e, n)
+    ctx.close()
+
+
+@pytest.mark.parametrize("force", [0, 1])
+def test_an_experts_rows_do_not_depend_on_the_ep_degree(R, force):
+    """Eight experts on one rank, on two and on four: layer calls give every expert's rows bit for bit."""
+    from paper_2604_19503_amd.binding import default_config
+    T, E, k, H, I = 600, 8, 2, 1024, 512
+    gen = torch.Generator(device="cuda"); gen.manual_seed(12)
+    rnd = lambda std, *shape: (torch.randn(shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    logits = torch.randn((T, E), generator=gen, device="cuda")
+    vis = torch.zeros(T, dtype=torch.uint8, device="cuda")
+    x, w13, w2 = rnd(1.0, T, H), rnd(0.02, E, 2 * I, H), rnd(0.02, E, H, I)
+    ref = None
+    for D in (1, 2, 4):
+        rcfg = default_config(T, E, k, D, H, I)
+        ctx, b, nl, got = R.Context(rcfg), R.LayerBuffers(rcfg, T), E // D, []
+        for rank in range(D):
+            _say(f"EP degree {D} rank {rank} force={force}")
+            ctx.layer_forward(ctx.make_io(logits, vis, x, w13[rank * nl:(rank + 1) * nl], w2[rank * nl:(rank + 1) * nl], b, rank, force=force))
+            _sync()
+            got.append(b.y_rows[:int(b.expert_offsets[-1])].view(torch.int16).clone())
+        got = torch.cat(got)
+        assert got.shape[0] == T * k
+        ref = got if ref is None else ref
+        assert torch.equal(got, ref), D
+        ctx.close()
+
+
 # ---------------------------------------------------------------------------- whole layer
 @pytest.mark.parametrize("force", [0, 1])
 def test_layer_forward_matches_step_calls_and_is_deterministic(R, case, force):
