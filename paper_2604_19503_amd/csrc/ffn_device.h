@@ -96,12 +96,14 @@ __device__ __forceinline__ int w_row_of_lane(int li) { return (((li >> 2) & 1) <
 // side ask for the same part of every row at the same time, that is of few HBM channels.  Starts that differ by slot and column
 // took a layer call of 24 tokens, weights from HBM, from 44.0 to 40.0 us (1000 tokens 71.2 -> 69.4); starts by column alone 42.9
 // us, but with cached weights 36.0 -> 36.8, and 16 384 tokens on a rank without load 171.7 -> 177.4 us.
-// FP4: neighbouring column tiles start one step apart, so that they read different parts of the weight rows.  The order depends
-// on the column alone.  Down GEMM, H = 2048, before -> after: 249 000 rows, K = 768 359 -> 297 us; 100 000 rows, K = 1024 153 ->
-// 137, K = 2048 242 -> 228; but 20 000 rows, K = 1408 43.2 -> 44.1, K = 2048 50.8 -> 53.6 us; no difference at 600 and 4000 rows.
+// FP4 down: neighbouring column tiles start one step apart, so that they read different parts of the weight rows.  The order
+// depends on the column alone.  H = 2048, before -> after: 249 000 rows, K = 768 359 -> 297 us; 100 000 rows, K = 1024 153 -> 137,
+// K = 2048 242 -> 228; but 20 000 rows, K = 1408 43.2 -> 44.1, K = 2048 50.8 -> 53.6 us; no difference at 600 and 4000 rows.
+// FP4 gate/up: the front; such starts gained nothing from 150 to 36 000 rows and cost up to 3 % (H = 2048, I = 512, 20 000 rows
+// 32.4 -> 33.2 us).
 template <bool FP4, bool GATEUP>
 __device__ __forceinline__ int k_start(int n0, int nks) {
-    if constexpr (FP4) return (int)((uint32_t)(n0 >> (GATEUP ? 7 : 8)) % (uint32_t)nks);      // (column tile of the wide shapes)
+    if constexpr (FP4 && !GATEUP) return (int)((uint32_t)(n0 >> 8) % (uint32_t)nks);      // (256: column tile of the wide shapes)
     else return 0;
 }
 

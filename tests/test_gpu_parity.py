@@ -508,8 +508,8 @@ def test_down_gemm_with_a_streamed_output_sums_in_the_order_of_a_small_one(R, I,
 @pytest.mark.parametrize("H,I", [(2048, 512), (512, 1536), (1152, 640), (1024, 1408)])     # pitches of 1 KB multiples and others, K odd and even
 def test_an_experts_rows_do_not_depend_on_its_slot_or_batch(R, H, I, prec):
     """The same expert and the same rows in every local slot, with segments from 1 row to several 256-row tiles, and alone in a
-    call over a subset of the experts (n_local = 1, shifted pointers): bit-identical rows.  BF16: output columns with the same
-    weights are bit-identical too, because every column sums its K front to back."""
+    call over a subset of the experts (n_local = 1, shifted pointers): bit-identical rows.  Columns of h, and BF16 columns of
+    the output, with the same weights are bit-identical too, because every column sums its K front to back."""
     from paper_2604_19503_amd.binding import default_config
     segments = [37, 300, 0, 1, 1100, 65]
     nl, rows, longest = len(segments), sum(segments), max(segments)
@@ -540,9 +540,9 @@ def test_an_experts_rows_do_not_depend_on_its_slot_or_batch(R, H, I, prec):
 
     _say(f"slots H={H} I={I} prec={prec}")
     y = ffn(segments, x, w13, w2)
+    h = b.h_mid.view(torch.uint8).view(-1)[:rows * (2 * I if prec == R.BF16 else I // 2)].reshape(rows, I // 32, -1)
+    assert torch.equal(h, h[:, :1].expand_as(h))
     if prec == R.BF16:
-        h = b.h_mid[:rows].view(torch.int16).reshape(rows, I // 32, 32)
-        assert torch.equal(h, h[:, :1].expand_as(h))
         cols = y.reshape(rows, H // 32, 32)
         assert torch.equal(cols, cols[:, :1].expand_as(cols))
     parts = list(torch.split(y, segments))
