@@ -10,8 +10,8 @@ namespace realb {
 
 constexpr int kWave = 64;
 constexpr int kPermChunk = 256;    // assignments ranked by one wave in permute
-// Smallest group of chunks that one block of the permutation's count and rank kernels handles (the workspace holds one
-// per-expert sum per group).
+// Chunks that one block of the permutation's count and rank kernels handles, a wave each (the workspace holds one per-expert
+// sum per group).
 constexpr int kPermGroup = 4;
 constexpr int kPermThreads = 64 * kPermGroup;      // block size of those kernels
 constexpr int kTopkThreads = 1024;     // block size of the routing kernel
@@ -110,7 +110,8 @@ __device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlan
 
 // 64 assignments, a lane each; v: the assignment's local expert, anything outside [0, n_local) if it has none.  own: the lanes
 // whose expert is this lane's (if this lane has one); of_lane: the lanes whose expert has this lane's number (lanes below
-// n_local).  A ballot per bit of the expert's number instead of one per expert: 3 to 6 instead of 8 to 64.
+// n_local).  One ballot for the local ones and one per bit of the expert's number: 4 for 8 local experts, 7 for 64, where one
+// per expert would be 8 and 64.
 struct SameExpert { unsigned long long own, of_lane; };
 __device__ __forceinline__ SameExpert same_expert(int v, int n_local, int lane) {
     const unsigned long long any = __ballot((unsigned)v < (unsigned)n_local);

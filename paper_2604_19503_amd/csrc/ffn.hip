@@ -321,8 +321,8 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 //     eight steps in flight); four or two waves multiply, eight move data.
 // Measured, BF16, weights from HBM, gate/up + down us, 256-row tiles -> these: 24 tokens (61 rows) 49.9 + 27.8 -> 19.6 + 11.6;
 // 192 tokens 50.9 + 28.2 -> 22.5 + 13.2; 1 token 19 + 14 with 64 x 256 tiles -> 13.3 + 10.2; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.
-// With four sets of weights in turn, under the profiler: 1 token 14.0 + 10.1, 24 tokens 23.9 + 12.3 (170 MB read, 4.7 TB/s),
-// 1000 tokens 38.3 + 26.1.  A split of the contraction over the waves of a block with operands straight in registers (no LDS)
+// With four sets of weights in turn, under the profiler: 1 token 14.5 + 10.4, 24 tokens 24.3 + 12.5 (170 MB read, 4.6 TB/s),
+// 1000 tokens 38.4 + 26.2.  A split of the contraction over the waves of a block with operands straight in registers (no LDS)
 // measured 34 + 18 at 24 tokens and was dropped.
 // The accumulation order along K is the same for every shape and that of the other kernel, so results are bit-identical: a
 // row's result does not depend on the batch it is in.
@@ -367,9 +367,11 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     const int li = lane & 31, half = lane >> 5;
 
     // Order of an expert's tiles.  An XCD takes a contiguous range of them, and what its blocks share they fetch once: with column
-    // tiles first the activations, with row tiles first the weights.  BF16 tiles of up to 192 rows have more bytes of weights
-    // than of activations, few row tiles per expert, and wait for memory: row tiles first (1000 tokens, gate/up: 190 -> 123 MB
-    // read from behind the L2; layer calls of 1000 / 16 384 tokens of 2169 / 9807 rows 73.2 / 209.0 -> 72.3 / 206.4 us).
+    // tiles first the activations, with row tiles first the weights.  Row tiles first for BF16 tiles of up to 192 rows, of which an
+    // expert has few.  Column tiles first against this, layer calls: 384 tokens 50.8 -> 46.0 us, 200 46.6 -> 44.7 (the 64-column
+    // shapes), 500 tokens of the Qwen3-VL shape 51.6 -> 49.6 with cached weights; with weights from HBM 200 tokens 52.0 -> 50.7, 1000
+    // 71.7 -> 71.0 (gate/up reads 168 -> 120 MB from behind the L2 in the same 38.4 us: the K-step binds it, not memory); 8 to
+    // 100 tokens, 2000 and 5003: within 1 % either way.
     // Column tiles first for 256-row tiles (row tiles first, FP4 down GEMM of 249 000 rows: 304 -> 409 us) and FP4 (0.7 % faster).
     constexpr bool ROWS_FIRST = !FP4 && MT < 4;
     // Expert table in LDS: entry e holds expert e's row segment and the inclusive prefix of row-tile

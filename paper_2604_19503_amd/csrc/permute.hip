@@ -12,7 +12,10 @@ constexpr int kIters = kPermChunk / 64;   // 64 assignments per wave iteration
 // Chunks (= waves) per block of the count and rank kernels.  They are bound by latency, and a wave's chain of instructions
 // takes the longer the more waves share its SIMD: blocks of 4 waves, one per SIMD.  8192 tokens, 65 536 assignments, 16 local
 // experts: ranking 10.4 us with blocks of 16 waves, 7.5 us with 4; with a ballot per bit of the expert's number (same_expert)
-// 6.0 us; counting 6.6 -> 4.1 us.
+// 6.0 us; counting 6.6 -> 4.1 us.  Blocks of 4 against 16 waves, both with those ballots: FP4 rank calls, whose encoders run
+// beside these kernels, 62.5 against 65.7 us (512 tokens, 8 local experts), 109.0 / 111.8 (3001, 16) and 147.9 / 150.2 (8192, 64);
+// realb_permute with 64 local experts, where every wave adds up 16 experts' group counts, 21.1 / 19.7 us at 85 chunks, 24.4 /
+// 24.8 at 256 and 34.4 / 31.3 at 512 -- and 50.4, 56.4 and 63.2 us with 16 waves and a ballot per expert.
 
 // The local expert (or -1) of each of the 4 x 64 assignments a = t*k + j of a wave's chunk.
 __device__ __forceinline__ void load_chunk(int (&le)[kIters], const int32_t* __restrict__ topk_ids, int chunk, int n_chunks, int A,
@@ -80,7 +83,7 @@ __global__ void __launch_bounds__(kPermThreads) perm_rank_kernel(const int32_t* 
     if (lane < n_local) {
         int v[kPermGroup];
 #pragma unroll
-        for (int q = 0; q < kPermGroup; ++q)                          // (q < wave: chunk group*G + q exists whenever this wave's chunk does)
+        for (int q = 0; q < kPermGroup; ++q)                          // (q < wave: that chunk exists whenever this wave's does)
             v[q] = (q < wave && group * kPermGroup + q < n_chunks) ? wave_cnt[(size_t)lane * n_chunks + group * kPermGroup + q] : 0;
 #pragma unroll
         for (int q = 0; q < kPermGroup; ++q) within += v[q];
@@ -311,8 +314,6 @@ static void launch_gather(int blocks, hipStream_t s, const void* x, const int32_
 using namespace realb;
 
 namespace realb {
-
-
 
 static int check_permute(const Ctx* c, const int32_t* topk_ids, int T, int rank, long long max_rows, const int32_t* expert_offsets,
                          const int32_t* row_to_assign, const int32_t* assign_to_row) {
