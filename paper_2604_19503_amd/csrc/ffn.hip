@@ -389,7 +389,9 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         const int lo = __builtin_amdgcn_readfirstlane(tab[64 + e]), hi = __builtin_amdgcn_readfirstlane(tab[128 + e]);
         const int first = e == 0 ? 0 : __builtin_amdgcn_readfirstlane(tab[e - 1]);
         if constexpr (ROWS_FIRST) {
-            const int rows = __builtin_amdgcn_readfirstlane(tab[e]) - first, local = t - first * n_tiles_n, col = local / rows;
+            const int rows = __builtin_amdgcn_readfirstlane(tab[e]) - first, local = t - first * n_tiles_n;
+            int col = local;
+            if (rows > 1) col = local / rows;                 // (decode steps: one row tile per expert, no second division)
             return TileInfo{e, lo + (local - col * rows) * TA, hi, col * COLS};
         }
         return TileInfo{e, lo + (mi - first) * TA, hi, nt * COLS};
@@ -515,17 +517,18 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
     // ---- producer position: the K-step it fetches next (pk of tile ptile).  Past the block's last tile
     //      it keeps refetching that tile's steps, which nobody reads.
+    constexpr bool STARTS = kHasStarts<FP4, GATEUP>;          // (without them the counters pn and ck, which then equal pk and ks, are not kept)
     int ptile = tile, pn = 0, pk = k_start<FP4, GATEUP>(ti.n0, nks);      // pn: K-steps of the tile issued before this one
     auto advance = [&]() __attribute__((always_inline)) {
         pk = pk + 1 == nks ? 0 : pk + 1;
-        if (++pn == nks) {
-            pn = 0;
+        if constexpr (STARTS) pn = pn + 1 == nks ? 0 : pn + 1;
+        if ((STARTS ? pn : pk) == 0) {
             if (ptile + nslots < tile_hi) {
                 ptile += nslots;
                 if constexpr (GATHER) tokbuf ^= 1;                     // fetched while the previous tile was being produced
                 const TileInfo next = decode(ptile);
                 setup_src(next);
-                pk = k_start<FP4, GATEUP>(next.n0, nks);
+                if constexpr (STARTS) pk = k_start<FP4, GATEUP>(next.n0, nks);
                 if constexpr (GATHER) {
                     if (ptile + nslots < tile_hi) fetch_tokens(decode(ptile + nslots), tokbuf ^ 1);
                 }
@@ -599,7 +602,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         ti = decode(tile);
         cur_row0 = ti.row0; cur_rows = ti.seg_hi - ti.row0; cur_n0 = ti.n0;
         ks = 0;
-        ck = k_start<FP4, GATEUP>(ti.n0, nks);
+        if constexpr (STARTS) ck = k_start<FP4, GATEUP>(ti.n0, nks);
         return true;
     };
 
@@ -628,7 +631,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         read_step(0, 0);
         auto step = [&](int set) __attribute__((always_inline)) {
             const bool last = ks == nks - 1;
-            const bool full = !(tail_half && ck == nks - 1);
+            const bool full = !(tail_half && (STARTS ? ck : ks) == nks - 1);
             // the next step has landed, this wave's reads of the current stage are done: its transfers may be replaced
             asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 2) * OPS) : "memory");
             left = stg;
@@ -657,7 +660,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
                 __builtin_amdgcn_sched_barrier(0);
             }
             ++ks;
-            ck = ck + 1 == nks ? 0 : ck + 1;
+            if constexpr (STARTS) ck = ck + 1 == nks ? 0 : ck + 1;
             return !last || finish_tile();
         };
         while (step(0) && step(1)) {}
@@ -719,7 +722,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
     while (true) {
         const bool last = ks == nks - 1;
-        const bool full = !(tail_half && ck == nks - 1);           // all four K-slices present
+        const bool full = !(tail_half && (STARTS ? ck : ks) == nks - 1);           // all four K-slices present
         const uint8_t* st = smem + stg * G::STAGE;
 
         // MFMAs of slice s out of fragment slot s&1.  PRODUCE 1: after each row tile's MFMAs one weight
@@ -772,7 +775,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         take_scales();
 
         ++ks;
-        ck = ck + 1 == nks ? 0 : ck + 1;
+        if constexpr (STARTS) ck = ck + 1 == nks ? 0 : ck + 1;
         if (last && !finish_tile()) break;
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no transfer may still be writing this block's LDS when it ends

@@ -102,8 +102,10 @@ __device__ __forceinline__ int w_row_of_lane(int li) { return (((li >> 2) & 1) <
 // FP4 gate/up: the front; such starts gained nothing from 150 to 36 000 rows and cost up to 3 % (H = 2048, I = 512, 20 000 rows
 // 32.4 -> 33.2 us).
 template <bool FP4, bool GATEUP>
+constexpr bool kHasStarts = FP4 && !GATEUP;
+template <bool FP4, bool GATEUP>
 __device__ __forceinline__ int k_start(int n0, int nks) {
-    if constexpr (FP4 && !GATEUP) return (int)((uint32_t)(n0 >> 8) % (uint32_t)nks);      // (256: column tile of the wide shapes)
+    if constexpr (kHasStarts<FP4, GATEUP>) return (int)((uint32_t)(n0 >> 8) % (uint32_t)nks);      // (256: column tile of the wide shapes)
     else return 0;
 }
 
