@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 //     eight steps in flight); four or two waves multiply, eight move data.
 // Measured, BF16, weights from HBM, gate/up + down us, 256-row tiles -> these: 24 tokens (61 rows) 49.9 + 27.8 -> 19.6 + 11.6;
 // 192 tokens 50.9 + 28.2 -> 22.5 + 13.2; 1 token 19 + 14 with 64 x 256 tiles -> 13.3 + 10.2; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.
-// With four sets of weights in turn, under the profiler: 1 token 14.5 + 10.4, 24 tokens 24.3 + 12.5 (170 MB read, 4.6 TB/s),
+// With four sets of weights in turn, under the profiler: 1 token 14.5 + 10.4, 24 tokens 24.3 + 12.6 (170 MB read, 4.6 TB/s),
 // 1000 tokens 38.4 + 26.2.  A split of the contraction over the waves of a block with operands straight in registers (no LDS)
 // measured 34 + 18 at 24 tokens and was dropped.
 // The accumulation order along K is the same for every shape and that of the other kernel, so results are bit-identical: a
@@ -370,7 +370,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     // tiles first the activations, with row tiles first the weights.  Row tiles first for BF16 tiles of up to 192 rows, of which an
     // expert has few.  Column tiles first against this, layer calls: 384 tokens 50.8 -> 46.0 us, 200 46.6 -> 44.7 (the 64-column
     // shapes), 500 tokens of the Qwen3-VL shape 51.6 -> 49.6 with cached weights; with weights from HBM 200 tokens 52.0 -> 50.7, 1000
-    // 71.7 -> 71.0 (gate/up reads 168 -> 120 MB from behind the L2 in the same 38.4 us: the K-step binds it, not memory); 8 to
+    // 71.7 -> 71.0 (gate/up reads 168 -> 120 MB from behind the L2 in 38.9 -> 38.4 us: the K-step binds it, not memory); 8 to
     // 100 tokens, 2000 and 5003: within 1 % either way.
     // Column tiles first for 256-row tiles (row tiles first, FP4 down GEMM of 249 000 rows: 304 -> 409 us) and FP4 (0.7 % faster).
     constexpr bool ROWS_FIRST = !FP4 && MT < 4;
