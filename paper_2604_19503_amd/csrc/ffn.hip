@@ -1,6 +1,7 @@
 // Stage 4, balanced MoE execution (paper Sec. "System Overview"): the SwiGLU
 // expert FFN of one rank as two grouped GEMMs, in the precision the scheduler
-// picked -- BF16 operands on v_mfma_f32_32x32x16_bf16, or MXFP4 operands (W4A4)
+// picked -- BF16 operands on v_mfma_f32_32x32x16_bf16 (tiles of 192 and more rows:
+// v_mfma_f32_16x16x32_bf16), or MXFP4 operands (W4A4)
 // on the block-scaled v_mfma_scale_f32_32x32x64_f8f6f4.
 //
 // Both precisions share one kernel body because their tiles are byte-identical:
@@ -25,6 +26,7 @@
 // store.  expert_offsets is read on the device, so no host round trip.
 #include "ffn_device.h"
 #include "encode_device.h"
+#include <type_traits>
 
 namespace realb {
 
@@ -350,6 +352,10 @@ struct TileGeo {
     static constexpr int LDS_BYTES = TOK_BASE + 2 * TOK_BUF;
 };
 
+// BF16 tiles of 192 and 256 rows: 16 x 16 MFMA tiles and a K-loop in which the two waves of a SIMD take turns at the matrix cores.
+template <bool FP4, int MT>
+constexpr bool kTurns = !FP4 && MT >= 3;
+
 // All tiles of height TA = 64*MT of the row segments [off_lo, off_hi) (lane e: expert e's).  Every wave of the block calls it.
 // GATHER (gate/up only): the activation rows are fetched straight from a token-indexed matrix (x itself,
 // or the tokens' FP4 codes and scales) through row_to_assign, so no permuted copy has to be written.
@@ -411,6 +417,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     const int kd = p.K >> 7;                              // FP4: scale dwords per row
 
     // ---- consumer side: fragment offsets inside a stage
+    constexpr bool TURNS = kTurns<FP4, MT>;
     const int sw = (li >> 1) & 7;
     const int f_off0 = li * KB + ((half ^ sw) << 4);       // slice s reads part 2s+half: offset f_off0 ^ (s << 5)
     const int a_base = wm * (32 * MT) * KB;
@@ -432,10 +439,13 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     // Weights: LDS position R holds weight-tile row (R & ~31) | w_row_of_lane(R & 31), which for
     // R & 31 = 8*j + prow is 16*((prow>>2)&1) + 4*j + (prow&3): instruction j is 4*j rows below
     // instruction 0, a scalar offset.  Per lane only the two part offsets differ (by parity of j).
+    // (TURNS: w_row_of_slot16, that is 16*(j&1) + 4*(j>>1) + 8*(prow>>2) + (prow&3).)
+    auto w_below = [&](int j) __attribute__((always_inline)) { return TURNS ? 16 * (j & 1) + 4 * (j >> 1) : 4 * j; };
     uint32_t b_voff[2];
     {
         // (a wave's first 8-row group is the g-th of a 32-row group, g = wave * OPS_W mod 4)
-        const int br0 = (wave * G::OPS_W >> 2) * 32 + (wave * G::OPS_W & 3) * 4 + (((prow >> 2) & 1) << 4) + (prow & 3);
+        const int br0 = TURNS ? wave * 32 + w_row_of_slot16(prow)
+                              : (wave * G::OPS_W >> 2) * 32 + (wave * G::OPS_W & 3) * 4 + (((prow >> 2) & 1) << 4) + (prow & 3);
 #pragma unroll
         for (int q = 0; q < 2; ++q) b_voff[q] = (uint32_t)w_tile_row<GATEUP, TW / 2>(br0, 0, I_up) * rowbytes + part16(q);
     }
@@ -510,7 +520,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
                 else v = (uint32_t)min(wave * (8 * MT) + j * 8 + prow, a_last) * rowbytes + part16(part_a(j));   // rows past the segment: its last row again
                 lds_dma16(a_tile + (v + koff), l);
             } else {
-                lds_dma16(b_tile + (size_t)(j * 4) * rowbytes + (b_voff[q] + koff), l + G::REGION_W + (wave * G::OPS_W + j) * 1024);
+                lds_dma16(b_tile + (size_t)w_below(j) * rowbytes + (b_voff[q] + koff), l + G::REGION_W + (wave * G::OPS_W + j) * 1024);
             }
         }
     };
@@ -557,7 +567,16 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 #pragma unroll
     for (int q = 1; q < G::NS - 1; ++q) { step_forward(); issue_step(pk, q); }
     step_forward();
-    if constexpr (TW < 256) {
+    // transfers from .. to-1 of a step (no scales), activations first
+    auto issue_some = [&](int from, int to, int k, int dstg) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = from; i < to; ++i) issue(i < G::OPS_A ? 2 + i : 6 + i - G::OPS_A, k, dstg);
+    };
+    constexpr int EARLY = 4;                                             // TURNS: transfers of a step that go out in the step that frees its stage
+    if constexpr (TURNS) {
+        issue_some(0, EARLY, pk, G::NS - 1);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 2) * OPS + EARLY) : "memory");
+    } else if constexpr (TW < 256) {
         issue_step(pk, G::NS - 1);
         asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((G::NS - 1) * OPS) : "memory");
     } else {
@@ -577,28 +596,45 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     //     slice, so every transfer has a whole step to land before the barrier that publishes it.
     int stg = 0, left = G::NS - 1;                        // stage of the current step, stage of the step before it
     int ks = 0, ck = k_start<FP4, GATEUP>(ti.n0, nks);          // steps of the tile multiplied so far, K-step being multiplied
-    v16f_t acc[MT][2];
+    v16f_t acc[TURNS ? 1 : MT][2];                        // 32 x 32 tiles
+    v4f_t acc16[TURNS ? MT : 1][2][4];                    // TURNS: 16 x 16 tiles, in pairs of row tiles
+    auto clear = [&]() __attribute__((always_inline)) {
+        if constexpr (TURNS) {
 #pragma unroll
-    for (int i = 0; i < MT; ++i)
+            for (int i = 0; i < 2 * MT; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < 4; ++j) acc16[i / 2][i % 2][j] = v4f_t{0.f, 0.f, 0.f, 0.f};
+        } else {
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        }
+    };
+    clear();
     int cur_row0 = ti.row0, cur_rows = ti.seg_hi - ti.row0, cur_n0 = ti.n0;
 
-    // Ends a tile: epilogue, accumulators back to zero, the block's next tile; false if there is none.
-    auto finish_tile = [&]() __attribute__((always_inline)) {
+    auto store16_tiles = [&](auto nt) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+            epilogue16<GATEUP, decltype(nt)::value>(p, acc16[mt], wm * (32 * MT) + mt * 32, cur_row0, cur_rows, cur_n0, wn, lane);
+    };
+    auto store_tile = [&]() __attribute__((always_inline)) {
         if (!multiplies || (!GATEUP && cur_n0 + wn * 64 >= p.n_out)) {}   // columns behind the output's end
+        else if constexpr (TURNS) {
+            if (nt_out) store16_tiles(std::true_type{});
+            else store16_tiles(std::false_type{});
+        }
         else if (nt_out) epilogue<FP4, GATEUP, MT, 2, true>(p, acc, cur_row0, cur_rows, cur_n0, wm, wn, li, half);
         else epilogue<FP4, GATEUP, MT, 2, false>(p, acc, cur_row0, cur_rows, cur_n0, wm, wn, li, half);
+    };
+    // Accumulators back to zero, the block's next tile; false if there is none.
+    auto next_tile = [&]() __attribute__((always_inline)) {
         tile += nslots;
         if (tile >= tile_hi) return false;
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+        clear();
         ti = decode(tile);
         cur_row0 = ti.row0; cur_rows = ti.seg_hi - ti.row0; cur_n0 = ti.n0;
         ks = 0;
@@ -661,9 +697,106 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
             }
             ++ks;
             if constexpr (STARTS) ck = ck + 1 == nks ? 0 : ck + 1;
-            return !last || finish_tile();
+            if (!last) return true;
+            store_tile();
+            return next_tile();
         };
         while (step(0) && step(1)) {}
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no transfer may still be writing this block's LDS when it ends
+        return;
+    }
+
+    if constexpr (TURNS) {
+        // The two waves of a SIMD take turns: waves 0..3 (rows wm = 0, one per SIMD) multiply while waves 4..7 read fragments and issue
+        // transfers, then the other way round, a barrier at each change; waves 4..7 are one change behind.  In the loop below,
+        // where all waves do the same at the same time, a wave that multiplies also blocks on its transfers (a CU takes one per 18-25
+        // cycles), and the step lasts as long as its MFMAs and half of its transfers one behind the other: 2900 cycles for 2048
+        // of MFMA.  Here a step is four turns per wave, each half the rows of a K-slice of 64 bytes: 16 MFMAs of 16 cycles.
+        //   section 0: fragments of slice 0 (weights, lower rows, upper rows), transfers   turn 0: slice 0, lower rows
+        //   section 1: fragments of slice 1 (weights, lower rows), transfers                turn 1: slice 0, upper rows
+        //   section 2: fragments of slice 1 (upper rows): the stage is read                 turn 2: slice 1, lower rows
+        //   section 3: transfers of the step after the next into that stage; the next step  turn 3: slice 1, upper rows
+        //              has landed
+        // Whole K-steps only (a BF16 row is a multiple of 128 bytes).  Measured with the 16 x 16 MFMA, 36 000 rows: gate/up K = 2048 345 -> 317
+        // us, down K = 1408 191 -> 177; 249 000 rows: K = 2048 1259 -> 1185, K = 768 807 -> 735 (with 32 x 32 MFMAs 340, 187, 1246, 757).  With
+        // operands of zeros, that is at the full clock, 297 -> 262: the rest is the power limit.  Sections that read one slice further
+        // ahead, transfers spread over 2, 3 or 4 sections, one turn per slice, and no turns but separate barriers for "read" and "landed": within 2 %, or slower.
+        constexpr int RS = MT;                             // 16-row tiles of a turn
+        constexpr int LGKM = 0xC07F;                       // s_waitcnt of the LDS counter alone (bits 8..11; no scalar load is in flight in the loop)
+        const int l16 = lane & 15, g = lane >> 4;
+        const int f_off = l16 * KB + ((g ^ (l16 >> 1)) << 4);            // slice s, part 4s + g: f_off ^ (s << 6)
+        u32x4_t xa[2][RS], xw[2][4];                       // [lower, upper rows], [slice]
+        auto fence = [&]() __attribute__((always_inline)) { __builtin_amdgcn_sched_barrier(0); };
+        auto barrier = [&]() __attribute__((always_inline)) { fence(); asm volatile("s_barrier" ::: "memory"); fence(); };
+        auto read_rows = [&](const uint8_t* st, int s, int h) __attribute__((always_inline)) {
+#pragma unroll
+            for (int i = 0; i < RS; ++i) xa[h][i] = *reinterpret_cast<const u32x4_t*>(st + a_base + (h * RS + i) * 16 * KB + (f_off ^ (s << 6)));
+        };
+        auto read_weights = [&](const uint8_t* st, int s) __attribute__((always_inline)) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) xw[s][t] = *reinterpret_cast<const u32x4_t*>(st + G::REGION_W + b_pos[t >> 1] * KB + (t & 1) * 16 * KB + (f_off ^ (s << 6)));
+        };
+        auto turn = [&](int s, int h) __attribute__((always_inline)) {
+            __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+            for (int i = 0; i < RS; ++i)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) mma16(acc16[(h * RS + i) / 2][(h * RS + i) % 2][t], xw[s][t], xa[h][i]);
+#pragma unroll
+            for (int i = 0; i < RS; ++i)                   // (the MFMAs stay in this turn instead of moving to where their results are used)
+#pragma unroll
+                for (int t = 0; t < 4; ++t) asm volatile("" : "+v"(acc16[(h * RS + i) / 2][(h * RS + i) % 2][t]));
+            __builtin_amdgcn_s_setprio(0);
+        };
+        __builtin_amdgcn_s_waitcnt(LGKM);
+        if (wm) barrier();
+        while (true) {
+            const bool last = ks == nks - 1;
+            const uint8_t* st = smem + stg * G::STAGE;
+            read_weights(st, 0);
+            read_rows(st, 0, 0);
+            fence();
+            issue_some(EARLY, EARLY + 2, pk, left);
+            fence();
+            read_rows(st, 0, 1);
+            fence();
+            __builtin_amdgcn_s_waitcnt(LGKM | RS << 8);    // all but the upper rows
+            barrier();
+            turn(0, 0);
+            barrier();
+            read_weights(st, 1);
+            read_rows(st, 1, 0);
+            fence();
+            issue_some(EARLY + 2, OPS, pk, left);
+            __builtin_amdgcn_s_waitcnt(LGKM | (4 + RS) << 8);            // slice 0
+            barrier();
+            turn(0, 1);
+            barrier();
+            read_rows(st, 1, 1);
+            fence();
+            __builtin_amdgcn_s_waitcnt(LGKM);
+            barrier();                                     // (waves 4..7 come to it one turn later: then the stage is free)
+            turn(1, 0);
+            barrier();
+            left = stg;
+            stg = stg + 1 == G::NS ? 0 : stg + 1;
+            advance();
+            fence();
+            issue_some(0, EARLY, pk, left);
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((G::NS - 2) * OPS + EARLY) : "memory");     // the next step, this wave's part
+            barrier();
+            turn(1, 1);
+            ++ks;
+            // Epilogue: both waves of a SIMD at the same time, between the same two barriers
+            if (!(last && wm)) barrier();
+            if (last) {
+                store_tile();
+                if (wm) barrier();
+                if (!next_tile()) break;
+                __builtin_amdgcn_s_waitcnt(LGKM);
+            }
+        }
+        if (!wm) barrier();
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no transfer may still be writing this block's LDS when it ends
         return;
     }
@@ -776,7 +909,10 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
         ++ks;
         if constexpr (STARTS) ck = ck + 1 == nks ? 0 : ck + 1;
-        if (last && !finish_tile()) break;
+        if (last) {
+            store_tile();
+            if (!next_tile()) break;
+        }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // no transfer may still be writing this block's LDS when it ends
 }

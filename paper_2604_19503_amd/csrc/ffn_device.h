@@ -18,6 +18,7 @@ inline void mark_used_on_device(std::atomic<unsigned long long>& seen, int devic
 
 typedef __attribute__((ext_vector_type(8))) int v8i_t;
 typedef __attribute__((ext_vector_type(16))) float v16f_t;
+typedef __attribute__((ext_vector_type(4))) float v4f_t;
 typedef __attribute__((ext_vector_type(8))) __bf16 v8bf_t;
 typedef __attribute__((ext_vector_type(2))) unsigned int u32x2_t;
 
@@ -68,6 +69,16 @@ __device__ __forceinline__ void mma(v16f_t& acc, const u32x4_t& w, const u32x4_t
     }
 }
 
+// The same for BF16 on 16 x 16 tiles: 16 weight rows x 16 activation rows over 64 bytes of K.  Lane l feeds the 16 bytes of part l/16
+// of row l%16 of either operand and gets output element (weight row 4*(l/16) + r, activation row l%16) in register r.  Its sums
+// are those of the 32 x 32 form bit for bit.  What it is for: large products are held back by power, and for the same
+// products this form moves half as many accumulators through the register file.  Registers only, random operands, sustained:
+// 2041 against 1822 TFLOP/s (operands of zeros: 2405 / 2424).  FP4 has such a form too (7360 against 6700), but a wave alone
+// issues its scaled MFMA only every 20 cycles instead of 16 and needs more work per scale: FP4 gate/up 122 -> 138 us.
+__device__ __forceinline__ void mma16(v4f_t& acc, const u32x4_t& w, const u32x4_t& x) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf_t, w), __builtin_bit_cast(v8bf_t, x), acc, 0, 0, 0);
+}
+
 // two floats -> two BF16 (nearest even) in one dword, first in the low half
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf2;
@@ -88,6 +99,10 @@ __device__ __forceinline__ int w_tile_row(int br, int n0, int I_up) {
 __device__ __forceinline__ int w_slot(int br) { return (br & ~31) | (((br >> 2) & 3) << 3) | (((br >> 4) & 1) << 2) | (br & 3); }
 // inverse: the weight-tile row that lane li (slot li) feeds to the MFMA
 __device__ __forceinline__ int w_row_of_lane(int li) { return (((li >> 2) & 1) << 4) | ((li >> 3) << 2) | (li & 3); }
+
+// The order for 16 x 16 tiles, of which two neighbouring ones make a group of 32 rows: the weight-tile row in slot 16a + 4g + q is
+// 8g + 4a + q, so that MFMA output rows 4g + q of the tiles a = 0, 1 -- lane group g, register q -- are 8 consecutive ones.
+__device__ __forceinline__ int w_row_of_slot16(int slot) { return (((slot >> 2) & 3) << 3) | (((slot >> 4) & 1) << 2) | (slot & 3); }
 
 // K-step (128 bytes of every operand row) at which the sum of an output column starts; from there it runs to the row's end and
 // on from the row's front.
@@ -242,6 +257,56 @@ __device__ __forceinline__ void epilogue_mt(const GemmParams& p, v16f_t (&a)[WN]
             store_tile_pair<NT>(p.out + ((size_t)(row0 + tile_row0) * p.n_out + col0) * 2, (size_t)p.n_out * 2, lane,
                                 rows_valid - tile_row0, lo8(t), hi8(t), lo8(t + 1), hi8(t + 1));
         }
+    }
+}
+
+// The same for 32 rows of BF16 on 16 x 16 tiles: a[i][c][r] belongs to activation row tile_row0 + 16*i + lane%16 of the block tile
+// and to weight row 8*(lane/16) + 4*(c&1) + r of the wave's group c/2 of 32 weight rows (gate/up: gate rows, up rows).
+template <bool GATEUP, bool NT>
+__device__ __forceinline__ void epilogue16(const GemmParams& p, const v4f_t (&a)[2][4], int tile_row0, int row0, int rows_valid, int n0, int wn, int lane) {
+    // 8 columns of either tile's row per lane -> 16 columns of row lane%32 of the pair, half lane/32 (c0, c1), as the stores want
+    // them: four lanes 16 apart that write one row's 64 bytes do not count as contiguous (down GEMM of 249 000 rows 740 -> 855 us)
+    auto side_by_side = [&](const u32x4_t& v0, const u32x4_t& v1, u32x4_t& c0, u32x4_t& c1) __attribute__((always_inline)) {
+        const uint32_t a0[4] = {v0.x, v0.y, v0.z, v0.w}, a1[4] = {v1.x, v1.y, v1.z, v1.w};
+        uint32_t r0[4], r1[4];
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            const auto t = __builtin_amdgcn_permlane16_swap(a0[d], a1[d], false, false);
+            r0[d] = t[0];
+            r1[d] = t[1];
+        }
+        c0 = u32x4_t{r0[0], r0[1], r0[2], r0[3]};
+        c1 = u32x4_t{r1[0], r1[1], r1[2], r1[3]};
+    };
+    if constexpr (GATEUP) {
+        u32x4_t h[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            uint32_t hb[4];                            // columns 8*(lane/16) + 2*q, 2*q + 1
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float g0 = a[i][q >> 1][(q & 1) * 2], u0 = a[i][2 + (q >> 1)][(q & 1) * 2];
+                const float g1 = a[i][q >> 1][(q & 1) * 2 + 1], u1 = a[i][2 + (q >> 1)][(q & 1) * 2 + 1];
+                hb[q] = pack_bf16x2(g0 * u0 * __builtin_amdgcn_rcpf(1.0f + __expf(-g0)),
+                                    g1 * u1 * __builtin_amdgcn_rcpf(1.0f + __expf(-g1)));
+            }
+            h[i] = u32x4_t{hb[0], hb[1], hb[2], hb[3]};
+        }
+        u32x4_t c0, c1;
+        side_by_side(h[0], h[1], c0, c1);
+        store_tile_rows<NT>(p.out + ((size_t)(row0 + tile_row0) * p.n_out + n0 + wn * 32) * 2, (size_t)p.n_out * 2, lane, rows_valid - tile_row0, c0, c1);
+    } else {
+        u32x4_t c[2][2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            auto packed = [&](int i) __attribute__((always_inline)) {
+                const v4f_t lo = a[i][2 * t], hi = a[i][2 * t + 1];
+                return u32x4_t{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3])};
+            };
+            side_by_side(packed(0), packed(1), c[t][0], c[t][1]);
+        }
+        store_tile_pair<NT>(p.out + ((size_t)(row0 + tile_row0) * p.n_out + n0 + wn * 64) * 2, (size_t)p.n_out * 2, lane, rows_valid - tile_row0,
+                            c[0][0], c[0][1], c[1][0], c[1][1]);
     }
 }
 

@@ -457,6 +457,43 @@ def test_tile_shapes_give_the_same_rows(R, H, I, segments):
     ctx.close()
 
 
+@pytest.mark.parametrize("K,segments", [(128, [1, 16, 17, 0, 33]), (256, [191, 192, 193, 0, 1]), (384, [255, 256, 257, 80, 15]), (2048, [385, 511, 0, 513, 2])])
+def test_bf16_tiles_of_16_by_16_sum_like_those_of_32_by_32(R, K, segments):
+    """BF16 tiles of 192 and 256 rows multiply in 16 x 16 tiles, all others in 32 x 32: the same h and the same y, bit for bit, on operands
+    whose magnitudes span 24 binades along K, where another order of the FP32 sums shows; segments at the edges of 16-row, 192-row and
+    256-row tiles, from the fewest K-steps (2) on."""
+    from paper_2604_19503_amd.binding import default_config, set_gemm_tile
+    nl, rows = len(segments), sum(segments)
+    rcfg = default_config(rows, nl, 1, 1, K, K)
+    ctx = R.Context(rcfg)
+    b = R.LayerBuffers(rcfg, rows)
+    gen = torch.Generator(device="cuda"); gen.manual_seed(K)
+    rnd = lambda std, *shape: torch.randn(shape, generator=gen, device="cuda") * std
+    spread = lambda *shape: torch.exp2(torch.randint(-12, 13, shape, generator=gen, device="cuda").float())
+    x = (rnd(1.0, rows, K) * spread(rows, K)).to(torch.bfloat16)
+    w13, w2 = rnd(2.0 ** -9 / K ** 0.5, nl, 2 * K, K).to(torch.bfloat16), (rnd(0.02, nl, K, K) * spread(nl, 1, K)).to(torch.bfloat16)
+    b.expert_offsets.copy_(torch.from_numpy(np.concatenate([[0], np.cumsum(segments)]).astype(np.int32)))
+    b.x_perm[:rows].copy_(x)
+    ref = None
+    for tile, shape in ((2, 0), (16, 0), (0, 3), (0, 2)):
+        _say(f"16 x 16 tiles K={K} tile={tile} shape={shape}")
+        b.y_rows.fill_(float("nan")); b.h_mid.zero_()
+        try:
+            set_gemm_tile(tile)
+            ctx.set_gemm_tile_shape(shape)
+            ctx.grouped_moe_ffn(R.BF16, w13, w2, b)
+            _sync()
+        finally:
+            set_gemm_tile(0)
+            ctx.set_gemm_tile_shape(0)
+        got = b.y_rows.view(torch.int16).clone(), b.h_mid.view(torch.int16).clone()
+        if ref is None:
+            ref = got
+            assert bool(torch.isfinite(b.y_rows[:rows].float()).all())
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1]), (tile, shape)
+    ctx.close()
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("I", [640, 768])               # FP4: 2.5 and 3 K-steps of the down GEMM
 def test_down_gemm_with_a_streamed_output_sums_in_the_order_of_a_small_one(R, I, prec):
