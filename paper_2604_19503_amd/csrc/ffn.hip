@@ -308,7 +308,7 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 //     an instruction, and eight waves issuing at once stall all MFMA issue) and keeps the producer a
 //     whole K-step ahead, so that no transfer is waited for;
 //   - is persistent: a block walks its XCD's tile range and its producer runs across tile boundaries
-//     (the expert table sits in LDS, so switching tiles touches no global memory); only the
+//     (the expert table sits in registers, so switching tiles touches no memory); only the
 //     register-only epilogue sits between two tiles' MFMA streams;
 //   - FP4: stages the E8M0 scales through LDS as well (global_load_lds_dword, 32 rows x 2 dwords
 //     per instruction), because one vector-memory instruction per lane-dword costs as much issue
@@ -346,8 +346,7 @@ struct TileGeo {
     static constexpr int SC_BASE = NS * STAGE;         // FP4: scale staging, per stage [TA + TW rows][2 dwords]
     static constexpr int SC_STAGE = (TA + TW) * 8;
     static constexpr int SC_W = TA * 8;
-    static constexpr int TAB_BASE = SC_BASE + NS * SC_STAGE;  // expert table, 3 x 64 ints
-    static constexpr int TOK_BASE = TAB_BASE + 3 * 64 * 4;    // gathering kernel: row_to_assign entries of a tile, two buffers x 8 waves x 64 ints
+    static constexpr int TOK_BASE = SC_BASE + NS * SC_STAGE;  // gathering kernel: row_to_assign entries of a tile, two buffers x 8 waves x 64 ints
     static constexpr int TOK_BUF = 8 * 64 * 4;
     static constexpr int LDS_BYTES = TOK_BASE + 2 * TOK_BUF;
 };
@@ -380,22 +379,22 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     // 100 tokens, 2000 and 5003: within 1 % either way.
     // Column tiles first for 256-row tiles (row tiles first, FP4 down GEMM of 249 000 rows: 304 -> 409 us) and FP4 (0.7 % faster).
     constexpr bool ROWS_FIRST = !FP4 && MT < 4;
-    // Expert table in LDS: entry e holds expert e's row segment and the inclusive prefix of row-tile
-    // counts (entries up to 63 repeat the total), so that decoding a tile index is one LDS read per
-    // lane, a ballot and three broadcast reads -- no global memory access between tiles.
-    int* tab = reinterpret_cast<int*>(smem + G::TAB_BASE);    // [0,64) prefix, [64,128) segment start, [128,192) segment end
+    // The expert table is in registers: lane e holds expert e's row segment and the inclusive prefix of row-tile counts (lanes from the
+    // last expert on repeat the total), so that decoding a tile index is a multiplication, a ballot and three lane reads.  (In LDS it
+    // was three dependent reads, for which every wave of the block stood still at each tile: see advance().)
     const int cum = wave_inclusive_scan(tiles_of<TA>(off_lo, off_hi));
     const int total = __builtin_amdgcn_readlane(cum, 63) * n_tiles_n;
-    __syncthreads();                                          // (a second phase: the first one's readers are done)
-    if (wave == 0) { tab[lane] = cum; tab[64 + lane] = off_lo; tab[128 + lane] = off_hi; }
-    __syncthreads();
+    __syncthreads();                                          // (a second phase: the first one's readers of the stages are done)
+    uint32_t nt_magic;
+    int nt_shift;
+    wide_magic(n_tiles_n, &nt_magic, &nt_shift);
     auto decode = [&](int t) __attribute__((always_inline)) {
-        const int mi = t / n_tiles_n, nt = t - mi * n_tiles_n;
-        const int e = __builtin_amdgcn_readfirstlane(__popcll(__ballot(tab[lane] <= mi)));   // experts that end at or before row tile mi
-        const int lo = __builtin_amdgcn_readfirstlane(tab[64 + e]), hi = __builtin_amdgcn_readfirstlane(tab[128 + e]);
-        const int first = e == 0 ? 0 : __builtin_amdgcn_readfirstlane(tab[e - 1]);
+        const int mi = div_by_magic(t, nt_magic, nt_shift), nt = t - mi * n_tiles_n;
+        const int e = __popcll(__ballot(cum <= mi));              // experts that end at or before row tile mi
+        const int lo = __builtin_amdgcn_readlane(off_lo, e), hi = __builtin_amdgcn_readlane(off_hi, e);
+        const int first = e == 0 ? 0 : __builtin_amdgcn_readlane(cum, e - 1);
         if constexpr (ROWS_FIRST) {
-            const int rows = __builtin_amdgcn_readfirstlane(tab[e]) - first, local = t - first * n_tiles_n;
+            const int rows = __builtin_amdgcn_readlane(cum, e) - first, local = t - first * n_tiles_n;
             int col = local;
             if (rows > 1) col = local / rows;                 // (decode steps: one row tile per expert, no second division)
             return TileInfo{e, lo + (local - col * rows) * TA, hi, col * COLS};

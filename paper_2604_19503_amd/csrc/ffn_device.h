@@ -57,6 +57,14 @@ __device__ __forceinline__ int div_by_magic(int a, uint32_t magic, int shift) {
     return (int)(((unsigned long long)(uint32_t)a * magic) >> shift);
 }
 
+// The same magic, on the device, for a wave-uniform 1 <= k < 2^15: floor(2^(31+s) / k) by two divisions of 31 bits.
+__device__ __forceinline__ void wide_magic(int k, uint32_t* magic, int* shift) {
+    const int s = k <= 1 ? 0 : 32 - __clz(k - 1);
+    const uint32_t q = 0x80000000u / (uint32_t)k, r = 0x80000000u - q * (uint32_t)k;      // 2^31 = q*k + r
+    *magic = (uint32_t)__builtin_amdgcn_readfirstlane((int)((q << s) + (r << s) / (uint32_t)k + 1));
+    *shift = 31 + s;
+}
+
 // acc += W_tile (A operand, 32 weight rows) x X_tile^T (B operand, 32 activation rows)
 template <bool FP4, int OPSEL>
 __device__ __forceinline__ void mma(v16f_t& acc, const u32x4_t& w, const u32x4_t& x, int sw, int sx) {
