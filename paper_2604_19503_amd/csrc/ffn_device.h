@@ -81,8 +81,8 @@ __device__ __forceinline__ void mma(v16f_t& acc, const u32x4_t& w, const u32x4_t
 // of row l%16 of either operand and gets output element (weight row 4*(l/16) + r, activation row l%16) in register r.  Its sums
 // are those of the 32 x 32 form bit for bit.  What it is for: large products are held back by power, and for the same
 // products this form moves half as many accumulators through the register file.  Registers only, random operands, sustained:
-// 2041 against 1822 TFLOP/s (operands of zeros: 2405 / 2424).  FP4 has such a form too (7360 against 6700), but a wave alone
-// issues its scaled MFMA only every 20 cycles instead of 16 and needs more work per scale: FP4 gate/up 122 -> 138 us.
+// 2041 against 1822 TFLOP/s (operands of zeros: 2405 / 2424).  FP4 has such a form too (7360 against 6700), but there a lane needs its
+// scale of each of twelve row tiles, not six, and with the loop that goes with it FP4 gate/up took 138 us instead of 122.
 __device__ __forceinline__ void mma16(v4f_t& acc, const u32x4_t& w, const u32x4_t& x) {
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf_t, w), __builtin_bit_cast(v8bf_t, x), acc, 0, 0, 0);
 }
@@ -156,14 +156,17 @@ __device__ __forceinline__ bool stream_output(const GemmParams& p) {
 // which the next kernel would otherwise read it back: worth it only for outputs too large to stay there.
 // Prepares the two store registers of store_tile_rows: ra = this lane's 16-byte piece of the even row of its
 // pair, rb = of the odd row.
+// (D = 2: the same between lanes two apart.)
+template <int D = 1>
 __device__ __forceinline__ void swap_halves(int lane, const u32x4_t& c0, const u32x4_t& c1, u32x4_t& ra, u32x4_t& rb) {
-    const bool odd = lane & 1;
+    constexpr int CTRL = D == 1 ? 0xB1 : 0x4E;             // quad_perm [1,0,3,2], [2,3,0,1]
+    const bool odd = lane & D;
     const uint32_t a0[4] = {c0.x, c0.y, c0.z, c0.w}, a1[4] = {c1.x, c1.y, c1.z, c1.w};
     uint32_t xa[4], xb[4];
 #pragma unroll
     for (int d = 0; d < 4; ++d) {
-        const uint32_t n0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)a0[d], 0xB1, 0xF, 0xF, true);   // the pair neighbour's c0
-        const uint32_t n1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)a1[d], 0xB1, 0xF, 0xF, true);   //                      c1
+        const uint32_t n0 = (uint32_t)__builtin_amdgcn_mov_dpp((int)a0[d], CTRL, 0xF, 0xF, true);   // the pair neighbour's c0
+        const uint32_t n1 = (uint32_t)__builtin_amdgcn_mov_dpp((int)a1[d], CTRL, 0xF, 0xF, true);   //                      c1
         xa[d] = odd ? n1 : a0[d];          // even row of the pair: even lane gives its c0, odd lane the even lane's c1
         xb[d] = odd ? a1[d] : n0;          // odd row of the pair:  even lane gives the odd lane's c0, odd lane its c1
     }
@@ -190,8 +193,10 @@ __device__ __forceinline__ void store_tile_rows(uint8_t* base, size_t row_pitch,
     store16<NT>(dst + row_pitch, rb, row_a + 1 < rows_left);
 }
 // Two neighbouring 32-column tiles of the same 32 rows (128 contiguous bytes per row).  The two 64-byte halves of
-// a row's line are written by consecutive instructions, so that they reach the memory side together (streamed
-// stores of half lines that arrive far apart cost extra write traffic).
+// a row's line are written by consecutive instructions, so that they reach the memory side together.
+// NT: non-temporal halves are not put together again on their way to memory, so a second swap, between lanes two apart, makes whole lines:
+// 8 rows x 128 bytes per instruction.  1 GB of such stores alone: 3.0 TB/s in halves, 5.1 TB/s in lines; in the down GEMM of 249 000 rows
+// (FP4, K = 768) 314 -> 277 us.  (Temporal stores: 6.2 TB/s in halves, 5.4 in lines, but they push the operands out of the L2: 339 us.)
 template <bool NT>
 __device__ __forceinline__ void store_tile_pair(uint8_t* base, size_t row_pitch, int lane, int rows_left, const u32x4_t& p0,
                                                 const u32x4_t& p1, const u32x4_t& q0, const u32x4_t& q1) {
@@ -199,12 +204,24 @@ __device__ __forceinline__ void store_tile_pair(uint8_t* base, size_t row_pitch,
     u32x4_t pa, pb, qa, qb;
     swap_halves(lane, p0, p1, pa, pb);
     swap_halves(lane, q0, q1, qa, qb);
-    const int row_a = li & ~1;
-    uint8_t* dst = base + (size_t)row_a * row_pitch + (half * 2 + (lane & 1)) * 16;
-    store16<NT>(dst, pa, row_a < rows_left);
-    store16<NT>(dst + 64, qa, row_a < rows_left);
-    store16<NT>(dst + row_pitch, pb, row_a + 1 < rows_left);
-    store16<NT>(dst + row_pitch + 64, qb, row_a + 1 < rows_left);
+    if constexpr (NT) {
+        u32x4_t r0, r1, r2, r3;
+        swap_halves<2>(lane, pa, qa, r0, r2);
+        swap_halves<2>(lane, pb, qb, r1, r3);
+        const int row = li & ~3;
+        uint8_t* dst = base + (size_t)row * row_pitch + ((lane & 2) * 2 + half * 2 + (lane & 1)) * 16;
+        store16<NT>(dst, r0, row < rows_left);
+        store16<NT>(dst + row_pitch, r1, row + 1 < rows_left);
+        store16<NT>(dst + 2 * row_pitch, r2, row + 2 < rows_left);
+        store16<NT>(dst + 3 * row_pitch, r3, row + 3 < rows_left);
+    } else {
+        const int row_a = li & ~1;
+        uint8_t* dst = base + (size_t)row_a * row_pitch + (half * 2 + (lane & 1)) * 16;
+        store16<NT>(dst, pa, row_a < rows_left);
+        store16<NT>(dst + 64, qa, row_a < rows_left);
+        store16<NT>(dst + row_pitch, pb, row_a + 1 < rows_left);
+        store16<NT>(dst + row_pitch + 64, qb, row_a + 1 < rows_left);
+    }
 }
 
 // Epilogue of one 32-row tile of a wave, straight from registers.  a[t][r] belongs to activation row tile_row0 + li of the

@@ -542,6 +542,44 @@ def test_down_gemm_with_a_streamed_output_sums_in_the_order_of_a_small_one(R, I,
 
 
 @pytest.mark.parametrize("prec", [0, 1])
+def test_streamed_output_rows_at_the_ends_of_segments(R, prec):
+    """The whole-line stores of outputs above 160 MiB, which exchange pieces between the lanes of four rows: segments that end 1, 2 and 3
+    rows into such a group, the first and last rows of each against the same rows as a small batch (other stores), bit for bit."""
+    from paper_2604_19503_amd.binding import default_config
+    H, I, segments = 2048, 128, [20001, 1, 20003, 2, 1026]
+    nl, rows, n = len(segments), sum(segments), 70
+    assert rows * H * 2 > (160 << 20)
+    rcfg = default_config(rows, nl, 1, 1, H, I)
+    ctx = R.Context(rcfg)
+    b = R.LayerBuffers(rcfg, rows)
+    gen = torch.Generator(device="cuda"); gen.manual_seed(7 + prec)
+    rnd = lambda std, *shape: (torch.randn(shape, generator=gen, device="cuda") * std).to(torch.bfloat16)
+    w13, w2, h = torch.zeros((nl, 2 * I, H), dtype=torch.bfloat16, device="cuda"), rnd(0.02, nl, H, I), rnd(1.0, rows, I)
+    ctx.quantize_experts_fp4(w13, w2, b)
+
+    def down(seg, src):
+        b.expert_offsets.copy_(torch.from_numpy(np.concatenate([[0], np.cumsum(seg)]).astype(np.int32)))
+        if prec == R.FP4:
+            q, s = R.quantize_rows_fp4(src)
+            b.h_mid.view(torch.uint8).view(-1)[:q.numel()].copy_(q.view(-1)); b.h_s.view(-1)[:s.numel()].copy_(s.view(-1))
+        else:
+            b.h_mid.view(torch.bfloat16).view(-1)[:src.numel()].copy_(src.reshape(-1))
+        b.y_rows.fill_(float("nan"))
+        ctx.grouped_moe_ffn_down(prec, w2, b)
+        _sync()
+        return b.y_rows[:src.shape[0]].view(torch.int16).clone()
+
+    _say(f"streamed segment ends prec={prec}")
+    got, lo = down(segments, h), 0
+    for e, size in enumerate(segments):
+        for at in sorted({lo, max(lo, lo + size - n)}):
+            m = min(n, lo + size - at)
+            assert torch.equal(down([m if i == e else 0 for i in range(nl)], h[at:at + m]), got[at:at + m]), (e, at)
+        lo += size
+    ctx.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("H,I", [(2048, 512), (512, 1536), (1152, 640), (1024, 1408)])     # pitches of 1 KB multiples and others, K odd and even
 def test_an_experts_rows_do_not_depend_on_its_slot_or_batch(R, H, I, prec):
     """The same expert and the same rows in every local slot, with segments from 1 row to several 256-row tiles, and alone in a
