@@ -140,10 +140,14 @@ struct TileInfo {
 };
 
 // BF16 outputs larger than what the memory-side cache would keep for the kernel that reads them next are
-// streamed past it with non-temporal stores (uniform per launch).
+// streamed past it with non-temporal stores (uniform per launch).  FP4 with K >= 1024: from 64 MiB on, since there keeping the
+// operands in the L2 is worth more than finding the output in the cache.  FP4 layer calls, limit 160 -> 64 MiB: K = 1408, 75 MB 174.1 -> 172.8
+// us, 110 MB 219.0 -> 219.1, 147 MB 275.0 -> 271.6; but K = 768, 127 MB 190.2 -> 191.9 (bound by its stores, which streamed are slower); BF16,
+// K = 1408, 147 MB 538 -> 543 us.
 __device__ __forceinline__ bool stream_output(const GemmParams& p) {
     const long long rows = __builtin_amdgcn_readfirstlane(p.offs[p.n_local]);
-    return rows * p.n_out * 2 > (160ll << 20);
+    const int limit_mib = p.As != nullptr && p.K >= 1024 ? 64 : 160;
+    return rows * p.n_out * 2 > ((long long)limit_mib << 20);
 }
 
 // Stores a 32-row x 32-column BF16 tile held as "lane (li, half) owns 16 consecutive columns of row li"
