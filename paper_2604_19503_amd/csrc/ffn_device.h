@@ -42,9 +42,11 @@ struct GemmParams {
     int start_seq;
     int tile_mode;           // direct-to-LDS kernel: 0 = tile shapes chosen on the device, 4 / 3 / 2 / 1 = 64 times that many rows of
                              //   256 weight rows, 5 = 64 x 128 tiles only
+    uint32_t col_magic[3];   // direct-to-LDS kernel: t / (column tiles) for tiles of 256, 128 and 64 weight rows, as src_magic.  From the host:
+    int col_shift[3];        //   two dependent divisions on the device stood in front of every block's first transfer
 };
 
-// Exact division of 0 <= a < 2^31 by a small constant k through one multiplication: with s = ceil(log2 k) and
+// Exact division of 0 <= a < 2^31 by a constant 1 <= k <= 2^30 through one multiplication: with s = ceil(log2 k) and
 // m = floor(2^(31+s) / k) + 1 < 2^32, the excess m*k - 2^(31+s) is at most k <= 2^s, so a*m / 2^(31+s) exceeds
 // a/k by less than 1/k and the floors agree.
 inline void division_magic(int k, uint32_t* magic, int* shift) {
@@ -55,14 +57,6 @@ inline void division_magic(int k, uint32_t* magic, int* shift) {
 }
 __device__ __forceinline__ int div_by_magic(int a, uint32_t magic, int shift) {
     return (int)(((unsigned long long)(uint32_t)a * magic) >> shift);
-}
-
-// The same magic, on the device, for a wave-uniform 1 <= k < 2^15: floor(2^(31+s) / k) by two divisions of 31 bits.
-__device__ __forceinline__ void wide_magic(int k, uint32_t* magic, int* shift) {
-    const int s = k <= 1 ? 0 : 32 - __clz(k - 1);
-    const uint32_t q = 0x80000000u / (uint32_t)k, r = 0x80000000u - q * (uint32_t)k;      // 2^31 = q*k + r
-    *magic = (uint32_t)__builtin_amdgcn_readfirstlane((int)((q << s) + (r << s) / (uint32_t)k + 1));
-    *shift = 31 + s;
 }
 
 // acc += W_tile (A operand, 32 weight rows) x X_tile^T (B operand, 32 activation rows)
