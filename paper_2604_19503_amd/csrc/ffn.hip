@@ -119,7 +119,7 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
     const int tile_hi = min(total, ((int)(blockIdx.x & 7) + 1) * per_xcd);
     int tile = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (tile >= tile_hi) return;
-    const bool nt_out = stream_output(p);
+    const bool nt_out = stream_output<FP4>(p);
 
     const int I_up = p.w_rows >> 1;                       // gate/up: offset of the up rows
     const size_t rowbytes = FP4 ? (size_t)(p.K >> 1) : (size_t)p.K * 2;
@@ -932,7 +932,7 @@ __device__ __forceinline__ void tile_body(const GemmParams& p, uint8_t* smem) {
     const int lane = threadIdx.x & 63;
     int lo = 0, hi = 0;
     if (lane < p.n_local) { lo = p.offs[lane]; hi = p.offs[lane + 1]; }
-    const bool nt_out = stream_output(p);
+    const bool nt_out = stream_output<FP4>(p);
     const int slots = gridDim.x;
     const int nt = GATEUP ? p.n_out / 128 : (p.n_out + 255) / 256;     // column tiles of 256 weight rows
     // Which rows go in 256-row tiles, and the shape of the tiles of the rest.
@@ -1145,6 +1145,7 @@ static int ffn_stages(realb_ctx* ctx, int prec, int stages, const int32_t* exper
     REALB_REQUIRE(h_mid && (!s1 || (x && w13)) && (!s2 || (w2 && y_rows)), REALB_EINVAL, "NULL argument");
     REALB_REQUIRE(prec == REALB_BF16 || (h_s && (!s1 || (x_s && w13_s)) && (!s2 || w2_s)), REALB_EINVAL,
                   "NULL scale tensor on the FP4 path");
+    if (prec == REALB_BF16) x_s = w13_s = w2_s = h_s = nullptr;      // ignored
     const int H = c->cfg.H, I = c->cfg.I;
     hipStream_t s = as_stream(stream);
     GemmParams g1{(const uint8_t*)x, x_s, (const uint8_t*)w13, w13_s, (uint8_t*)h_mid, h_s, expert_offsets, n_local, H, 2 * I, I, 0, nullptr, 0, 0, nullptr, 0, 0};

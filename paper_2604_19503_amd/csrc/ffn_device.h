@@ -138,9 +138,10 @@ struct TileInfo {
 // operands in the L2 is worth more than finding the output in the cache.  FP4 layer calls, limit 160 -> 64 MiB: K = 1408, 75 MB 174.1 -> 172.8
 // us, 110 MB 219.0 -> 219.1, 147 MB 275.0 -> 271.6; but K = 768, 127 MB 190.2 -> 191.9 (bound by its stores, which streamed are slower); BF16,
 // K = 1408, 147 MB 538 -> 543 us.
+template <bool FP4>
 __device__ __forceinline__ bool stream_output(const GemmParams& p) {
     const long long rows = __builtin_amdgcn_readfirstlane(p.offs[p.n_local]);
-    const int limit_mib = p.As != nullptr && p.K >= 1024 ? 64 : 160;
+    const int limit_mib = FP4 && p.K >= 1024 ? 64 : 160;
     return rows * p.n_out * 2 > ((long long)limit_mib << 20);
 }
 

@@ -54,9 +54,13 @@ int __hipPopCallConfiguration(dim3_t* grid, dim3_t* block, size_t* lds, void** s
 int hipLaunchKernel(const void* f, dim3_t grid, dim3_t block, void** args, size_t lds, void* stream) {
     const char* name = "?";
     char line[512];
-    (void)args; (void)lds;
+    (void)lds;
     for (size_t i = 0; i < n_kernels; ++i) if (kernels[i].host == f) name = kernels[i].name;
-    snprintf(line, sizeof line, "launch %s grid %u block %u stream %p", name, grid.x, block.x, stream);
+    int n = snprintf(line, sizeof line, "launch %s grid %u block %u stream %p", name, grid.x, block.x, stream);
+    if (strstr(name, "ffn_") && n < (int)sizeof line) {      /* a GEMM: its parameters begin with the six operands */
+        void* const* o = (void* const*)args[0];
+        snprintf(line + n, sizeof line - n, " operands %p %p %p %p %p %p", o[0], o[1], o[2], o[3], o[4], o[5]);
+    }
     record(line);
     /* the runtime's limit: fewer than 2^32 threads in a grid */
     if ((uint64_t)grid.x * block.x >= (1ull << 32) || (failing[0] && strstr(name, failing))) last_error = 9;

@@ -31,6 +31,10 @@ class Host:
         self.lib.realb_rank_forward.argtypes = [vp, vp, C.c_int, vp]
         self.lib.realb_prefetch_join.argtypes = [vp, vp]
         self.lib.realb_combine.argtypes = [vp, vp, vp, vp, C.c_int, vp, vp]
+        rows = [vp, C.c_int, vp, C.c_int, C.c_longlong]
+        self.lib.realb_grouped_moe_ffn.argtypes = rows + [vp] * 10
+        self.lib.realb_grouped_moe_ffn_gate_up.argtypes = rows + [vp] * 7
+        self.lib.realb_grouped_moe_ffn_down.argtypes = rows + [vp] * 6
         self.cfg = binding.default_config(T, E, k, D, H, I)
         self.ctx = vp()
         assert self.lib.realb_create(C.byref(self.cfg), C.byref(self.ctx)) == 0
@@ -155,6 +159,28 @@ def speculation_without_buffers(stub):
     return out, [len([c for c in calls if c[0] == "launch"]) for _, calls in (forced, plain)]
 
 
+def gemm_operands(stub):
+    """(entry point, kernel selector, precision, with scale tensors) -> the launches' kernels and operands (activations, their scales,
+    weights, their scales, output, its scales)."""
+    h = Host(stub)
+    offs, x, x_s, w13, w13_s, w2, w2_s, h_mid, h_s, y = (h.new() for _ in range(10))
+    out = []
+    for tile in (0, 2, 8, 16):
+        h.lib.realb_set_gemm_tile(tile)
+        for prec in (0, 1):
+            for scales in (True, False) if prec == 0 else (True,):
+                s = lambda t: t if scales else None
+                calls = {"": (x, s(x_s), w13, s(w13_s), w2, s(w2_s), h_mid, s(h_s), y, A),
+                         "_gate_up": (x, s(x_s), w13, s(w13_s), h_mid, s(h_s), A),
+                         "_down": (h_mid, s(h_s), w2, s(w2_s), y, A)}
+                for name, args in calls.items():
+                    h.stub.calls_clear()
+                    assert getattr(h.lib, "realb_grouped_moe_ffn" + name)(h.ctx, prec, offs, 8, 4096, *args) == 0
+                    lines = h.stub.calls_log().decode().splitlines()
+                    out.append([name, tile, prec, scales, [[l.split()[1], [_num(o) for o in l.split("operands ")[1].split()]] for l in lines]])
+    return [x_s, w13_s, w2_s, h_s], out
+
+
 def largest_grids(stub, T, H, force):
     """(return value, threads of the largest launch) of a rank call (force) or of combine alone (None)."""
     h = Host(stub, T=T, E=2, k=1, D=2, H=H)
@@ -215,6 +241,21 @@ def test_speculative_encoding_needs_its_buffers(stub):
     refused, launches = _run(stub, "speculation_without_buffers")
     assert refused == [[EINVAL, []], [EINVAL, []]]
     assert all(n > 0 for n in launches)
+
+
+def test_bf16_gemms_get_no_scale_tensors(stub):
+    """BF16 ignores the scale pointers: its kernels get the same operands whether a caller passes any or not (a kernel that took a
+    pointer to scales for the sign of FP4 would follow FP4's rules in BF16).  FP4's kernels get them all."""
+    scales, launches = _run(stub, "gemm_operands")
+    bf16 = {(name, tile, with_scales): l for name, tile, prec, with_scales, l in launches if prec == 0}
+    for name, tile, with_scales in bf16:
+        assert bf16[name, tile, with_scales] and bf16[name, tile, with_scales] == bf16[name, tile, False], (name, tile)
+        assert not any(o in scales for _, ops in bf16[name, tile, with_scales] for o in ops), (name, tile)
+    x_s, w13_s, w2_s, h_s = scales
+    for name, tile, prec, _, l in launches:
+        if prec == 1:
+            want = {"": [[x_s, w13_s, h_s], [h_s, w2_s, 0]], "_gate_up": [[x_s, w13_s, h_s]], "_down": [[h_s, w2_s, 0]]}[name]
+            assert [[ops[1], ops[3], ops[5]] for _, ops in l] == want, (name, tile)
 
 
 @pytest.mark.parametrize("T,H,force", [
