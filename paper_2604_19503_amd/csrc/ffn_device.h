@@ -133,15 +133,21 @@ struct TileInfo {
     int n0;       // first output column of the tile
 };
 
-// BF16 outputs larger than what the memory-side cache would keep for the kernel that reads them next are
-// streamed past it with non-temporal stores (uniform per launch).  FP4 with K >= 1024: from 64 MiB on, since there keeping the
-// operands in the L2 is worth more than finding the output in the cache.  FP4 layer calls, limit 160 -> 64 MiB: K = 1408, 75 MB 174.1 -> 172.8
-// us, 110 MB 219.0 -> 219.1, 147 MB 275.0 -> 271.6; but K = 768, 127 MB 190.2 -> 191.9 (bound by its stores, which streamed are slower); BF16,
-// K = 1408, 147 MB 538 -> 543 us.
+// BF16 outputs larger than what the memory-side cache would keep for the kernel that reads them next are streamed past it with
+// non-temporal stores (uniform per launch): from 160 MiB on, FP4 GEMMs with K >= 1024 from 136 MiB on.  Layer calls, FP4 limit 160 / 64 MiB,
+// H = 2048, us, with three sets of all buffers in turn, and with one set of buffers and three of weights and tokens; two boxes of the
+// same kind differ by 1 % in what the limit gives:
+//   K = 1408: 80 MiB 185.8 / 183.9, 178.5 / 179.0; 100 MiB 215.0 / 215.2, 211.6 / 213.1; 125 MiB 252.0 / 251.9, 248.8 / 250.3; 133 MiB 264.2 / 261.7,
+//             261.5 / 260.1; 141 MiB 279.6 / 275.1, 275.3 / 274.4; 150 MiB 288.5 / 285.1, 284.8 / 284.0
+//   K = 1024: 68 MiB 139.1 / 139.4, 134.0 / 135.4; 100 MiB 172.1 / 174.4, 170.4 / 173.4; 125 MiB 205.3 / 206.3, 203.9 / 205.8; 133 MiB 213.4 / 211.6,
+//             209.7 / 209.9; 141 MiB 225.0 / 220.5, 219.7 / 217.4; 150 MiB 232.2 / 227.3, 227.7 / 226.3
+//   K = 896:  141 MiB 205.3 / 202.5, 201.0 / 200.4;  K = 768: 141 MiB 190.1 / 187.7, 185.5 / 186.5; 158 MiB 205.0 / 205.2, 201.9 / 203.2
+//   K = 512, H = 1024: 145 MiB 160.8 / 161.3, 157.6 / 159.0;  BF16, K = 1408: 145 MiB 556.5 / 562.5, 558.5 / 559.1
+// H = 1024 (from 141 MiB on) and 4096 gain as H = 2048 does, 0 to 2.7 %.  Below the limits keeping the rows in the cache is as fast or up to 2 % faster.
 template <bool FP4>
 __device__ __forceinline__ bool stream_output(const GemmParams& p) {
     const long long rows = __builtin_amdgcn_readfirstlane(p.offs[p.n_local]);
-    const int limit_mib = FP4 && p.K >= 1024 ? 64 : 160;
+    const int limit_mib = FP4 && p.K >= 1024 ? 136 : 160;
     return rows * p.n_out * 2 > ((long long)limit_mib << 20);
 }
 
