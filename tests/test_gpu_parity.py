@@ -494,6 +494,93 @@ def test_bf16_tiles_of_16_by_16_sum_like_those_of_32_by_32(R, K, segments):
     ctx.close()
 
 
+def _spread_operands(rows, nl, H, I, seed):
+    """x, w13 and w2 whose magnitudes span 24 binades along K, where another order of the FP32 sums shows."""
+    gen = torch.Generator(device="cuda"); gen.manual_seed(seed)
+    rnd = lambda std, *shape: torch.randn(shape, generator=gen, device="cuda") * std
+    spread = lambda *shape: torch.exp2(torch.randint(-12, 13, shape, generator=gen, device="cuda").float())
+    return ((rnd(1.0, rows, H) * spread(rows, H)).to(torch.bfloat16), rnd(2.0 ** -9 / H ** 0.5, nl, 2 * I, H).to(torch.bfloat16),
+            (rnd(0.02, nl, H, I) * spread(nl, 1, I)).to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("H,I", [(128, 2048), (256, 2048), (4096, 128), (4096, 256)])       # 2 and 4 K-steps: of gate/up, of down
+def test_bf16_tiles_of_16_by_16_one_behind_the_other(R, H, I):
+    """Tiles of 192 and 256 rows where every block takes at least three: the epilogue between the barriers of a SIMD's two waves, the
+    change to the next tile and the producer that is in it already.  The same h and the same y, bit for bit, as the kernel that
+    multiplies in 32 x 32."""
+    from paper_2604_19503_amd.binding import default_config, set_gemm_tile
+    segments = [6001, 1, 0, 5003, 2500]
+    nl, rows = len(segments), sum(segments)
+    columns = I // 128 if I > H else H // 256
+    assert sum(-(-s // 256) for s in segments) * columns // 8 >= 3 * 32        # per XCD, on 32 blocks
+    rcfg = default_config(rows, nl, 1, 1, H, I)
+    ctx = R.Context(rcfg)
+    b = R.LayerBuffers(rcfg, rows)
+    x, w13, w2 = _spread_operands(rows, nl, H, I, H + I)
+    b.expert_offsets.copy_(torch.from_numpy(np.concatenate([[0], np.cumsum(segments)]).astype(np.int32)))
+    b.x_perm[:rows].copy_(x)
+    ref = None
+    for tile, shape in ((2, 0), (16, 0), (0, 3), (0, 0)):
+        _say(f"16 x 16 tiles one behind the other H={H} I={I} tile={tile} shape={shape}")
+        b.y_rows.fill_(float("nan")); b.h_mid.zero_()
+        try:
+            set_gemm_tile(tile)
+            ctx.set_gemm_tile_shape(shape)
+            ctx.grouped_moe_ffn(R.BF16, w13, w2, b)
+            _sync()
+        finally:
+            set_gemm_tile(0)
+            ctx.set_gemm_tile_shape(0)
+        got = b.y_rows.view(torch.int16).clone(), b.h_mid.view(torch.int16).clone()
+        if ref is None:
+            ref = got
+            assert bool(torch.isfinite(b.y_rows[:rows].float()).all())
+        assert torch.equal(got[1], ref[1]) and torch.equal(got[0], ref[0]), (tile, shape)
+    ctx.close()
+
+
+@pytest.mark.parametrize("H", [128, 256])
+def test_gathering_bf16_tiles_one_behind_the_other(R, H):
+    """The same for the layer call, whose gate/up GEMM fetches its rows through row_to_assign, the entries one tile ahead: four tiles of 256
+    rows per block, against the permuted rows in the kernel that multiplies in 32 x 32."""
+    from paper_2604_19503_amd.binding import default_config, set_gemm_tile
+    T, E, k, I = 8192, 8, 2, 2048
+    assert T * k // 256 * (I // 128) >= 4 * 256
+    rcfg = default_config(T, E, k, 1, H, I)
+    ctx = R.Context(rcfg)
+    b = R.LayerBuffers(rcfg, T)
+    x, w13, w2 = _spread_operands(T, E, H, I, H)
+    gen = torch.Generator(device="cuda"); gen.manual_seed(5)
+    logits = torch.randn((T, E), generator=gen, device="cuda")
+    logits[:, 0] += 1.0                                 # segments of different lengths
+    vis = torch.zeros(T, dtype=torch.uint8, device="cuda")
+    names = ("h_mid", "y_rows", "out")
+    ctx.route_stats(logits, vis, b)
+    ctx.permute(x, b, 0, R.BF16)
+    try:
+        set_gemm_tile(2)
+        ctx.grouped_moe_ffn(R.BF16, w13, w2, b)
+        _sync()
+    finally:
+        set_gemm_tile(0)
+    ctx.combine(b)
+    _sync()
+    assert int(b.expert_offsets[-1]) == T * k and bool(torch.isfinite(b.out.float()).all())
+    ref = [getattr(b, n).view(torch.int16).clone() for n in names]
+    for tile in (16, 0):
+        _say(f"gathering tiles one behind the other H={H} tile={tile}")
+        for n in names: getattr(b, n).fill_(float("nan"))
+        try:
+            set_gemm_tile(tile)
+            assert ctx.layer_forward(ctx.make_io(logits, vis, x, w13, w2, b, 0, force=R.BF16)) == R.BF16
+            _sync()
+        finally:
+            set_gemm_tile(0)
+        for n, want in zip(names, ref):
+            assert torch.equal(getattr(b, n).view(torch.int16), want), (tile, n)
+    ctx.close()
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("I", [640, 768])               # FP4: 2.5 and 3 K-steps of the down GEMM
 def test_down_gemm_with_a_streamed_output_sums_in_the_order_of_a_small_one(R, I, prec):
