@@ -4,18 +4,20 @@
 // v_mfma_f32_16x16x32_bf16), or MXFP4 operands (W4A4)
 // on the block-scaled v_mfma_scale_f32_32x32x64_f8f6f4.
 //
-// Both precisions share one kernel body because their tiles are byte-identical:
-// a K-step is 64 bytes of every operand row (32 BF16 or 128 FP4 values), made of
-// two MFMA K-slices of 32 bytes, and a lane's fragment is 16 contiguous bytes of
-// one row (8 BF16 values, or the 32 FP4 values of exactly one MX block, whose
-// E8M0 scale is therefore one byte per lane).
+// Both precisions share their tiles, which are byte-identical: a K-step is 64 bytes
+// of every operand row in the register-staged kernel (32 BF16 or 128 FP4 values) and
+// 128 in the direct-to-LDS one, made of MFMA K-slices of 32 bytes (16 x 16 MFMAs: 64),
+// and a lane's fragment is 16 contiguous bytes of one row (8 BF16 values, or the 32
+// FP4 values of exactly one MX block, whose E8M0 scale is therefore one byte per lane).
+// The K-loop is one code for both, but for the BF16 tiles of 192 and 256 rows.
 //
 // The MFMA runs "transposed": the weight rows are its A operand and the
 // activation rows its B operand, so a lane ends up with one activation row and
-// 16 weight rows.  The weight rows of a 32-row tile are stored in LDS in a
-// permuted order chosen so that those 16 are CONSECUTIVE output columns
-// (columns 16*half .. 16*half+15 of the tile, half = lane/32).  The epilogues
-// therefore need no LDS and no barrier:
+// 16 weight rows (16 x 16 MFMAs: two rows and 8 weight rows of either, which the
+// epilogue exchanges between lanes to the same).  The weight rows of a 32-row tile
+// are stored in LDS in a permuted order chosen so that those 16 are CONSECUTIVE
+// output columns (columns 16*half .. 16*half+15 of the tile, half = lane/32).  The
+// epilogues therefore need no LDS and no barrier:
 //   gate/up : a wave holds the gate and the up tile of the same 32 columns, so
 //             SwiGLU is element-wise in registers; h is rounded to BF16 and a
 //             lane stores 32 contiguous bytes, or -- FP4 path -- shares the
@@ -292,9 +294,9 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 // Tile kernel with direct-to-LDS loads (the default): 256 x 256 tiles for long expert segments, smaller shapes for short
 // ones and for what is left behind the last whole round of tiles.
 //
-// What bounds the 256 x 256 tiles on this chip is the path from L2 into the CU, not the MFMA rate:
-// a CU takes in about one 1-KB vector-memory instruction per 18-26 cycles, and the vector L1
-// fetches whole 128-byte lines.  So this kernel
+// What bounds the 256 x 256 tiles on this chip is the path from L2 into the CU, not the MFMA rate (BF16 tiles of 192 and 256
+// rows, whose waves take turns so that transfers and MFMAs overlap: the power limit): a CU takes in about one 1-KB vector-memory
+// instruction per 18-26 cycles, and the vector L1 fetches whole 128-byte lines.  So this kernel
 //   - fetches 128 bytes of every operand row per K-step (a full line: 256 FP4 or 64 BF16 values,
 //     four MFMA K-slices), which halves the L2->L1 traffic of 64-byte steps;
 //   - uses a 256 x 256 block tile (8 waves of 128 x 64), the largest whose two 64-KB stages fit the
@@ -323,9 +325,10 @@ __global__ void __launch_bounds__(128 * WGN, MINB) ffn_gemm_kernel(const GemmPar
 //     eight steps in flight); four or two waves multiply, eight move data.
 // Measured, BF16, weights from HBM, gate/up + down us, 256-row tiles -> these: 24 tokens (61 rows) 49.9 + 27.8 -> 19.6 + 11.6;
 // 192 tokens 50.9 + 28.2 -> 22.5 + 13.2; 1 token 19 + 14 with 64 x 256 tiles -> 13.3 + 10.2; 1000 tokens (2169 rows) 56.5 + 30.7 -> 37 + 23.
-// With four sets of weights in turn, under the profiler: 1 token 14.5 + 10.4, 24 tokens 24.3 + 12.6 (170 MB read, 4.6 TB/s),
-// 1000 tokens 38.4 + 26.2.  A split of the contraction over the waves of a block with operands straight in registers (no LDS)
-// measured 34 + 18 at 24 tokens and was dropped.
+// With four sets of weights in turn, under the profiler: 1 token 14.6 + 10.6, 24 tokens 24.0 + 12.3 (170 MB read, 138 of them weights
+// and the rest K-steps that the producer fetches behind a block's last tile: 3.8 TB/s of what is needed), 1000 tokens 37.9 + 26.1.
+// A split of the contraction over the waves of a block with operands straight in registers (no LDS) measured 34 + 18 at 24 tokens and
+// was dropped.
 // The accumulation order along K is the same for every shape and that of the other kernel, so results are bit-identical: a
 // row's result does not depend on the batch it is in.
 constexpr int KB = 128;                    // bytes of each operand row per K-step
@@ -380,8 +383,9 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     // Column tiles first for 256-row tiles (row tiles first, FP4 down GEMM of 249 000 rows: 304 -> 409 us) and FP4 (0.7 % faster).
     constexpr bool ROWS_FIRST = !FP4 && MT < 4;
     // The expert table is in registers: lane e holds expert e's row segment and the inclusive prefix of row-tile counts (lanes from the
-    // last expert on repeat the total), so that decoding a tile index is a multiplication, a ballot and three lane reads.  (In LDS it
-    // was three dependent reads, for which every wave of the block stood still at each tile: see advance().)
+    // last expert on repeat the total), so that decoding a tile index is a multiplication, a ballot and three lane reads (row tiles first: a
+    // fourth and, for experts of several row tiles, a division).  In LDS it was three dependent reads, for which every wave of the
+    // block stood still at each tile: see advance().
     const int cum = wave_inclusive_scan(tiles_of<TA>(off_lo, off_hi));
     const int total = __builtin_amdgcn_readlane(cum, 63) * n_tiles_n;
     __syncthreads();                                          // (a second phase: the first one's readers of the stages are done)
@@ -525,7 +529,8 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
     };
 
     // ---- producer position: the K-step it fetches next (pk of tile ptile).  Past the block's last tile
-    //      it keeps refetching that tile's steps, which nobody reads.
+    //      it keeps refetching that tile's steps, which nobody reads but the block waits for: with the 64 x 128 tiles of K = 2048
+    //      5 steps for 32, with the 64 x 64 tiles of K = 1408 8 for 22 (24 tokens: 107 + 63 MB read for 92 + 46 MB of weights).
     constexpr bool STARTS = kHasStarts<FP4, GATEUP>;          // (without them the counters pn and ck, which then equal pk and ks, are not kept)
     int ptile = tile, pn = 0, pk = k_start<FP4, GATEUP>(ti.n0, nks);      // pn: K-steps of the tile issued before this one
     auto advance = [&]() __attribute__((always_inline)) {
@@ -710,7 +715,7 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
         // transfers, then the other way round, a barrier at each change; waves 4..7 are one change behind.  In the loop below,
         // where all waves do the same at the same time, a wave that multiplies also blocks on its transfers (a CU takes one per 18-25
         // cycles), and the step lasts as long as its MFMAs and half of its transfers one behind the other: 2900 cycles for 2048
-        // of MFMA.  Here a step is four turns per wave, each half the rows of a K-slice of 64 bytes: 16 MFMAs of 16 cycles.
+        // of MFMA.  Here a step is four turns per wave, each half the rows of a K-slice of 64 bytes: 16 MFMAs of 16 cycles (192 rows: 12).
         //   section 0: fragments of slice 0 (weights, lower rows, upper rows), transfers   turn 0: slice 0, lower rows
         //   section 1: fragments of slice 1 (weights, lower rows), transfers                turn 1: slice 0, upper rows
         //   section 2: fragments of slice 1 (upper rows): the stage is read                 turn 2: slice 1, lower rows
@@ -918,10 +923,14 @@ __device__ __forceinline__ void tile_phase(const GemmParams& p, uint8_t* smem, c
 
 // Which tiles: the whole rounds of 256 x 256 tiles first (a round = one tile on every block; the 256-row tile costs the least
 // per row), then what is left in the smallest shape that still fits ONE round.  A last round of 256-row tiles lasts as long
-// as a full one, however empty it is; a round of 192-row tiles lasts 0.85 of it, 128-row tiles 0.6, 64-row tiles 0.4 (BF16,
-// K = 2048: 50, 43, 30 and 22 us).  Measured, BF16 gate/up: 13 162 rows 171 -> 149 us, 36 183 rows 377 -> 355 us; with the
-// 192-row tiles 3 548 rows 64.3 -> 58.0 us, FP4 20.6 -> 18.5 us.  With FP4 operands a round is 13 us and the second pipeline
-// start (3 us) eats what 192- or 128-row tiles would save behind whole rounds (50.6 -> 52.4 us), so there they are used only
+// as a full one, however empty it is; a round of 192-row tiles lasts 0.80 of it, 128-row tiles 0.63, 64-row tiles 0.41 (gate/up of 256 tiles,
+// K = 2048, BF16 53.9, 43.1, 33.7 and 22.3 us; FP4 22.4, 18.1, 14.2 and 10.3).  Measured against 256-row tiles alone, BF16 gate/up,
+// I = 1408: 3 548 rows (all in 192-row tiles) 47.5 -> 42.0 us, FP4 18.7 -> 17.5; 13 162 rows 140.8 -> 130.4, 36 183 rows 342.9 -> 331.0.
+// Against the best single shape the choice is within 3 % at most sizes; further off: BF16 5 000 rows gate/up 64.9 against 61.3 in 128-row
+// tiles, I = 768 1 000 rows down 13.6 / 11.9 (128), 10 000 rows down 40.3 / 36.2 (192); FP4 5 000 rows gate/up 27.8 / 23.7 (128), 7 500 rows
+// down 25.5 / 21.0 (128).
+// With FP4 operands the second pipeline start eats what 192- or 128-row tiles would save behind whole rounds (down of 11 000 rows,
+// K = 768, 19.7 -> 21.8 us, of 13 162 rows, K = 1408, 30.7 -> 32.8; gate/up between 4 % less and 3 % more), so there they are used only
 // when they hold all rows.  A block has at most one tile of a chosen small shape; forced to take
 // several, 64 x 128 tiles need at least four K-steps: their producer runs up to five steps ahead, and a tile's gather entries
 // are fetched one tile ahead.
@@ -1007,7 +1016,8 @@ static int raise_lds_limit(K kernel, std::atomic<unsigned long long>& seen, cons
     return REALB_OK;
 }
 
-// Column tiles per width, as divisors.  Layer calls, found on the device -> here: 24 tokens 43.2 -> 42.8 us, 1000 73.3 -> 72.7.
+// Column tiles per width, as divisors: exact for every width, and no division on the device (layer calls of 24 and 1000 tokens
+// against divisors found there: 1 % less at the most, which is what the runs of one side differ by).
 static void set_column_tiles(GemmParams& p, bool gate_up) {
     for (int i = 0; i < 3; ++i) {
         const int cols = (gate_up ? 128 : 256) >> i;                // output columns of a tile
